@@ -107,8 +107,9 @@ extern "C" {
 #define LJMD_TILE 64     /* atoms per neighbor-list tile: one wavefront */
 #define LJMD_MAX_TEAM 16 /* largest team (lanes per atom) of ljmd_compute_forces_csr */
 /* Tiled FULL-list forces (ljmd_compute_forces, ljmd_compute_forces_aosoa, the
- * fused steps) take four lanes per atom up to this many atoms (one 128-atom
- * block per compute unit), two beyond: the team size fixes the summation order. */
+ * fused steps) take four lanes per atom, which fixes their summation order.  HALF
+ * lists take eight lanes per atom up to this many atoms (one 128-atom block per
+ * compute unit), fewer beyond. */
 #define LJMD_SMALL_GRID_ATOMS 32768
 
 typedef struct {
@@ -218,8 +219,7 @@ int ljmd_build_neighbors_csr(const ljmd_box *box, double rlist, int kind, int64_
  * (truncated, unshifted; one absolute rc for every type pair).
  *   precision  LJMD_FP64 or LJMD_MIXED
  *   kind       list kind built by ljmd_build_neighbors.  FULL: a team of
- *              lanes per atom (four up to LJMD_SMALL_GRID_ATOMS atoms, else
- *              two), no atomics, bitwise deterministic.  HALF: Newton's third
+ *              four lanes per atom, no atomics, bitwise deterministic.  HALF: Newton's third
  *              law with FP64 atomic updates (summation order not fixed).
  *   ntypes     1..LJMD_MAX_TYPES; eps_packed/sigma_packed: device FP64
  *              [ntypes(ntypes+1)/2], upper triangle row-major:
@@ -360,7 +360,7 @@ int ljmd_md_step_noalloc(const ljmd_box *box, int precision, double rc, int32_t 
 /*
  * ljmd_md_step_chained -- ljmd_md_step without its own column-sum launch: the
  * step's energy/virial/kinetic partial rows (one per block) stay in half `half`
- * of ws, and the launch's first workgroup also sums the rows the previous
+ * of ws, and a workgroup of its own also sums the rows the previous
  * chained call left in the other half into ev_prev.  A run of steps alternates
  * half = 0, 1, 0, ... and so costs one launch per step; the sums of the last
  * step come from ljmd_md_step_sums.  Positions, velocities, forces and per-atom
@@ -373,7 +373,9 @@ int ljmd_md_step_noalloc(const ljmd_box *box, int precision, double rc, int32_t 
  *            other half is then not read).  The previous call must have had the
  *            same n and the other half, and must precede this one on the stream.
  *   ws       >= ljmd_workspace_bytes(LJMD_OP_MD_CHAIN, n, 0, ntypes), kept
- *            between the calls of a run
+ *            between the calls of a run, with the same ws_bytes in each (twice
+ *            ljmd_workspace_bytes(LJMD_OP_FORCES, ...) is also accepted, with the
+ *            same results; a small system then runs in fewer, larger blocks)
  * Other arguments as in ljmd_md_step.
  */
 int ljmd_md_step_chained(const ljmd_box *box, int precision, double rc, int32_t ntypes,
@@ -412,10 +414,9 @@ int ljmd_list_to_csr(int64_t n, const int32_t *nbr, const int32_t *nnbr, int32_t
  * (paper: Cabana's hierarchical neighbor traversal -- one thread per particle
  * or a team of threads per particle; "Parallel Loops").  Lane t of a team takes
  * row entries t, t + team, ...; the team's sums are combined in a fixed
- * butterfly order, so results are bitwise deterministic.  ljmd_compute_forces
- * walks a FULL tiled list with teams of four up to LJMD_SMALL_GRID_ATOMS atoms
- * and of two beyond; with the same team the forces and per-atom energies here
- * are bitwise those (E and W agree to rounding).
+ * butterfly order, so results are bitwise deterministic.  With a team of two or
+ * of four the forces and per-atom energies are bitwise those of
+ * ljmd_compute_forces over the FULL tiled list (E and W agree to rounding).
  *   team     1, 2, 4, 8 or 16
  *   offsets, csr  as produced by ljmd_list_to_csr (entries must be in [0, n))
  *   ws       >= ljmd_workspace_bytes(LJMD_OP_FORCES_CSR, n, 0, ntypes) when

@@ -24,6 +24,9 @@ int launch_build(const GridK &g, const BoxK &b, double rlist, int kind, int64_t 
                  int32_t *max_count, hipStream_t st);
 size_t force_workspace(int64_t n);
 int64_t force_workspace_atoms();
+size_t chain_workspace(int64_t n);
+int chain_atoms(int64_t n, size_t ws_bytes);
+size_t chain_half(int64_t n, size_t ws_bytes);
 int launch_forces(const BoxK &b, int precision, int kind, double rc, int32_t ntypes,
                   const double *eps, const double *sig, int64_t n, const double *x,
                   const int32_t *type, const int32_t *nbr, const int32_t *nnbr, int32_t maxn,
@@ -32,8 +35,9 @@ int launch_md_step(const BoxK &b, int precision, double rc, int32_t ntypes, cons
                    const double *sig, int64_t n, const double *x, const int32_t *type,
                    const int32_t *nbr, const int32_t *nnbr, int32_t maxn, double dt, double mass,
                    double *v, double *x_next, int open_next, double *F, double *e_atom, double *ev,
-                   double *partial, const double *prev_partial, double *prev_ev, hipStream_t st);
-int launch_md_step_sums(int64_t n, const double *partial, double *ev, hipStream_t st);
+                   double *partial, int atoms, const double *prev_partial, double *prev_ev,
+                   hipStream_t st);
+int launch_md_step_sums(int64_t n, int atoms, const double *partial, double *ev, hipStream_t st);
 int launch_forces_aosoa(const BoxK &b, int precision, double rc, int32_t ntypes, const double *eps,
                         const double *sig, int64_t n, int vlen, const double *x,
                         const int32_t *type, const int32_t *nbr, const int32_t *nnbr,
@@ -264,7 +268,7 @@ size_t ljmd_workspace_bytes(int op, int64_t n, int64_t ncells, int32_t ntypes) {
   switch (op) {
     case LJMD_OP_BIN: return bin_workspace(n, ncells > 0 ? ncells : 1);
     case LJMD_OP_FORCES: return force_workspace(n);
-    case LJMD_OP_MD_CHAIN: return 2 * force_workspace(n);
+    case LJMD_OP_MD_CHAIN: return 2 * chain_workspace(n);
     case LJMD_OP_BACKWARD:
       return bwd_workspace(n, ntypes < 1 ? 1 : (ntypes > LJMD_MAX_TYPES ? LJMD_MAX_TYPES : ntypes));
     case LJMD_OP_INTEGRATE:
@@ -559,7 +563,8 @@ int ljmd_md_step(const ljmd_box *box, int precision, double rc, int32_t ntypes,
   LJMD_TRY(check_ws(ws, ws_bytes, force_workspace(n)));
   return launch_md_step(make_box(box), precision, rc, ntypes, eps_packed, sigma_packed, n, x, type,
                         nbr, nnbr, maxn, dt, mass, v, x_next, open_next, F, e_atom, ev,
-                        (double *)ws, nullptr, nullptr, (hipStream_t)stream);
+                        (double *)ws, (int)force_workspace_atoms(), nullptr, nullptr,
+                        (hipStream_t)stream);
 }
 
 int ljmd_md_step_noalloc(const ljmd_box *box, int precision, double rc, int32_t ntypes,
@@ -581,7 +586,8 @@ int ljmd_md_step_noalloc(const ljmd_box *box, int precision, double rc, int32_t 
   LJMD_TRY(scratch_address(&rows));
   return launch_md_step(make_box(box), precision, rc, ntypes, eps_packed, sigma_packed, n, x, type,
                         nbr, nnbr, maxn, dt, mass, v, x_next, open_next, F, e_atom, ev,
-                        (double *)rows, nullptr, nullptr, (hipStream_t)stream);
+                        (double *)rows, (int)force_workspace_atoms(), nullptr, nullptr,
+                        (hipStream_t)stream);
 }
 
 int ljmd_md_step_chained(const ljmd_box *box, int precision, double rc, int32_t ntypes,
@@ -595,10 +601,11 @@ int ljmd_md_step_chained(const ljmd_box *box, int precision, double rc, int32_t 
   if (half != 0 && half != 1) return set_error(LJMD_EINVAL, "half = %d must be 0 or 1", half);
   LJMD_TRY(check_ws(ws, ws_bytes, 2 * force_workspace(n)));
   double *rows = (double *)ws;
-  const size_t h = force_workspace(n) / sizeof(double);
+  const size_t h = chain_half(n, ws_bytes);
   return launch_md_step(make_box(box), precision, rc, ntypes, eps_packed, sigma_packed, n, x, type,
                         nbr, nnbr, maxn, dt, mass, v, x_next, open_next, F, e_atom, nullptr,
-                        rows + half * h, rows + (1 - half) * h, ev_prev, (hipStream_t)stream);
+                        rows + half * h, chain_atoms(n, ws_bytes), rows + (1 - half) * h, ev_prev,
+                        (hipStream_t)stream);
 }
 
 int ljmd_md_step_sums(int64_t n, int half, const void *ws, size_t ws_bytes, double *ev,
@@ -607,8 +614,9 @@ int ljmd_md_step_sums(int64_t n, int half, const void *ws, size_t ws_bytes, doub
   if (half != 0 && half != 1) return set_error(LJMD_EINVAL, "half = %d must be 0 or 1", half);
   if (!ev) return set_error(LJMD_EINVAL, "ev is NULL");
   LJMD_TRY(check_ws(const_cast<void *>(ws), ws_bytes, 2 * force_workspace(n)));
-  const size_t h = force_workspace(n) / sizeof(double);
-  return launch_md_step_sums(n, (const double *)ws + half * h, ev, (hipStream_t)stream);
+  const size_t h = chain_half(n, ws_bytes);
+  return launch_md_step_sums(n, chain_atoms(n, ws_bytes), (const double *)ws + half * h, ev,
+                             (hipStream_t)stream);
 }
 
 int ljmd_force_backward(const ljmd_box *box, int precision, double rc, int32_t ntypes,

@@ -102,7 +102,7 @@ __global__ __launch_bounds__(kThreads * TEAM) void k_vjp(BwdArgs a) {
   constexpr int MT = LJMD_MAX_TYPES;
   constexpr int NW = kWaves * TEAM;  // wavefronts per block
   __shared__ double tab[(TT == 1 ? 1 : MT * MT) * 7];
-  __shared__ double red[NW * (TT == 0 ? 1 : 2 * TT * TT)];
+  __shared__ double red[kRedRows * NW * (TT == 0 ? 1 : 2 * TT * TT)];
   __shared__ double acc[TT == 0 ? kThreads * 2 * MT : 1];
   __shared__ int32_t tid_type[TT == 0 ? kThreads : 1];
   const int T = TT == 0 ? a.ntypes : TT;
@@ -253,14 +253,9 @@ __global__ __launch_bounds__(kThreads * TEAM) void k_vjp(BwdArgs a) {
       walk(std::false_type{});
     else
       walk(std::true_type{});
-    if constexpr (TEAM > 1) {
-#pragma unroll
-      for (int mask = TEAM / 2; mask > 0; mask >>= 1) {
-        ax += __shfl_xor(ax, mask, kWave);
-        ay += __shfl_xor(ay, mask, kWave);
-        az += __shfl_xor(az, mask, kWave);
-      }
-    }
+    ax = team_sum<TEAM>(ax);
+    ay = team_sum<TEAM>(ay);
+    az = team_sum<TEAM>(az);
     double *o = a.gx + 3 * (int64_t)i;
     if (tm != 0) {
       // the team's lead lane writes gx

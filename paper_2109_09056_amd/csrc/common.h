@@ -83,12 +83,6 @@ __device__ __forceinline__ double readlane_f64(double v, int src) {
   return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
 }
 
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int off = kWave / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, kWave);
-  return v;
-}
-
 __device__ __forceinline__ int wave_max(int v) {
 #pragma unroll
   for (int off = kWave / 2; off > 0; off >>= 1) {
@@ -98,24 +92,98 @@ __device__ __forceinline__ int wave_max(int v) {
   return v;
 }
 
-// Block of `NW` waves: sums NV values per thread into out[0..NV) for the
-// block, in a fixed order (wave tree, then waves 0..NW-1).  Every thread of
-// the block must call it.  `red` is __shared__ storage of NW*NV doubles.
-template <int NW, int NV>
-__device__ __forceinline__ void block_sum(const double (&v)[NV], double *red, double *out) {
-  const int lane = threadIdx.x & (kWave - 1);
-  const int w = threadIdx.x / kWave;
+// v of the lane that DPP control CTRL reads (quad_perm, row rotation, ...): two
+// VALU moves, where a shuffle through ds_bpermute would take two LDS round trips.
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double v) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const int lo = (int)(uint32_t)b, hi = (int)(uint32_t)(b >> 32);
+  const uint32_t l2 = (uint32_t)__builtin_amdgcn_mov_dpp(lo, CTRL, 0xf, 0xf, true);
+  const uint32_t h2 = (uint32_t)__builtin_amdgcn_mov_dpp(hi, CTRL, 0xf, 0xf, true);
+  return __builtin_bit_cast(double, ((uint64_t)h2 << 32) | l2);
+}
+constexpr int kDppXor1 = 0xB1;  // quad_perm [1, 0, 3, 2]
+constexpr int kDppXor2 = 0x4E;  // quad_perm [2, 3, 0, 1]
+constexpr int kDppRor4 = 0x124;  // row (16 lanes) rotated by 4
+constexpr int kDppRor8 = 0x128;  // by 8: lane ^ 8
+
+// v summed over the aligned group of TEAM lanes (TEAM a power of two up to
+// 16) by a butterfly, widest exchange first: both lanes of every exchange add
+// the same two numbers, so every lane ends with the same, order-fixed sum.
+template <int TEAM>
+__device__ __forceinline__ double team_sum(double v) {
+  static_assert(TEAM == 1 || TEAM == 2 || TEAM == 4 || TEAM == 8 || TEAM == 16, "team of lanes");
+  if constexpr (TEAM >= 16) v += dpp_f64<kDppRor8>(v);
+  if constexpr (TEAM >= 8) v += __shfl_xor(v, 4, kWave);
+  if constexpr (TEAM >= 4) v += dpp_f64<kDppXor2>(v);
+  if constexpr (TEAM >= 2) v += dpp_f64<kDppXor1>(v);
+  return v;
+}
+
+// Sums of NV (up to 8) values over each row of 16 lanes.  With P = NV rounded
+// up to a power of two, two exchanges inside the quad halve the values a lane
+// carries (lane bit 0 keeps the even or odd ones, bit 1 likewise), then the four
+// quads of the row are added: 8 values take 6 exchanged doubles and 10 adds per lane
+// instead of the 48 of a butterfly per value.  On return lane l < 16 of the
+// row's first min(P, 4) lanes holds columns l % 4, l % 4 + 4 in out[0], out[1].
+template <int NV>
+__device__ __forceinline__ void row_sums(const double (&v)[NV], double (&out)[2]) {
+  constexpr int P = NV > 4 ? 8 : (NV > 2 ? 4 : NV);
+  const bool b0 = threadIdx.x & 1, b1 = threadIdx.x & 2;
+  double a[P];
 #pragma unroll
-  for (int q = 0; q < NV; ++q) {
-    double s = wave_sum(v[q]);
-    if (lane == 0) red[w * NV + q] = s;
+  for (int q = 0; q < P; ++q) a[q] = q < NV ? v[q < NV ? q : 0] : 0.0;
+  constexpr int H = P > 1 ? P / 2 : 1;
+  double r[H];
+  if constexpr (P > 1) {
+#pragma unroll
+    for (int k = 0; k < H; ++k)
+      r[k] = (b0 ? a[2 * k + 1] : a[2 * k]) + dpp_f64<kDppXor1>(b0 ? a[2 * k] : a[2 * k + 1]);
+  } else {
+    r[0] = a[0] + dpp_f64<kDppXor1>(a[0]);
+  }
+  constexpr int G = H > 1 ? H / 2 : 1;
+#pragma unroll
+  for (int k = 0; k < G; ++k) {
+    double t;
+    if constexpr (H > 1)
+      t = (b1 ? r[2 * k + 1] : r[2 * k]) + dpp_f64<kDppXor2>(b1 ? r[2 * k] : r[2 * k + 1]);
+    else
+      t = r[k] + dpp_f64<kDppXor2>(r[k]);
+    t += dpp_f64<kDppRor4>(t);
+    out[k] = t + dpp_f64<kDppRor8>(t);
+  }
+}
+
+// Block of `NW` waves: sums NV (up to 8) values per thread into out[0..NV)
+// for the block, in a fixed order (rows of 16 lanes by row_sums, then the rows).
+// Every thread of the block must call it.  `red` is __shared__ storage of
+// kRedRows * NW * NV doubles.  HALVES = 2: the sum of the first half of the block's
+// rows plus the sum of the second, as two blocks of half the size would leave.
+constexpr int kRedRows = kWave / 16;
+template <int NW, int NV, int HALVES = 1>
+__device__ __forceinline__ void block_sum(const double (&v)[NV], double *red, double *out) {
+  constexpr int P = NV > 4 ? 8 : (NV > 2 ? 4 : NV);
+  constexpr int kRows = kRedRows * NW;
+  double s[2];
+  row_sums<NV>(v, s);
+  const int l = threadIdx.x & 15;
+  double *row = red + (threadIdx.x >> 4) * NV;
+  if (l < (P < 4 ? P : 4)) {
+    if (l < NV) row[l] = s[0];
+    if (P == 8 && l + 4 < NV) row[l + 4] = s[1];
   }
   __syncthreads();
   if (threadIdx.x < NV) {
-    double s = 0.0;
+    double t[HALVES];
 #pragma unroll
-    for (int k = 0; k < NW; ++k) s += red[k * NV + threadIdx.x];
-    out[threadIdx.x] = s;
+    for (int h = 0; h < HALVES; ++h) {
+      t[h] = 0.0;
+#pragma unroll
+      for (int k = 0; k < kRows / HALVES; ++k)
+        t[h] += red[(h * (kRows / HALVES) + k) * NV + threadIdx.x];
+    }
+    out[threadIdx.x] = HALVES == 2 ? t[0] + t[HALVES - 1] : t[0];
   }
 }
 
@@ -126,19 +194,28 @@ __device__ __forceinline__ void block_sum(const double (&v)[NV], double *red, do
 // t % stride; the THREADS/stride threads of a column are then added by a tree
 // in `part` (THREADS doubles of LDS).  Fixed order throughout; every thread of
 // the block calls it and part[0..stride) is visible to all of them on return.
-template <int THREADS>
+// PAIRS: the sums of the rows 2r and 2r + 1 (the second absent at an odd end) take
+// the place of the rows.
+template <int THREADS, bool PAIRS = false>
 __device__ __forceinline__ void colsum_lds(int64_t rows, int stride, const double *__restrict__ p,
                                            double *part) {
   const int t = threadIdx.x;
   double s = 0.0;
-  const int64_t total = rows * stride;
+  const int64_t all = rows * stride;
+  const int64_t total = PAIRS ? (rows + 1) / 2 * stride : all;
   constexpr int B = 16;  // loads in flight per thread
   for (int64_t f0 = t; f0 < total; f0 += (int64_t)B * THREADS) {
     double v[B];
 #pragma unroll
     for (int k = 0; k < B; ++k) {
       const int64_t f = f0 + (int64_t)k * THREADS;
-      v[k] = f < total ? p[f] : 0.0;
+      if constexpr (PAIRS) {
+        const int64_t g = 2 * f - (f & (stride - 1));  // row 2r, the same column
+        v[k] = f < total ? p[g] : 0.0;
+        if (g + stride < all) v[k] += p[g + stride];
+      } else {
+        v[k] = f < total ? p[f] : 0.0;
+      }
     }
 #pragma unroll
     for (int k = 0; k < B; ++k) s += v[k];
@@ -153,13 +230,13 @@ __device__ __forceinline__ void colsum_lds(int64_t rows, int stride, const doubl
 
 // One launch of colsum_lds: out[q] = scale * column q for q < ncols (+= when
 // accumulate).
-template <int THREADS>
+template <int THREADS, bool PAIRS = false>
 __global__ __launch_bounds__(THREADS) void k_colsum(int64_t rows, int stride, int ncols,
                                                    const double *__restrict__ p,
                                                    double *__restrict__ out, double scale,
                                                    int accumulate) {
   __shared__ double part[THREADS];
-  colsum_lds<THREADS>(rows, stride, p, part);
+  colsum_lds<THREADS, PAIRS>(rows, stride, p, part);
   const int t = threadIdx.x;
   if (t < ncols) out[t] = accumulate ? out[t] + scale * part[t] : scale * part[t];
 }

@@ -14,15 +14,14 @@
 // accumulation of F, e, E and W are FP64.  The pair energy u is taken in
 // FP64 from the FP32 reciprocal refined by one FP64 Newton step.
 //
-// FULL list: a team of lanes (two; four for grids of at most one block per
-// compute unit) owns atom i and walks its row of the tile (row k of lane l of
-// tile t at nbr[(t*maxn + k)*64 + l]; lane t of the team takes entries t,
-// t + team, ...); no atomics, fixed summation order, so the result is bitwise
-// reproducible.  HALF list: the owner adds s*d to F_i in
+// FULL list: a team of four lanes owns atom i and walks its row of the tile
+// (row k of lane l of tile t at nbr[(t*maxn + k)*64 + l]; lane t of the team
+// takes entries t, t + 4, ...); no atomics, fixed summation order, so the result
+// is bitwise reproducible.  HALF list: the owner adds s*d to F_i in
 // registers and subtracts it from F_j with FP64 hardware atomics.
 // Energy and virial: per-block partial sums in a fixed tree order, then one
-// column-sum launch (deterministic); in chained steps the first workgroup of
-// the next step's launch sums them instead.  Full lists take the virial as
+// column-sum launch (deterministic); in chained steps a workgroup of the next
+// step's launch sums them instead.  Full lists take the virial as
 // sum_i x_i (x) F_i plus the pairs that cross a box face (add_pair).
 #include <type_traits>
 
@@ -30,11 +29,19 @@
 
 namespace ljmd {
 
-constexpr int kForceThreads = 128;  // atoms per block of the tiled kernels
-constexpr int kForceWaves = kForceThreads / kWave;
+constexpr int kForceAtoms = 128;     // atoms per partial row of the full-list kernels
+constexpr int kHalfRowAtoms = 64;    // the small block: half of them
 constexpr int kCsrThreads = 256;    // threads per block of the CSR kernel (256 / team atoms)
 constexpr int kCsrWaves = kCsrThreads / kWave;
 constexpr int kEvStride = 8;  // partial row: E, Wxx, Wyy, Wzz, Wxy, Wxz, Wyz, pad
+// Full list: four lanes per atom, three slots per group and lane.  Four lanes of
+// one row gather from nearby addresses (consecutive entries are mostly nearby
+// atoms), so a gather instruction touches fewer cache lines.  Fused step at 500,000
+// atoms / two types at 256,000 (us): two lanes with 6 slots 86.7 / 62.3; four
+// lanes with 2, 3, 4, 5 slots 86.6 / 57.0, 83.2 / 55.8, 98.5 / 64.5, 101 / 66.4;
+// eight lanes with 3 slots 105 / 67.8.
+constexpr int kTeam = 4;
+constexpr int kSlots = 3;
 
 struct ForceArgs {
   BoxK b;
@@ -140,8 +147,8 @@ struct Acc {
   double wxx = 0.0, wyy = 0.0, wzz = 0.0, wxy = 0.0, wxz = 0.0, wyz = 0.0;
 };
 
-// One neighbor j of atom i: minimum image (WRAP), cutoff test, pair force and
-// the row's accumulators.  `valid` is false for padding slots of a short group.
+// One neighbor j (of type tj, read for T1 = false only) of atom i: minimum
+// image (WRAP), cutoff test, pair force and the row's accumulators.  `valid` is false for padding slots of a short group.
 //
 // Virial of the full list, W = 1/2 sum_i sum_j d_ij (x) f_ij with
 // d_ij = x_i - x_j + S_ij (S_ij = -k L, the minimum-image shift):
@@ -151,7 +158,7 @@ struct Acc {
 // S != 0), and every lane adds 2 x_i (x) (its part of F_i) once (add_xf).
 template <bool MIXED, bool T1, bool EV, bool WRAP>
 __device__ __forceinline__ void add_pair(const ForceArgs &a, double xi, double yi, double zi,
-                                         double xj, double yj, double zj, int32_t j, bool valid,
+                                         double xj, double yj, double zj, int32_t tj, bool valid,
                                          int ti, const Coef &c1, const double *tab, Acc &s) {
   double dx = xi - xj, dy = yi - yj, dz = zi - zj;
   double sx = 0.0, sy = 0.0, sz = 0.0;
@@ -172,7 +179,7 @@ __device__ __forceinline__ void add_pair(const ForceArgs &a, double xi, double y
     if constexpr (T1) {
       c = c1;
     } else {
-      const double *t = tab + 4 * (ti * a.ntypes + a.type[j]);
+      const double *t = tab + 4 * (ti * a.ntypes + tj);
       c = Coef{t[0], t[1], t[2], t[3]};
     }
     const PairOut p = lj_pair<MIXED, EV>(dx, dy, dz, r2, c);
@@ -254,57 +261,39 @@ __device__ __forceinline__ void load_pos(const double *x, int32_t j, int64_t n, 
   }
 }
 
-// Walk atom i's row in groups of U slots: the U index loads, then the U
-// position gathers, then the U pair evaluations, so several loads are in
-// flight per lane.  Whole groups read their indices at fixed offsets from one
-// row pointer (no per-slot address arithmetic); the last, partial group loads
-// indices and positions only for slots below cnt.
-// Slots are visited in row order, so the sums are the same as one slot at a
-// time.  STRIDE > 1: the lane owns every STRIDE-th entry of the row (row points
-// at its first one).  WRAP = false skips the minimum image; the caller only takes that
-// path when every atom of the wavefront is at least rc from all box faces,
-// where any pair closer than rc has the same raw and minimum-image
-// displacement, and any other pair has some |raw component| above L/2 > rc
-// and is rejected by the cutoff test either way.
-template <bool MIXED, bool T1, bool EV, int U, bool WRAP, bool WIDE, int STRIDE = 1, int V = 1>
+// Walk the lane's entries of atom i's row (every TEAM-th, row points at the first
+// of its cnt) in groups of U slots: the U index loads, then the U gathers of
+// position and type, then the U pair evaluations, so several loads are in flight
+// per lane.  Slots beyond cnt repeat the lane's first entry and are masked: one
+// copy of the group's code instead of a whole and a partial one (a short launch
+// spends most of its time fetching instructions).  The type is gathered with the
+// position rather than after the cutoff test: no second round trip (two types,
+// 256,000 atoms: fused step 69.0 -> 62.2 us).  Slots are visited in row order, so
+// the sums are the same as one slot at a time.  WRAP = false skips the minimum
+// image; the caller only takes that path when every atom of the wavefront is at
+// least rc from all box faces, where any pair closer than rc has the same raw and
+// minimum-image displacement, and any other pair has some |raw component| above
+// L/2 > rc and is rejected by the cutoff test either way.
+template <bool MIXED, bool T1, bool EV, int U, bool WRAP, bool WIDE, int TEAM, int V>
 __device__ __forceinline__ void walk_row(const ForceArgs &a, const int32_t *row, int32_t cnt,
                                          double xi, double yi, double zi, int ti,
                                          const Coef &c1, const double *tab, Acc &s) {
-  constexpr int kStep = STRIDE * kWave;  // ints between this lane's consecutive entries
-  const int32_t whole = cnt - cnt % U;
-  int32_t k = 0;
-  for (; k < whole; k += U, row += U * kStep) {
-    int32_t j[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) j[u] = row[u * kStep];
-    double xj[U], yj[U], zj[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      load_pos<V, WIDE>(a.x, j[u], a.n, xj[u], yj[u], zj[u]);
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-      add_pair<MIXED, T1, EV, WRAP>(a, xi, yi, zi, xj[u], yj[u], zj[u], j[u], true, ti, c1, tab,
-                                    s);
-  }
-  if (k < cnt) {
-    int32_t j[U];
+  constexpr int kStep = TEAM * kWave;  // ints between this lane's consecutive entries
+#pragma unroll 1
+  for (int32_t k = 0; k < cnt; k += U, row += U * kStep) {
+    int32_t j[U], tj[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) j[u] = row[(k + u < cnt ? u : 0) * kStep];
     double xj[U], yj[U], zj[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      xj[u] = xi;
-      yj[u] = yi;
-      zj[u] = zi;
-      if (k + u < cnt) {  // no gathers for the padding slots
-        load_pos<V, WIDE>(a.x, j[u], a.n, xj[u], yj[u], zj[u]);
-      }
+      load_pos<V, WIDE>(a.x, j[u], a.n, xj[u], yj[u], zj[u]);
+      tj[u] = T1 ? 0 : a.type[j[u]];
     }
 #pragma unroll
     for (int u = 0; u < U; ++u)
-      add_pair<MIXED, T1, EV, WRAP>(a, xi, yi, zi, xj[u], yj[u], zj[u], j[u], k + u < cnt, ti, c1,
-                                    tab, s);
+      add_pair<MIXED, T1, EV, WRAP>(a, xi, yi, zi, xj[u], yj[u], zj[u], tj[u], k + u < cnt, ti,
+                                    c1, tab, s);
   }
 }
 
@@ -320,8 +309,17 @@ __device__ __forceinline__ void walk_row(const ForceArgs &a, const int32_t *row,
 // step -- closing half kick (kinetic energy taken there), and when open_next
 // the next step's half kick, drift and wrap into x_next -- with exactly the
 // operations of ljmd_integrate, so the trajectory is bitwise the same as the
-// unfused calls; lane t handles components t, t + TEAM, ...  Partial rows
-// then carry the kinetic energy in column 7.
+// unfused calls; lane t < 3 handles component t (one pass of the code, its
+// velocity loaded ahead of the row).  Partial rows then carry the kinetic energy
+// in column 7.
+//
+// What bounds it: at 500,000 atoms the two gather instructions per list entry
+// (texture address unit); below about 30,000 atoms a launch is mostly
+// instruction-fetch and memory latency, so code executed once per block counts.
+// Fused step per launch, with two lanes per atom in whole and partial groups,
+// sums through ds_bpermute and the previous step's sums in block 0 -> now (us):
+// 256 atoms FP64 11.4 -> 6.7, 32,000 mixed 11.9 -> 9.0, 42,592 mixed 16.9 ->
+// 11.3, 256,000 two types FP64 71.4 -> 55.9, 500,000 mixed 89.5 -> 83.5.
 // Column sums of `rows` partial rows of kEvStride doubles by the THREADS threads
 // of one block, out[q] = sum_r p[r*kEvStride + q] for q < kEvStride: thread t
 // reads the flat array at t, t + THREADS, ... (column t % kEvStride), the lanes
@@ -358,18 +356,28 @@ __device__ void block_colsum(const double *__restrict__ p, int64_t rows, double 
   }
 }
 
-template <bool MIXED, bool T1, bool EV, int U, bool SKIP, bool STEP, bool WIDE, int TEAM,
-          int V = 1>
-__global__ __launch_bounds__(kForceThreads * TEAM) void k_force_full(ForceArgs a) {
+//
+// Rows of partial sums stand in the order of the atoms (row = logical block), and
+// a 128-atom block adds its two 64-atom halves last: its row is bitwise the sum of
+// the two rows of 64-atom blocks, so the block size never shows in a result.
+template <bool MIXED, bool T1, bool EV, bool STEP, bool WIDE, int ATOMS, int V = 1>
+__global__ __launch_bounds__(ATOMS * kTeam) void k_force_full(ForceArgs a) {
   static_assert(!STEP || V == 1, "the fused step works on [n][3] arrays");
+  static_assert(kTeam == 4, "one component per lane");
+  constexpr int kThreads = ATOMS * kTeam;
   __shared__ double tab[T1 ? 4 : 4 * LJMD_MAX_TYPES * LJMD_MAX_TYPES];
-  __shared__ double red[kForceWaves * TEAM * 8];
+  __shared__ double red[kRedRows * (kThreads / kWave) * 8];
+  int nblk = gridDim.x, blk = blockIdx.x;
   if constexpr (STEP) {
     // chained steps: the previous launch's partial rows are complete (stream
-    // order); block 0 is dispatched first, so its extra pass is off the tail
-    if (a.prev_ev && blockIdx.x == 0) {  // block-uniform
-      block_colsum<kForceThreads * TEAM>(a.prev_partial, a.prev_rows, a.prev_ev, red);
-      __syncthreads();  // `red` is read above and written again by block_sum
+    // order); a block of its own, dispatched first, sums them
+    if (a.prev_ev) {
+      if (blk == 0) {  // block-uniform
+        block_colsum<kThreads>(a.prev_partial, a.prev_rows, a.prev_ev, red);
+        return;
+      }
+      --nblk;
+      --blk;
     }
   }
   Coef c1{};
@@ -378,8 +386,9 @@ __global__ __launch_bounds__(kForceThreads * TEAM) void k_force_full(ForceArgs a
   } else {
     load_table(a, tab);
   }
-  const int t = (int)threadIdx.x % TEAM;
-  const int32_t i = xcd_block(blockIdx.x, gridDim.x) * kForceThreads + (int)threadIdx.x / TEAM;
+  const int t = (int)threadIdx.x % kTeam;
+  blk = xcd_block(blk, nblk);
+  const int32_t i = blk * ATOMS + (int)threadIdx.x / kTeam;
   Acc s;
   double ke = 0.0;
   const bool live = i < a.n;
@@ -389,74 +398,63 @@ __global__ __launch_bounds__(kForceThreads * TEAM) void k_force_full(ForceArgs a
     yi = a.x[aos_index<V>(i, 1, a.n)];
     zi = a.x[aos_index<V>(i, 2, a.n)];
   }
-  bool interior = false;
-  if constexpr (SKIP) {
-    const double m = a.rc;
-    const bool in = !live || (xi >= m && xi <= a.b.L[0] - m && yi >= m && yi <= a.b.L[1] - m &&
-                              zi >= m && zi <= a.b.L[2] - m);
-    interior = __ballot(!in) == 0;  // wavefront-uniform
+  double v0 = 0.0;
+  if constexpr (STEP) {
+    if (live && t < 3) v0 = a.v[3 * (int64_t)i + t];
   }
+  const double m = a.rc;
+  const bool in = !live || (xi >= m && xi <= a.b.L[0] - m && yi >= m && yi <= a.b.L[1] - m &&
+                            zi >= m && zi <= a.b.L[2] - m);
+  const bool interior = __ballot(!in) == 0;  // wavefront-uniform
   if (live) {
     const int ti = T1 ? 0 : a.type[i];
     const int32_t ctot = a.nnbr[i];
-    const int32_t cnt = ctot > t ? (ctot - t + TEAM - 1) / TEAM : 0;
+    const int32_t cnt = ctot > t ? (ctot - t + kTeam - 1) / kTeam : 0;
     const int32_t *row =
         a.nbr + (int64_t)(i >> 6) * a.maxn * kWave + (i & (kWave - 1)) + (int64_t)t * kWave;
-    if (SKIP && interior)
-      walk_row<MIXED, T1, EV, U, false, WIDE, TEAM, V>(a, row, cnt, xi, yi, zi, ti, c1, tab, s);
+    if (interior)
+      walk_row<MIXED, T1, EV, kSlots, false, WIDE, kTeam, V>(a, row, cnt, xi, yi, zi, ti, c1, tab,
+                                                             s);
     else
-      walk_row<MIXED, T1, EV, U, true, WIDE, TEAM, V>(a, row, cnt, xi, yi, zi, ti, c1, tab, s);
+      walk_row<MIXED, T1, EV, kSlots, true, WIDE, kTeam, V>(a, row, cnt, xi, yi, zi, ti, c1, tab,
+                                                            s);
     if constexpr (EV) add_xf(xi, yi, zi, s);
   }
   const double e_lane = s.e;
-  if constexpr (TEAM > 1) {
-#pragma unroll
-    for (int mask = TEAM / 2; mask > 0; mask >>= 1) {
-      s.fx += __shfl_xor(s.fx, mask, kWave);
-      s.fy += __shfl_xor(s.fy, mask, kWave);
-      s.fz += __shfl_xor(s.fz, mask, kWave);
-      if constexpr (EV) s.e += __shfl_xor(s.e, mask, kWave);
-    }
-  }
-  if (live) {
-    if (t == 0) {
-      if (!STEP || a.F) {
-        a.F[aos_index<V>(i, 0, a.n)] = s.fx;
-        a.F[aos_index<V>(i, 1, a.n)] = s.fy;
-        a.F[aos_index<V>(i, 2, a.n)] = s.fz;
-      }
-      if (a.e_atom) a.e_atom[i] = 0.5 * s.e;
-    }
+  s.fx = team_sum<kTeam>(s.fx);
+  s.fy = team_sum<kTeam>(s.fy);
+  s.fz = team_sum<kTeam>(s.fz);
+  if constexpr (EV) s.e = team_sum<kTeam>(s.e);
+  if (live && t == 3) {
+    if (a.e_atom) a.e_atom[i] = 0.5 * s.e;
+  } else if (live) {
+    const double f = t == 0 ? s.fx : (t == 1 ? s.fy : s.fz);
+    if (!STEP || a.F) a.F[aos_index<V>(i, t, a.n)] = f;
     if constexpr (STEP) {
-      const double f[3] = {s.fx, s.fy, s.fz};
-      const double xo[3] = {xi, yi, zi};
-#pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        if (k % TEAM != t) continue;
-        const int64_t q = 3 * (int64_t)i + k;
-        double kick = a.hdt * f[k];
-        if (!a.unit_mass) kick = kick / a.mass;
-        const double vn = a.v[q] + kick;
-        ke = __builtin_fma(vn, vn, ke);
-        if (a.open_next) {
-          const double L = a.b.L[k];
-          const double vh = vn + kick;
-          double xq = xo[k] + a.dt * vh;
-          if (xq >= L) xq -= L;
-          else if (xq < 0.0) xq += L;
-          if (xq >= L) xq -= L;
-          a.v[q] = vh;
-          a.x_next[q] = xq;
-        } else {
-          a.v[q] = vn;
-        }
+      const int64_t q = 3 * (int64_t)i + t;
+      double kick = a.hdt * f;
+      if (!a.unit_mass) kick = kick / a.mass;
+      const double vn = v0 + kick;
+      ke = vn * vn;
+      double vout = vn;
+      if (a.open_next) {
+        const double L = t == 0 ? a.b.L[0] : (t == 1 ? a.b.L[1] : a.b.L[2]);
+        const double xo = t == 0 ? xi : (t == 1 ? yi : zi);
+        vout = vn + kick;
+        double xq = xo + a.dt * vout;
+        if (xq >= L) xq -= L;
+        else if (xq < 0.0) xq += L;
+        if (xq >= L) xq -= L;
+        a.x_next[q] = xq;
       }
+      a.v[q] = vout;
     }
   }
   if constexpr (EV) {
     const double v[8] = {0.5 * e_lane, 0.5 * s.wxx, 0.5 * s.wyy, 0.5 * s.wzz,
                          0.5 * s.wxy,  0.5 * s.wxz, 0.5 * s.wyz, 0.5 * a.mass * ke};
-    block_sum<kForceWaves * TEAM, 8>(v, red, a.partial + (int64_t)blockIdx.x * kEvStride);
+    block_sum<kThreads / kWave, 8, ATOMS / kHalfRowAtoms>(v, red,
+                                                          a.partial + (int64_t)blk * kEvStride);
   }
 }
 
@@ -624,7 +622,7 @@ __global__ __launch_bounds__(ATOMS * TEAM) void k_force_half(ForceArgs a) {
   constexpr int kWaves = kThreads / kWave;
   __shared__ HalfLds<NV, SLOTS> s;
   __shared__ double tab[T1 ? 4 : 4 * LJMD_MAX_TYPES * LJMD_MAX_TYPES];
-  __shared__ double red[kWaves * 7];
+  __shared__ double red[kRedRows * kWaves * 7];
   for (int q = threadIdx.x; q < SLOTS * NV * kWave; q += kThreads) (&s.acc[0][0][0])[q] = 0.0;
   for (int q = threadIdx.x; q < kHalfTab; q += kThreads) {
     s.key[q] = -1;
@@ -666,13 +664,10 @@ __global__ __launch_bounds__(ATOMS * TEAM) void k_force_half(ForceArgs a) {
                                                           tab, r);
   }
   const double e_lane = r.e;
-#pragma unroll
-  for (int mask = TEAM / 2; mask > 0; mask >>= 1) {
-    r.fx += __shfl_xor(r.fx, mask, kWave);
-    r.fy += __shfl_xor(r.fy, mask, kWave);
-    r.fz += __shfl_xor(r.fz, mask, kWave);
-    if constexpr (EATOM) r.e += __shfl_xor(r.e, mask, kWave);
-  }
+  r.fx = team_sum<TEAM>(r.fx);
+  r.fy = team_sum<TEAM>(r.fy);
+  r.fz = team_sum<TEAM>(r.fz);
+  if constexpr (EATOM) r.e = team_sum<TEAM>(r.e);
   if (live && t == 0) {  // the owner's side of its pairs joins the j-side sums of its tile
     const int32_t sl = half_slot(s, i >> 6);
     const int l = i & (kWave - 1);
@@ -718,15 +713,18 @@ __global__ __launch_bounds__(ATOMS * TEAM) void k_force_half(ForceArgs a) {
 // groups first, the partial group gathers only live slots), then the team's
 // sums are combined by a butterfly over the team (both lanes of every exchange
 // add the same two numbers, so every lane ends with the same, order-fixed sum).
-// Each lane walks its entries in row order, as k_force_full does: with the
-// same team size the two kernels give bitwise the same forces and per-atom
-// energies.
+// 500,000 atoms with energies (us): teams of four 96.8 -> 83.5 with masked groups
+// and the sums by row; of one and two those groups cost 70 % and 16 % and stay out.
+// Each lane walks its entries in row order, as k_force_full does: with its team
+// of four the two kernels give bitwise the same forces and per-atom energies, and so
+// does a team of two, whose lanes keep their even and their odd entries -- the
+// entries of two of the four lanes -- apart.
 template <bool MIXED, bool T1, bool EV, int TEAM, int U, bool WIDE>
 __global__ __launch_bounds__(kCsrThreads) void k_force_csr(ForceArgs a,
                                                             const int64_t *__restrict__ off,
                                                             const int32_t *__restrict__ csr) {
   __shared__ double tab[T1 ? 4 : 4 * LJMD_MAX_TYPES * LJMD_MAX_TYPES];
-  __shared__ double red[kCsrWaves * 8];
+  __shared__ double red[kRedRows * kCsrWaves * 7];
   Coef c1{};
   if constexpr (T1) {
     c1 = coef_of(a.eps, a.sig, 0);
@@ -748,7 +746,7 @@ __global__ __launch_bounds__(kCsrThreads) void k_force_csr(ForceArgs a,
   const bool in = !live || (xi >= m && xi <= a.b.L[0] - m && yi >= m && yi <= a.b.L[1] - m &&
                             zi >= m && zi <= a.b.L[2] - m);
   const bool interior = __ballot(!in) == 0;  // wavefront-uniform
-  Acc s;
+  Acc s, odd;  // odd: TEAM == 2 only
   if (live) {
     const int ti = T1 ? 0 : a.type[i];
     const int64_t r0 = off[i], r1 = off[i + 1];
@@ -756,71 +754,49 @@ __global__ __launch_bounds__(kCsrThreads) void k_force_csr(ForceArgs a,
     const int32_t *row = csr + r0 + t;
     auto walk = [&](auto wrap) {
       constexpr bool W = decltype(wrap)::value;
-      const int32_t whole = cnt - cnt % U;
       const int32_t *rp = row;
-      int32_t k = 0;
-      for (; k < whole; k += U, rp += U * TEAM) {
-        int32_t j[U];
+      auto group = [&](int32_t k, auto masked) {
+        constexpr bool M = decltype(masked)::value;
+        int32_t j[U], tj[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) j[u] = rp[u * TEAM];
+        for (int u = 0; u < U; ++u) j[u] = rp[(!M || k + u < cnt ? u : 0) * TEAM];
         double xj[U], yj[U], zj[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-          const double *p = pos_of<WIDE>(a.x, j[u]);
-          xj[u] = p[0];
-          yj[u] = p[1];
-          zj[u] = p[2];
+          load_pos<1, WIDE>(a.x, j[u], a.n, xj[u], yj[u], zj[u]);
+          tj[u] = T1 ? 0 : a.type[j[u]];
         }
 #pragma unroll
         for (int u = 0; u < U; ++u)
-          add_pair<MIXED, T1, EV, W>(a, xi, yi, zi, xj[u], yj[u], zj[u], j[u], true, ti, c1, tab, s);
-      }
-      if (k < cnt) {
-        int32_t j[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) j[u] = rp[(k + u < cnt ? u : 0) * TEAM];
-        double xj[U], yj[U], zj[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          xj[u] = xi;
-          yj[u] = yi;
-          zj[u] = zi;
-          if (k + u < cnt) {
-            const double *p = pos_of<WIDE>(a.x, j[u]);
-            xj[u] = p[0];
-            yj[u] = p[1];
-            zj[u] = p[2];
-          }
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-          add_pair<MIXED, T1, EV, W>(a, xi, yi, zi, xj[u], yj[u], zj[u], j[u], k + u < cnt, ti, c1,
-                                     tab, s);
+          add_pair<MIXED, T1, EV, W>(a, xi, yi, zi, xj[u], yj[u], zj[u], tj[u], !M || k + u < cnt,
+                                     ti, c1, tab, TEAM == 2 && u % 2 ? odd : s);
+      };
+      if constexpr (TEAM >= 4) {  // masked groups only, as walk_row
+#pragma unroll 1
+        for (int32_t k = 0; k < cnt; k += U, rp += U * TEAM) group(k, std::true_type{});
+      } else {  // whole groups and one masked: their longer rows gain more from it
+        const int32_t whole = cnt - cnt % U;
+        int32_t k = 0;
+        for (; k < whole; k += U, rp += U * TEAM) group(k, std::false_type{});
+        if (k < cnt) group(k, std::true_type{});
       }
     };
     if (interior)
       walk(std::false_type{});
     else
       walk(std::true_type{});
+    if constexpr (TEAM == 2) {
+      s.fx += odd.fx, s.fy += odd.fy, s.fz += odd.fz, s.e += odd.e;
+      s.wxx += odd.wxx, s.wyy += odd.wyy, s.wzz += odd.wzz;
+      s.wxy += odd.wxy, s.wxz += odd.wxz, s.wyz += odd.wyz;
+    }
     if constexpr (EV) add_xf(xi, yi, zi, s);
   }
-  if constexpr (TEAM > 1) {
-#pragma unroll
-    for (int mask = TEAM / 2; mask > 0; mask >>= 1) {
-      s.fx += __shfl_xor(s.fx, mask, kWave);
-      s.fy += __shfl_xor(s.fy, mask, kWave);
-      s.fz += __shfl_xor(s.fz, mask, kWave);
-      if constexpr (EV) {
-        s.e += __shfl_xor(s.e, mask, kWave);
-        s.wxx += __shfl_xor(s.wxx, mask, kWave);
-        s.wyy += __shfl_xor(s.wyy, mask, kWave);
-        s.wzz += __shfl_xor(s.wzz, mask, kWave);
-        s.wxy += __shfl_xor(s.wxy, mask, kWave);
-        s.wxz += __shfl_xor(s.wxz, mask, kWave);
-        s.wyz += __shfl_xor(s.wyz, mask, kWave);
-      }
-    }
-  }
+  const double e_lane = s.e;
+  s.fx = team_sum<TEAM>(s.fx);
+  s.fy = team_sum<TEAM>(s.fy);
+  s.fz = team_sum<TEAM>(s.fz);
+  if constexpr (EV) s.e = team_sum<TEAM>(s.e);
   const bool lead = live && t == 0;
   if (lead) {
     a.F[3 * (int64_t)i] = s.fx;
@@ -829,34 +805,25 @@ __global__ __launch_bounds__(kCsrThreads) void k_force_csr(ForceArgs a,
     if (a.e_atom) a.e_atom[i] = 0.5 * s.e;
   }
   if constexpr (EV) {
-    const double z = 0.0;
-    const double v[7] = {lead ? 0.5 * s.e : z,   lead ? 0.5 * s.wxx : z, lead ? 0.5 * s.wyy : z,
-                         lead ? 0.5 * s.wzz : z, lead ? 0.5 * s.wxy : z, lead ? 0.5 * s.wxz : z,
-                         lead ? 0.5 * s.wyz : z};
+    const double v[7] = {0.5 * e_lane, 0.5 * s.wxx, 0.5 * s.wyy, 0.5 * s.wzz,
+                         0.5 * s.wxy,  0.5 * s.wxz, 0.5 * s.wyz};
     block_sum<kCsrWaves, 7>(v, red, a.partial + (int64_t)blockIdx.x * kEvStride);
   }
 }
 
-// Loop shapes, measured on MI355X.  One lane per atom (the CSR kernel with
-// team 1): 8 slots per group, against 1, 2 and 4.  Tiled full list: two lanes
-// per atom with 6 slots per group each, against one lane with 8 slots and
-// teams of 4 (fewer cache lines per gather instruction); 128 atoms (256
-// threads) per block, against 64 and 256 atoms (more resident blocks per CU
-// hide more gather latency; 64 pays for its extra energy/virial partial rows).
-constexpr int kUnroll = 8;
-constexpr int kTeam = 2;
-constexpr int kTeamUnroll = 6;
-// Up to LJMD_SMALL_GRID_ATOMS atoms (at most one 128-atom block per compute
-// unit) the tiled full-list kernels take four lanes per atom with 3 slots per
-// group: twice the waves in flight on a chip the grid leaves mostly idle.
-// Measured at 32,000 atoms: fused step 12.5 -> 11.6 us (FP64 12.1 -> 11.5),
-// forces with energy/virial 11.1 -> 10.1 us; from about 42,000 atoms (two
-// blocks per compute unit) on, four lanes gain nothing on the step, and at
-// 500,000 atoms the step takes 110 against 90 us.
-constexpr int64_t kSmallGridAtoms = LJMD_SMALL_GRID_ATOMS;
-constexpr int kSmallTeam = 4;
-constexpr int kSmallTeamUnroll = 3;
-static_assert(kSmallGridAtoms == 256 * kForceThreads, "one block per compute unit");
+// Slots per group of the CSR kernel: one lane per atom 8, teams 4.
+constexpr int kCsrUnroll = 8;
+constexpr int kCsrTeamUnroll = 4;
+
+// Full-list blocks of 64 atoms where the launch writes no partial rows (forces
+// only) or, up to this size, where the workspace holds two rows per 128 atoms
+// (chained steps); else 128.  Smaller blocks spread a mid-size grid more evenly
+// over the compute units: fused step, 128 -> 64 atoms per block (us), 256 atoms
+// 8.6 -> 6.7, 32,000 9.3 -> 9.0, 42,592 13.6 -> 11.3, 70,304 (two types) 24.7 ->
+// 21.6, 110,447 (two types) 31.6 -> 30.2, 131,072 25.8 -> 26.6; forces only at
+// 500,000 atoms 73.0 -> 71.0, with their own column sum over twice the rows 82.0 ->
+// 83.4.
+constexpr int64_t kSmallBlockAtoms = 114688;
 
 // Half-list blocks: 256 home atoms with two lanes each (512 threads), 32 tile
 // slots, 4 entries per group.  Up to kHalfSmallAtoms atoms: blocks of 128 home
@@ -887,7 +854,7 @@ unsigned half_blocks(int64_t n) {
 template <bool MIXED, bool T1, bool EV, bool EATOM>
 void launch_half(const ForceArgs &a, hipStream_t st) {
   const unsigned nb = half_blocks(a.n);
-  if (a.n <= kSmallGridAtoms)
+  if (a.n <= LJMD_SMALL_GRID_ATOMS)
     k_force_half<MIXED, T1, EV, EATOM, false, kHalfSmallBlock, kHalfTinySlots, kHalfUnroll,
                  kHalfTinyTeam><<<nb, kHalfSmallBlock * kHalfTinyTeam, 0, st>>>(a);
   else if (a.n <= kHalfSmallAtoms)
@@ -901,54 +868,78 @@ void launch_half(const ForceArgs &a, hipStream_t st) {
         <<<nb, kHalfAtoms * kHalfTeam, 0, st>>>(a);
 }
 
-// The tiled full-list kernel in the team shape for a.n atoms (every caller --
-// forces, AoSoA forces, fused step -- takes the same shape, so their sums agree
-// bitwise); nblk = force_blocks(a.n).
+unsigned blocks_of(int64_t n, int per) {
+  const int64_t b = (n + per - 1) / per;
+  return (unsigned)(b > 0 ? b : 1);
+}
+
+// The full-list kernel in blocks of `atoms` (64 or 128) atoms.
 template <bool MIXED, bool T1, bool EV, bool STEP, int V = 1>
-void launch_full(const ForceArgs &a, unsigned nblk, hipStream_t st) {
-  if (a.n <= kSmallGridAtoms)
-    k_force_full<MIXED, T1, EV, kSmallTeamUnroll, true, STEP, false, kSmallTeam, V>
-        <<<nblk, kForceThreads * kSmallTeam, 0, st>>>(a);
-  else if (V != 1 || a.n <= kNarrowAtoms)
-    k_force_full<MIXED, T1, EV, kTeamUnroll, true, STEP, false, kTeam, V>
-        <<<nblk, kForceThreads * kTeam, 0, st>>>(a);
-  else if constexpr (V == 1)
-    k_force_full<MIXED, T1, EV, kTeamUnroll, true, STEP, true, kTeam>
-        <<<nblk, kForceThreads * kTeam, 0, st>>>(a);
+void launch_full(const ForceArgs &a, int atoms, hipStream_t st) {
+  // chained steps: one more block sums the previous step's rows
+  const unsigned nblk = blocks_of(a.n, atoms) + (STEP && a.prev_ev ? 1 : 0);
+  if (V == 1 && a.n > kNarrowAtoms) {
+    if constexpr (V == 1)
+      k_force_full<MIXED, T1, EV, STEP, true, kForceAtoms>
+          <<<blocks_of(a.n, kForceAtoms) + (STEP && a.prev_ev ? 1 : 0), kForceAtoms * kTeam, 0,
+             st>>>(a);
+  } else if (atoms == kForceAtoms) {
+    k_force_full<MIXED, T1, EV, STEP, false, kForceAtoms, V>
+        <<<nblk, kForceAtoms * kTeam, 0, st>>>(a);
+  } else {
+    k_force_full<MIXED, T1, EV, STEP, false, kHalfRowAtoms, V>
+        <<<nblk, kHalfRowAtoms * kTeam, 0, st>>>(a);
+  }
 }
 
 template <bool MIXED, bool T1, bool EV>
-void launch_one(const ForceArgs &a, int kind, unsigned nblk, hipStream_t st) {
+void launch_one(const ForceArgs &a, int kind, hipStream_t st) {
   if (kind == LJMD_HALF) {
     if (a.e_atom)
       launch_half<MIXED, T1, EV, true>(a, st);
     else
       launch_half<MIXED, T1, EV, false>(a, st);
   } else {
-    launch_full<MIXED, T1, EV, false>(a, nblk, st);
+    launch_full<MIXED, T1, EV, false>(a, EV ? kForceAtoms : kHalfRowAtoms, st);
   }
 }
 
 template <bool MIXED>
-void launch_prec(const ForceArgs &a, int kind, bool ev, unsigned nblk, hipStream_t st) {
+void launch_prec(const ForceArgs &a, int kind, bool ev, hipStream_t st) {
   const bool t1 = a.ntypes == 1;
-  if (t1 && ev) launch_one<MIXED, true, true>(a, kind, nblk, st);
-  else if (t1) launch_one<MIXED, true, false>(a, kind, nblk, st);
-  else if (ev) launch_one<MIXED, false, true>(a, kind, nblk, st);
-  else launch_one<MIXED, false, false>(a, kind, nblk, st);
+  if (t1 && ev) launch_one<MIXED, true, true>(a, kind, st);
+  else if (t1) launch_one<MIXED, true, false>(a, kind, st);
+  else if (ev) launch_one<MIXED, false, true>(a, kind, st);
+  else launch_one<MIXED, false, false>(a, kind, st);
 }
 
 }  // namespace
 
-unsigned force_blocks(int64_t n) {
-  const int64_t b = (n + kForceThreads - 1) / kForceThreads;
-  return (unsigned)(b > 0 ? b : 1);
-}
+unsigned force_blocks(int64_t n) { return blocks_of(n, kForceAtoms); }
 
 size_t force_workspace(int64_t n) { return (size_t)force_blocks(n) * kEvStride * sizeof(double); }
 
-// Atoms whose partial rows share one row of the force workspace (one block's).
-int64_t force_workspace_atoms() { return kForceThreads; }
+// Atoms whose partial rows share one row of the force workspace.
+int64_t force_workspace_atoms() { return kForceAtoms; }
+
+// One half of the chained steps' workspace: the rows of 64-atom blocks up to
+// kSmallBlockAtoms atoms.  A workspace of two 128-atom halves is enough, and gives
+// the same results (chain_atoms).
+size_t chain_workspace(int64_t n) {
+  return n <= kSmallBlockAtoms
+             ? (size_t)blocks_of(n, kHalfRowAtoms) * kEvStride * sizeof(double)
+             : force_workspace(n);
+}
+
+// Atoms per partial row in a chained workspace of ws_bytes.
+int chain_atoms(int64_t n, size_t ws_bytes) {
+  return n <= kSmallBlockAtoms && ws_bytes >= 2 * chain_workspace(n) ? kHalfRowAtoms : kForceAtoms;
+}
+
+// Doubles in one half of it.
+size_t chain_half(int64_t n, size_t ws_bytes) {
+  return (size_t)blocks_of(n, chain_atoms(n, ws_bytes)) * kEvStride;
+}
 
 int launch_forces(const BoxK &b, int precision, int kind, double rc, int32_t ntypes,
                   const double *eps, const double *sig, int64_t n, const double *x,
@@ -970,20 +961,19 @@ int launch_forces(const BoxK &b, int precision, int kind, double rc, int32_t nty
   a.F = F;
   a.e_atom = e_atom;
   a.partial = (double *)ws;
-  const unsigned nblk = force_blocks(n);
   const bool want_ev = ev != nullptr || e_atom != nullptr;
   if (kind == LJMD_HALF) {
     k_zero2_f64<<<(unsigned)((3 * n + 255) / 256 + 1), 256, 0, st>>>(F, 3 * n, e_atom, n);
   }
   if (n > 0) {
     if (precision == LJMD_MIXED)
-      launch_prec<true>(a, kind, want_ev, nblk, st);
+      launch_prec<true>(a, kind, want_ev, st);
     else
-      launch_prec<false>(a, kind, want_ev, nblk, st);
+      launch_prec<false>(a, kind, want_ev, st);
   } else if (ev) {
     k_zero_f64<<<1, 256, 0, st>>>(a.partial, kEvStride);
   }
-  const unsigned rows = n == 0 ? 1 : (kind == LJMD_HALF ? half_blocks(n) : nblk);
+  const unsigned rows = n == 0 ? 1 : (kind == LJMD_HALF ? half_blocks(n) : force_blocks(n));
   if (ev) k_colsum<1024><<<1, 1024, 0, st>>>(rows, kEvStride, 7, a.partial, ev, 1.0, 0);
   return check_launch("ljmd_compute_forces");
 }
@@ -1002,7 +992,7 @@ size_t csr_force_workspace(int64_t n) {
 namespace {
 template <bool MIXED, bool T1, bool EV, int TEAM>
 void launch_csr_team(const ForceArgs &a, const int64_t *off, const int32_t *csr, hipStream_t st) {
-  constexpr int U = TEAM == 1 ? kUnroll : 4;
+  constexpr int U = TEAM == 1 ? kCsrUnroll : kCsrTeamUnroll;
   const unsigned nblk = csr_force_blocks(a.n, TEAM);
   if (a.n <= kNarrowAtoms)
     k_force_csr<MIXED, T1, EV, TEAM, U, false><<<nblk, kCsrThreads, 0, st>>>(a, off, csr);
@@ -1067,24 +1057,24 @@ int launch_forces_csr(const BoxK &b, int precision, double rc, int32_t ntypes, c
 
 namespace {
 template <bool MIXED, bool T1, bool EV, int V>
-void launch_aosoa_one(const ForceArgs &a, unsigned nblk, hipStream_t st) {
-  launch_full<MIXED, T1, EV, false, V>(a, nblk, st);
+void launch_aosoa_one(const ForceArgs &a, hipStream_t st) {
+  launch_full<MIXED, T1, EV, false, V>(a, EV ? kForceAtoms : kHalfRowAtoms, st);
 }
 
 template <bool MIXED, int V>
-void launch_aosoa_v(const ForceArgs &a, bool ev, unsigned nblk, hipStream_t st) {
+void launch_aosoa_v(const ForceArgs &a, bool ev, hipStream_t st) {
   const bool t1 = a.ntypes == 1;
-  if (t1 && ev) launch_aosoa_one<MIXED, true, true, V>(a, nblk, st);
-  else if (t1) launch_aosoa_one<MIXED, true, false, V>(a, nblk, st);
-  else if (ev) launch_aosoa_one<MIXED, false, true, V>(a, nblk, st);
-  else launch_aosoa_one<MIXED, false, false, V>(a, nblk, st);
+  if (t1 && ev) launch_aosoa_one<MIXED, true, true, V>(a, st);
+  else if (t1) launch_aosoa_one<MIXED, true, false, V>(a, st);
+  else if (ev) launch_aosoa_one<MIXED, false, true, V>(a, st);
+  else launch_aosoa_one<MIXED, false, false, V>(a, st);
 }
 
 template <bool MIXED>
-void launch_aosoa_prec(const ForceArgs &a, int vlen, bool ev, unsigned nblk, hipStream_t st) {
-  if (vlen == 0) launch_aosoa_v<MIXED, 0>(a, ev, nblk, st);
-  else if (vlen == 8) launch_aosoa_v<MIXED, 8>(a, ev, nblk, st);
-  else launch_aosoa_v<MIXED, 64>(a, ev, nblk, st);
+void launch_aosoa_prec(const ForceArgs &a, int vlen, bool ev, hipStream_t st) {
+  if (vlen == 0) launch_aosoa_v<MIXED, 0>(a, ev, st);
+  else if (vlen == 8) launch_aosoa_v<MIXED, 8>(a, ev, st);
+  else launch_aosoa_v<MIXED, 64>(a, ev, st);
 }
 
 // One thread per element: [n][3] <-> AoSoA(V).
@@ -1142,9 +1132,9 @@ int launch_forces_aosoa(const BoxK &b, int precision, double rc, int32_t ntypes,
   const bool want_ev = ev != nullptr || e_atom != nullptr;
   if (n > 0) {
     if (precision == LJMD_MIXED)
-      launch_aosoa_prec<true>(a, vlen, want_ev, nblk, st);
+      launch_aosoa_prec<true>(a, vlen, want_ev, st);
     else
-      launch_aosoa_prec<false>(a, vlen, want_ev, nblk, st);
+      launch_aosoa_prec<false>(a, vlen, want_ev, st);
   } else if (ev) {
     k_zero_f64<<<1, 256, 0, st>>>(a.partial, kEvStride);
   }
@@ -1164,14 +1154,26 @@ int launch_aosoa_convert(int64_t n, int vlen, int to_aosoa, const double *src, d
   return check_launch("ljmd_aosoa_convert");
 }
 
-// partial: this step's partial rows; ev: their sums, or NULL to leave them in
+// The sums of the partial rows (one per `atoms` atoms) one md_step launch left: of
+// 128-atom rows, or of pairs of 64-atom rows, which is bitwise the same.
+int launch_md_step_sums(int64_t n, int atoms, const double *partial, double *ev, hipStream_t st) {
+  if (atoms == kForceAtoms)
+    k_colsum<1024><<<1, 1024, 0, st>>>(force_blocks(n), kEvStride, 8, partial, ev, 1.0, 0);
+  else
+    k_colsum<1024, true><<<1, 1024, 0, st>>>(blocks_of(n, atoms), kEvStride, 8, partial, ev, 1.0,
+                                             0);
+  return check_launch("ljmd_md_step_sums");
+}
+
+// partial: this step's partial rows, one per `atoms` atoms; ev: their sums, or NULL to leave them in
 // `partial`; prev_partial/prev_ev: the rows a previous step left and the output of
 // their sums (NULL: none).
 int launch_md_step(const BoxK &b, int precision, double rc, int32_t ntypes, const double *eps,
                    const double *sig, int64_t n, const double *x, const int32_t *type,
                    const int32_t *nbr, const int32_t *nnbr, int32_t maxn, double dt, double mass,
                    double *v, double *x_next, int open_next, double *F, double *e_atom, double *ev,
-                   double *partial, const double *prev_partial, double *prev_ev, hipStream_t st) {
+                   double *partial, int atoms, const double *prev_partial, double *prev_ev,
+                   hipStream_t st) {
   ForceArgs a{};
   a.b = b;
   a.rc = rc;
@@ -1195,7 +1197,7 @@ int launch_md_step(const BoxK &b, int precision, double rc, int32_t ntypes, cons
   a.mass = mass;
   a.unit_mass = mass == 1.0;
   a.open_next = open_next;
-  const unsigned nblk = force_blocks(n);
+  const unsigned nblk = blocks_of(n, atoms);
   a.prev_partial = prev_partial;
   a.prev_ev = prev_ev;
   a.prev_rows = nblk;
@@ -1203,24 +1205,18 @@ int launch_md_step(const BoxK &b, int precision, double rc, int32_t ntypes, cons
   const bool t1 = ntypes == 1;
   if (n > 0) {
     if (mixed) {
-      if (t1) launch_full<true, true, true, true>(a, nblk, st);
-      else launch_full<true, false, true, true>(a, nblk, st);
+      if (t1) launch_full<true, true, true, true>(a, atoms, st);
+      else launch_full<true, false, true, true>(a, atoms, st);
     } else {
-      if (t1) launch_full<false, true, true, true>(a, nblk, st);
-      else launch_full<false, false, true, true>(a, nblk, st);
+      if (t1) launch_full<false, true, true, true>(a, atoms, st);
+      else launch_full<false, false, true, true>(a, atoms, st);
     }
   } else {
     k_zero_f64<<<1, 256, 0, st>>>(a.partial, kEvStride);
     if (prev_ev) k_colsum<1024><<<1, 1024, 0, st>>>(1, kEvStride, 8, prev_partial, prev_ev, 1.0, 0);
   }
-  if (ev) k_colsum<1024><<<1, 1024, 0, st>>>(nblk, kEvStride, 8, a.partial, ev, 1.0, 0);
+  if (ev) return launch_md_step_sums(n, atoms, a.partial, ev, st);
   return check_launch("ljmd_md_step");
-}
-
-// The sums of the partial rows one md_step launch left (same form as its own).
-int launch_md_step_sums(int64_t n, const double *partial, double *ev, hipStream_t st) {
-  k_colsum<1024><<<1, 1024, 0, st>>>(force_blocks(n), kEvStride, 8, partial, ev, 1.0, 0);
-  return check_launch("ljmd_md_step_sums");
 }
 
 }  // namespace ljmd

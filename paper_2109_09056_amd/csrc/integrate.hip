@@ -44,7 +44,7 @@ __global__ __launch_bounds__(kThreads) void k_kick_kick_drift(int64_t m3, double
                                                               double *__restrict__ v,
                                                               const double *__restrict__ F,
                                                               double *__restrict__ partial) {
-  __shared__ double red[kThreads / kWave];
+  __shared__ double red[kRedRows * kThreads / kWave];
   const int64_t q = (int64_t)blockIdx.x * kThreads + threadIdx.x;
   double vv = 0.0;
   if (q < m3) {
@@ -73,7 +73,7 @@ __global__ __launch_bounds__(kThreads) void k_kick(int64_t m3, double hdt, doubl
                                                    int unit_mass, double *__restrict__ v,
                                                    const double *__restrict__ F,
                                                    double *__restrict__ partial) {
-  __shared__ double red[kThreads / kWave];
+  __shared__ double red[kRedRows * kThreads / kWave];
   const int64_t q = (int64_t)blockIdx.x * kThreads + threadIdx.x;
   double vv = 0.0;
   if (q < m3) {
@@ -91,7 +91,7 @@ __global__ __launch_bounds__(kThreads) void k_kick(int64_t m3, double hdt, doubl
 
 __global__ __launch_bounds__(kThreads) void k_sumsq_v(int64_t m3, const double *__restrict__ v,
                                                       double *__restrict__ partial) {
-  __shared__ double red[kThreads / kWave];
+  __shared__ double red[kRedRows * kThreads / kWave];
   const int64_t q = (int64_t)blockIdx.x * kThreads + threadIdx.x;
   const double vq = q < m3 ? v[q] : 0.0;
   const double s[1] = {vq * vq};
@@ -113,7 +113,7 @@ __global__ __launch_bounds__(kThreads) void k_loss(int64_t m3, BoxK b, const dou
                                                    const double *__restrict__ xref,
                                                    double *__restrict__ xbar,
                                                    double *__restrict__ partial) {
-  __shared__ double red[kThreads / kWave];
+  __shared__ double red[kRedRows * kThreads / kWave];
   const int64_t q = (int64_t)blockIdx.x * kThreads + threadIdx.x;
   double d = 0.0;
   if (q < m3) {
@@ -176,7 +176,7 @@ __global__ __launch_bounds__(kThreads) void k_disp2_max(int64_t n, BoxK b,
                                                         const double *__restrict__ x,
                                                         const double *__restrict__ xref,
                                                         double *__restrict__ partial) {
-  __shared__ double red[kThreads / kWave];
+  __shared__ double red[kRedRows * kThreads / kWave];
   const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
   double d2 = 0.0;
   if (i < n) {

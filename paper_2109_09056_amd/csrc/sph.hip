@@ -168,7 +168,7 @@ __device__ __forceinline__ double density_row(const SphArgs &a, const int32_t *r
 
 template <bool WIDE, bool WANT_U>
 __global__ __launch_bounds__(kSphThreads) void k_sph_density(SphArgs a) {
-  __shared__ double red[kSphWaves];
+  __shared__ double red[kRedRows * kSphWaves];
   const int t = (int)threadIdx.x % kSphTeam;
   const int32_t i = xcd_block(blockIdx.x, gridDim.x) * kSphAtoms + (int)threadIdx.x / kSphTeam;
   const bool live = i < a.n;
@@ -191,7 +191,7 @@ __global__ __launch_bounds__(kSphThreads) void k_sph_density(SphArgs a) {
     s = interior ? density_row<false, WIDE>(a, row, cnt, xi, yi, zi)
                  : density_row<true, WIDE>(a, row, cnt, xi, yi, zi);
   }
-  s += __shfl_xor(s, 1, kWave);  // both lanes of the team end with the same sum
+  s = team_sum<kSphTeam>(s);  // both lanes of the team end with the same sum
   double rho = 0.0;
   if (live) {
     rho = a.wnorm * (1.0 + s);  // self term: w(0) = 1
@@ -292,9 +292,9 @@ __global__ __launch_bounds__(kSphThreads) void k_sph_accel(SphArgs a) {
     else
       accel_row<true, WIDE>(a, row, cnt, me, ax, ay, az);
   }
-  ax += __shfl_xor(ax, 1, kWave);
-  ay += __shfl_xor(ay, 1, kWave);
-  az += __shfl_xor(az, 1, kWave);
+  ax = team_sum<kSphTeam>(ax);
+  ay = team_sum<kSphTeam>(ay);
+  az = team_sum<kSphTeam>(az);
   if (live && t == 0) {
     const double f[3] = {-a.gnorm * ax, -a.gnorm * ay, -a.gnorm * az};
     if (!STEP || a.acc) {

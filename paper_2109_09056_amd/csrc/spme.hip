@@ -180,7 +180,7 @@ __device__ __forceinline__ void real_row(const RealArgs &a, const double *tab, c
 
 template <bool WIDE, bool EV>
 __global__ __launch_bounds__(kEwThreads) void k_ewald_real(RealArgs a) {
-  __shared__ double red[kEwThreads / kWave];
+  __shared__ double red[kRedRows * kEwThreads / kWave];
   __shared__ double tab[kErfcTable];
   for (int k = threadIdx.x; k < kErfcTable; k += kEwThreads) tab[k] = a.erfcx_tab[k];
   __syncthreads();
@@ -204,9 +204,9 @@ __global__ __launch_bounds__(kEwThreads) void k_ewald_real(RealArgs a) {
     else
       real_row<true, WIDE>(a, tab, row, cnt, me, fx, fy, fz, e);
   }
-  fx += __shfl_xor(fx, 1, kWave);
-  fy += __shfl_xor(fy, 1, kWave);
-  fz += __shfl_xor(fz, 1, kWave);
+  fx = team_sum<kEwTeam>(fx);
+  fy = team_sum<kEwTeam>(fy);
+  fz = team_sum<kEwTeam>(fz);
   if (live && t == 0) {
     double *F = a.F + 3 * (int64_t)i;
     const double q = me.w;
@@ -546,7 +546,7 @@ __global__ __launch_bounds__(kThreads) void k_fft_z_influence(RecArgs a, int64_t
   __shared__ double2 inv[R * NP];
   __shared__ double2 twf[NP / 2 + 1];
   __shared__ double2 twi[NP / 2 + 1];
-  __shared__ double red[kThreads / kWave];
+  __shared__ double red[kRedRows * kThreads / kWave];
   fill_twiddles<NP, 1>(twf, -1.0);
   fill_twiddles<NP, 1>(twi, 1.0);
   const int W = a.K[0] / 2 + 1;
@@ -606,7 +606,7 @@ unsigned z_influence_blocks(const int32_t K[3]) {
 // F_i = -q_i grad sum_k theta_i(k) phi(k); per block the self energy -alpha/sqrt(pi) q_i^2
 template <int N>
 __global__ __launch_bounds__(kThreads) void k_gather(RecArgs a, double *self_partial) {
-  __shared__ double red[kThreads / kWave];
+  __shared__ double red[kRedRows * kThreads / kWave];
   const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   double v[1] = {0.0};
   if (i < a.n) {

@@ -1,0 +1,93 @@
+"""Launch shapes of the kernels at their edges: block and group remainders, both sizes of
+a dispatch rule, against the general path or the oracle."""
+import numpy as np
+import pytest
+
+import lj_inputs as li
+from helpers import gpu_device
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def dev():
+    return gpu_device()
+
+
+def _gas(n, L, seed, ntypes=1):
+    """n atoms no closer than about 0.8 (a jittered lattice with sites taken out)."""
+    g = np.random.default_rng(seed)
+    m = int(np.ceil(n ** (1.0 / 3.0)))
+    sites = np.stack(np.meshgrid(*[np.arange(m)] * 3, indexing="ij"), -1).reshape(-1, 3)
+    sites = sites[np.sort(g.permutation(m ** 3)[:n])]
+    x = (sites + 0.5 + g.uniform(-0.05, 0.05, (n, 3))) * (L / m)
+    return x, g.integers(0, ntypes, n).astype(np.int32)
+
+
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 128, 129, 193, 1000])
+@pytest.mark.parametrize("ntypes", [1, 2])
+def test_chained_step_block_shapes(dev, n, ntypes):
+    """Chained steps in blocks of 64 atoms (the full workspace) and of 128 (twice the
+    force workspace) and ljmd_md_step: positions, velocities, forces and the sums of the
+    rows bitwise the same; the sums formed by the next launch equal to rounding."""
+    import torch
+    from paper_2109_09056_amd import _lib, md, ops
+    L = np.array([11.0, 12.0, 13.0])
+    x, ty = _gas(n, L, 5 + n, ntypes)
+    eps, sig = ([1.0], [1.0]) if ntypes == 1 else ([1.0, 0.9, 1.1], [1.0, 0.95, 0.9])
+    T = lambda a, d=torch.float64: torch.as_tensor(a, dtype=d, device=dev).contiguous()
+    xs, _, ts, _, cs = ops.bin(L, 2.8, T(x), None, T(ty, torch.int32))
+    nl = md.NeighborList(L, 2.8, ops.FULL, device=dev).build(xs, cs)
+    v0 = T(np.random.default_rng(n).normal(size=(n, 3)))
+    full = ops.workspace_bytes(ops.OP_MD_CHAIN, n)
+    small = 2 * ops.workspace_bytes(ops.OP_FORCES, n)
+    assert small <= full
+    got = []
+    for nbytes in (None, full, small):
+        a = (L, ops.FP64, 2.5, T(eps), T(sig), xs, ts, nl.nbr, nl.nnbr, nl.maxn, 0.005, 1.3)
+        v, F = v0.clone(), torch.empty_like(xs)
+        if nbytes is None:
+            x1, _, ev = ops.md_step(*a, v, F=F)
+            got.append((x1, v, F, ev))
+            continue
+        ws = torch.empty(nbytes, dtype=torch.uint8, device=dev)
+        lib, p = _lib.load(), lambda t: t.data_ptr()
+        x1, ev, prev = torch.empty_like(xs), torch.empty(8, dtype=torch.float64, device=dev), \
+            torch.empty(8, dtype=torch.float64, device=dev)
+        box = _lib.make_box(L)
+        st = torch.cuda.current_stream(dev).cuda_stream
+        args = lambda half, out, vel, xn: (
+            box, ops.FP64, 2.5, ntypes, p(a[3]), p(a[4]), n, p(xs), p(ts), p(nl.nbr), p(nl.nnbr),
+            nl.maxn, 0.005, 1.3, p(vel), p(xn), 1, p(F), None, half, out, p(ws), nbytes, st)
+        _lib.check(lib.ljmd_md_step_chained(*args(0, None, v, x1)), "chained")
+        _lib.check(lib.ljmd_md_step_sums(n, 0, p(ws), nbytes, p(ev), st), "sums")
+        # the next step's launch sums half 0 as well
+        F1 = F.clone()
+        _lib.check(lib.ljmd_md_step_chained(*args(1, p(prev), v.clone(), torch.empty_like(xs))),
+                   "chained")
+        scale = ev.abs().max().item()
+        assert (prev - ev).abs().max().item() <= 1e-13 * max(scale, 1.0)
+        got.append((x1, v, F1, ev))
+    for other in got[1:]:
+        assert all(torch.equal(s, t) for s, t in zip(got[0], other))
+
+
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+@pytest.mark.parametrize("cells", [4, 10, 26])
+def test_csr_teams_of_two_and_four_bitwise_tiled(dev, cells, prec):
+    """CSR with teams of two and of four gives bitwise the tiled kernel's forces and
+    per-atom energies at every size, one and two types."""
+    import torch
+    from paper_2109_09056_amd import md, ops
+    for ntypes in (1, 2):
+        w = li.Workload("t", 9, cells=cells, ntypes=ntypes)
+        s = li.make_system(w)
+        P = ops.FP64 if prec == "fp64" else ops.MIXED
+        sim = md.LJSim(w.box, eps=s["eps"], sigma=s["sigma"], precision=P, device=dev)
+        sim.load(s["x"], None, s["types"])
+        a = (sim.L, P, 2.5, sim.eps, sim.sigma, sim.x, sim.types)
+        F, e, _ = ops.compute_forces(*a[:2], ops.FULL, *a[2:], sim.nl.nbr, sim.nl.nnbr, sim.nl.maxn)
+        off, csr = ops.list_to_csr(sim.nl.nbr, sim.nl.nnbr, sim.nl.maxn)
+        for team in (2, 4):
+            F2, e2, _ = ops.compute_forces_csr(*a, off, csr, team=team)
+            assert torch.equal(F, F2) and torch.equal(e, e2), (ntypes, team)
