@@ -23,13 +23,15 @@
 // charge is spread onto a real grid (LDS-privatised per wavefront, then FP64
 // atomics); the 3-D transform is real-to-complex: the x pass turns each row of
 // K0 reals into K0/2 + 1 coefficients through one complex FFT of length K0/2
-// plus a split step, and the y and z passes run on that half grid, each pass
-// a set of radix-2 FFTs over rows staged in LDS (rows along y and z loaded
-// with consecutive x across lanes, so every pass reads and writes whole cache
-// lines); the influence function B C is applied on the half grid, each
-// coefficient with 0 < m_0 < K0/2 counted twice in the energy (Hermitian
-// symmetry of a real input); the inverse mirrors it and leaves phi real; the
-// gather is one thread per particle.
+// plus a split step, and the y and z passes run on that half grid, each pass two
+// register transforms per row with one exchange through LDS (rows along y and z
+// loaded with consecutive x across lanes, so every pass reads and writes whole cache
+// lines).  The z pass multiplies by the influence function between its forward and
+// inverse transforms, each coefficient with 0 < m_0 < K0/2 counted twice in the
+// energy (Hermitian symmetry of a real input); the inverse mirrors it and leaves phi
+// real; the gather takes two lanes per particle.
+#include <type_traits>
+
 #include "common.h"
 
 namespace ljmd {
@@ -39,6 +41,8 @@ namespace {
 constexpr double kPi = 3.14159265358979323846;
 constexpr int kMaxGrid = 256;  // points per edge
 constexpr int kThreads = 256;
+constexpr int kGatherAtoms = 256;  // particles per gather block
+constexpr int kGatherTeam = 2;     // lanes per particle
 constexpr int kEwAtoms = 128;  // real space: particles per block
 constexpr int kEwTeam = 2;
 constexpr int kEwThreads = kEwAtoms * kEwTeam;
@@ -266,18 +270,18 @@ struct RecArgs {
   const double *q;
   double *grid;        // [K2][K1][K0] real: Q, later phi; x fastest
   double2 *half;       // [K2][K1][K0/2 + 1] complex transform of the grid
-  double *bmod;        // |b_a(m)|^2 tables at bmod + a * kMaxGrid
-  double *partial;     // influence blocks, then gather blocks
+  double *bmod;        // axis factors of the influence function at bmod + a * kMaxGrid
+  double *partial;     // reciprocal energy, then gather blocks
   double *F;
   int accumulate;
 };
 
-__device__ __forceinline__ int wrapi(int k, int K) {
-  k %= K;
-  return k < 0 ? k + K : k;
-}
+// k mod K for a grid edge K, a power of two.
+__device__ __forceinline__ int wrapi(int k, int K) { return k & (K - 1); }
 
-// |b_a(m)|^2 = |sum_{k=0}^{n-2} M_n(k+1) e^{2 pi i m k / K_a}|^-2 for every axis a, m < K_a.
+// |b_a(m)|^2 e^{-pi^2 (m'/L_a)^2 / alpha^2} for every axis a, m < K_a (m' = m, or m - K_a
+// above K_a/2), with |b_a(m)|^2 = |sum_{k=0}^{n-2} M_n(k+1) e^{2 pi i m k / K_a}|^-2: the
+// influence function's factors of one axis (its Gaussian is a product over the axes).
 template <int N>
 __global__ __launch_bounds__(kThreads) void k_bmod(RecArgs a) {
   const int t = blockIdx.x * blockDim.x + threadIdx.x;
@@ -292,7 +296,9 @@ __global__ __launch_bounds__(kThreads) void k_bmod(RecArgs a) {
     re += mk[k + 1] * c;
     im += mk[k + 1] * s;
   }
-  a.bmod[ax * kMaxGrid + m] = 1.0 / (re * re + im * im);
+  const double f = (m <= a.K[ax] / 2 ? m : m - a.K[ax]) * a.b.invL[ax];
+  a.bmod[ax * kMaxGrid + m] =
+      exp(-kPi * kPi * (f * f) / (a.alpha * a.alpha)) / (re * re + im * im);
 }
 
 __global__ __launch_bounds__(kThreads) void k_zero_grid(double *g, int64_t npts) {
@@ -386,79 +392,198 @@ __global__ __launch_bounds__(kWave) void k_spread(RecArgs a) {
   }
 }
 
-// Radix-2 transforms of rows of length NP, R rows per block staged in LDS:
-// bit-reversed load, log2(NP) butterfly stages, natural-order result.
-// sign = -1: sum_k v_k e^{-2 pi i m k / NP}; +1: the unnormalised inverse.
-// Rows per block: 1024 points, at most 64 rows.
-template <int NP>
-constexpr int fft_rows() {
-  return 1024 / NP < 64 ? 1024 / NP : 64;
-}
+// ------------------------------------------------------------------ FFTs --
+//
+// A row of NP = R1 R2 points is transformed in two register steps with one
+// exchange through LDS.  With input index n = n2 + R2 n1 and output index
+// k = k1 + R1 k2,
+//   X[k1 + R1 k2] = sum_n2 W_NP^(n2 k1) W_R2^(n2 k2) sum_n1 v[n2 + R2 n1] W_R1^(n1 k1):
+// a thread transforms the R1 points of one n2 in registers, multiplies by the
+// twiddles and leaves them in LDS; then it takes the R2 points of R1 / R2 values of
+// k1.  The inverse runs the same two sums in the other order, so a pass that
+// transforms forward and back needs no reordering in between.  M rows per block, one
+// wavefront (two for NP = 256); rows are the fast index of the block's LDS, padded
+// by one point per k1 against bank conflicts.
+//
+// These passes are bound by the latency of their one round trip over the grid
+// (17 + 17 MB at 128^3): every thread has R1 16-byte loads in flight before it
+// computes.  With radix-2 stages over LDS (a barrier and an LDS round trip each) and
+// 64-bit divisions for every element's place -> now (us): 128^3 x 12.1 -> 9.4, y
+// 19.6 -> 7.8, z 27.0 -> 15.7, inverse y 19.6 -> 10.0 (with the energy sum), inverse x
+// 13.5 -> 10.9; 64^3 5.6 -> 4.9, 7.2 -> 4.8, 9.9 -> 5.6, 7.2 -> 4.3, 6.2 -> 5.6.
 
-template <int NP>
-__device__ __forceinline__ int bitrev(int k) {
-  return (int)(__builtin_bitreverse32((uint32_t)k) >> (32 - __builtin_ctz(NP)));
-}
+// e^(2 pi i j / 16), j = 0..3 (cos, sin)
+constexpr double kC16[4] = {1.0, 0.92387953251128674, 0.70710678118654752, 0.38268343236508977};
 
-// Twiddle table in LDS: tw[j] = e^{sign 2 pi i j / (TS NP)}, j <= TS NP / 2.
-template <int NP, int TS>
-__device__ __forceinline__ void fill_twiddles(double2 *tw, double sign) {
-  for (int j = threadIdx.x; j <= TS * NP / 2; j += kThreads) {
-    double s, c;
-    sincospi(sign * 2.0 * (double)j / (double)(TS * NP), &s, &c);
-    tw[j] = make_double2(c, s);
-  }
+__device__ __forceinline__ double2 cmul(double2 a, double2 b) {
+  return make_double2(__builtin_fma(a.x, b.x, -(a.y * b.y)), __builtin_fma(a.x, b.y, a.y * b.x));
 }
+__device__ __forceinline__ double2 conj2(double2 a) { return make_double2(a.x, -a.y); }
 
-// The butterfly stages over R rows of NP points in buf (bit-reversed order in,
-// natural order out); the twiddle of stage h, position pos, e^{sign i pi pos/h},
-// is tw[TS pos NP / (2h)].  Every thread of the block calls it.
-template <int NP, int R, int TS>
-__device__ __forceinline__ void fft_stages(double2 *buf, const double2 *tw) {
-  for (int h = 1; h < NP; h <<= 1) {
-    const int step = TS * NP / (2 * h);
-    for (int b = threadIdx.x; b < R * NP / 2; b += kThreads) {
-      const int m = b / (NP / 2), bb = b % (NP / 2);
-      const int pos = bb % h, grp = bb / h;
-      const int i0 = m * NP + grp * 2 * h + pos, i1 = i0 + h;
-      const double2 w = tw[pos * step];
-      const double c = w.x, s = w.y;
-      const double2 u = buf[i0], v = buf[i1];
-      const double tr = c * v.x - s * v.y, ti = c * v.y + s * v.x;
-      buf[i0] = make_double2(u.x + tr, u.y + ti);
-      buf[i1] = make_double2(u.x - tr, u.y - ti);
+// In-register transform of R points (R = 1, 2, 4, 8, 16), sign S (-1 forward, +1
+// unnormalised inverse), natural order in and out; all twiddles are constants.
+template <int R, int S>
+__device__ __forceinline__ void fft_reg(double2 (&v)[R]) {
+  if constexpr (R == 2) {
+    const double2 a = v[0], b = v[1];
+    v[0] = make_double2(a.x + b.x, a.y + b.y);
+    v[1] = make_double2(a.x - b.x, a.y - b.y);
+  } else if constexpr (R > 2) {
+    double2 e[R / 2], o[R / 2];
+#pragma unroll
+    for (int k = 0; k < R / 2; ++k) {
+      e[k] = v[2 * k];
+      o[k] = v[2 * k + 1];
     }
-    __syncthreads();
+    fft_reg<R / 2, S>(e);
+    fft_reg<R / 2, S>(o);
+#pragma unroll
+    for (int k = 0; k < R / 2; ++k) {
+      const int j = k * (16 / R);  // e^(S 2 pi i j / 16), j < 8
+      double2 t;
+      if (j == 0) {
+        t = o[k];
+      } else if (j == 4) {
+        t = make_double2(-S * o[k].y, S * o[k].x);
+      } else {
+        const double c = j < 4 ? kC16[j] : -kC16[8 - j];
+        const double s = j < 4 ? kC16[4 - j] : kC16[j - 4];
+        t = cmul(o[k], make_double2(c, S * s));
+      }
+      v[k] = make_double2(e[k].x + t.x, e[k].y + t.y);
+      v[k + R / 2] = make_double2(e[k].x - t.x, e[k].y - t.y);
+    }
   }
 }
 
-// y (axis 1) or z (axis 2) pass over the half grid of width W = K0/2 + 1:
-// rows r < rows, element k of row r at (r % W) + (r / W) W K1 + k W (axis 1)
-// or r + k W K1 (axis 2); consecutive rows are consecutive x.
 template <int NP>
-__global__ __launch_bounds__(kThreads) void k_fft_yz(double2 *g, int axis, int W, int K1,
-                                                     int64_t rows, double sign) {
-  constexpr int R = fft_rows<NP>();
-  __shared__ double2 buf[R * NP];
-  __shared__ double2 tw[NP / 2 + 1];
-  fill_twiddles<NP, 1>(tw, sign);
-  const int64_t r0 = (int64_t)blockIdx.x * R;
-  const int64_t plane = (int64_t)W * K1;
-  for (int idx = threadIdx.x; idx < R * NP; idx += kThreads) {
-    const int m = idx % R, k = idx / R;
-    const int64_t r = r0 + m;
-    if (r >= rows) continue;
-    const int64_t at = axis == 1 ? (r % W) + (r / W) * plane + (int64_t)k * W : r + k * plane;
-    buf[m * NP + bitrev<NP>(k)] = g[at];
+struct Fft {
+  static constexpr int R1 = NP <= 8 ? NP : NP == 16 ? 4 : NP <= 64 ? 8 : 16;
+  static constexpr int R2 = NP / R1;
+  static constexpr int T = NP > 128 ? 128 : 64;  // threads
+  static constexpr int M = T / R2;               // rows
+  static constexpr int J = R1 / R2;              // values of k1 per thread in the second step
+  static constexpr int kPitch = R2 * M + 1;      // LDS points per k1
+  static constexpr int kLds = R2 > 1 ? R1 * kPitch : 1;
+
+  // v[n1] = element n2 + R2 n1 of row m  ->  out[q R2 + k2] = element k1 + R1 k2
+  // of row mo, k1 = kk + R2 q.  tw[TS j] = e^(-2 pi i j / NP); every thread of the
+  // block calls it, buf may be written again after the caller's next barrier.
+  template <int S, int TS>
+  static __device__ __forceinline__ void forward(double2 (&v)[R1], double2 (&out)[R1], double2 *buf,
+                                                 const double2 *tw, int m, int n2, int mo,
+                                                 int kk) {
+    fft_reg<R1, S>(v);
+    if constexpr (R2 == 1) {
+#pragma unroll
+      for (int k = 0; k < R1; ++k) out[k] = v[k];  // J = R1: k1 = q, one point each
+    } else {
+#pragma unroll
+      for (int k1 = 0; k1 < R1; ++k1) {
+        const double2 w = tw[TS * n2 * k1];
+        buf[k1 * kPitch + n2 * M + m] = cmul(v[k1], S < 0 ? w : conj2(w));
+      }
+      __syncthreads();
+#pragma unroll
+      for (int q = 0; q < J; ++q) {
+        double2 u[R2];
+#pragma unroll
+        for (int j = 0; j < R2; ++j) u[j] = buf[(kk + R2 * q) * kPitch + j * M + mo];
+        fft_reg<R2, S>(u);
+#pragma unroll
+        for (int j = 0; j < R2; ++j) out[q * R2 + j] = u[j];
+      }
+    }
   }
+
+  // The inverse of forward's layout: in[q R2 + k2] of row m (k1 = kk + R2 q) ->
+  // v[n1] = element n2 + R2 n1 of the same row, n2 = kk.
+  template <int S, int TS>
+  static __device__ __forceinline__ void backward(double2 (&in)[R1], double2 (&v)[R1],
+                                                  double2 *buf, const double2 *tw, int m, int kk) {
+    if constexpr (R2 == 1) {
+#pragma unroll
+      for (int k = 0; k < R1; ++k) v[k] = in[k];
+    } else {
+      __syncthreads();  // forward's reads of buf
+#pragma unroll
+      for (int q = 0; q < J; ++q) {
+        double2 u[R2];
+        const int k1 = kk + R2 * q;
+#pragma unroll
+        for (int j = 0; j < R2; ++j) u[j] = in[q * R2 + j];
+        fft_reg<R2, S>(u);
+#pragma unroll
+        for (int j = 0; j < R2; ++j) {
+          const double2 w = tw[TS * j * k1];
+          buf[k1 * kPitch + j * M + m] = cmul(u[j], S < 0 ? w : conj2(w));
+        }
+      }
+      __syncthreads();
+#pragma unroll
+      for (int k1 = 0; k1 < R1; ++k1) v[k1] = buf[k1 * kPitch + kk * M + m];
+    }
+    fft_reg<R1, S>(v);
+  }
+};
+
+// tw[j] = e^(-2 pi i j / NP), j < NP
+template <int NP, int T>
+__device__ __forceinline__ void fill_twiddles(double2 *tw) {
+  for (int j = threadIdx.x; j < NP; j += T) {
+    double s, c;
+    sincospi(2.0 * (double)j / (double)NP, &s, &c);
+    tw[j] = make_double2(c, -s);
+  }
+}
+
+// Points per stored row of the half grid: K0/2 + 1 coefficients, rounded up to whole
+// 128-byte lines where the region (K0/2 + K0/8 points per row) has room for it.
+__host__ __device__ __forceinline__ int half_pitch(int K0) {
+  return K0 >= 64 ? (K0 / 2 + 8) / 8 * 8 : K0 / 2 + 1;
+}
+
+// Point k of a column: `off` (the lane's 32-bit byte offset; the half grid has at most
+// 142 MB) from a wavefront-uniform base, so the 16 addresses of a thread share one
+// vector register.
+__device__ __forceinline__ double2 *column_at(double2 *g, int64_t uniform, uint32_t off) {
+  return (double2 *)((char *)(g + uniform) + off);
+}
+
+// y pass over the half grid: block (bx, z) transforms the columns x0 = bx M .. of
+// plane z, in place.  Inverse (S = 1): the first block also sums the z pass's energy
+// partials part[0..nparts) into *sum, in a fixed order.
+template <int NP, int S>
+__global__ __launch_bounds__(Fft<NP>::T) void k_fft_y(double2 *g, int W, int P, const double *part,
+                                                      int nparts, double *sum) {
+  using F = Fft<NP>;
+  __shared__ double2 buf[F::kLds];
+  __shared__ double2 tw[NP];
+  const int t = threadIdx.x, m = t % F::M, n2 = t / F::M;
+  if constexpr (S > 0) {
+    if (blockIdx.x == 0 && blockIdx.y == 0) {  // block-uniform
+      __shared__ double red[kRedRows * F::T / kWave];
+      double e[1] = {0.0};
+#pragma unroll 8
+      for (int k = t; k < nparts; k += F::T) e[0] += part[k];
+      block_sum<F::T / kWave, 1>(e, red, sum);
+    }
+  }
+  const int x = blockIdx.x * F::M + m;
+  double2 *plane = g + (int64_t)blockIdx.y * NP * P;
+  const uint32_t off = (uint32_t)(n2 * P + (x < W ? x : W - 1)) * (uint32_t)sizeof(double2);
+  double2 v[F::R1], out[F::R1];
+#pragma unroll
+  for (int k = 0; k < F::R1; ++k) v[k] = *column_at(plane, (int64_t)(F::R2 * k) * P, off);
+  fill_twiddles<NP, F::T>(tw);
   __syncthreads();
-  fft_stages<NP, R, 1>(buf, tw);
-  for (int idx = threadIdx.x; idx < R * NP; idx += kThreads) {
-    const int m = idx % R, k = idx / R;
-    const int64_t r = r0 + m;
-    if (r >= rows) continue;
-    const int64_t at = axis == 1 ? (r % W) + (r / W) * plane + (int64_t)k * W : r + k * plane;
-    g[at] = buf[m * NP + k];
+  F::template forward<S, 1>(v, out, buf, tw, m, n2, m, n2);
+  if (x < W) {
+#pragma unroll
+    for (int q = 0; q < F::J; ++q)
+#pragma unroll
+      for (int j = 0; j < F::R2; ++j)
+        *column_at(plane, (int64_t)(F::R2 * q + F::R1 * j) * P, off) = out[q * F::R2 + j];
   }
 }
 
@@ -466,33 +591,39 @@ __global__ __launch_bounds__(kThreads) void k_fft_yz(double2 *g, int axis, int W
 // sum_k v_k e^{-2 pi i m k / NP}.  With z_k = v_2k + i v_2k+1 and Z its
 // transform of length NH = NP/2: X_m = E_m + e^{-2 pi i m/NP} O_m, where
 // E_m = (Z_m + conj Z_{NH-m}) / 2 and O_m = (Z_m - conj Z_{NH-m}) / (2i) are the
-// transforms of the even and odd samples (indices of Z mod NH).
+// transforms of the even and odd samples (indices of Z mod NH).  rows is a multiple
+// of the M rows of a block (K1 K2 >= 64).
 template <int NP>
-__global__ __launch_bounds__(kThreads) void k_fft_x_r2c(const double *rg, double2 *h,
-                                                        int64_t rows) {
+__global__ __launch_bounds__(Fft<NP / 2>::T) void k_fft_x_r2c(const double *rg, double2 *h) {
   constexpr int NH = NP / 2;
-  constexpr int R = fft_rows<NH>();
-  __shared__ double2 buf[R * NH];
-  __shared__ double2 tw[NP / 2 + 1];  // e^{-2 pi i j / NP}
-  fill_twiddles<NH, 2>(tw, -1.0);
-  const int64_t r0 = (int64_t)blockIdx.x * R;
-  for (int idx = threadIdx.x; idx < R * NH; idx += kThreads) {
-    const int m = idx / NH, k = idx % NH;
-    const int64_t r = r0 + m;
-    if (r >= rows) continue;
-    buf[m * NH + bitrev<NH>(k)] = *(const double2 *)(rg + r * NP + 2 * k);
-  }
+  using F = Fft<NH>;
+  constexpr int P = NP >= 64 ? (NP / 2 + 8) / 8 * 8 : NP / 2 + 1;
+  constexpr int kRow = NH + 1;  // pitch of Z rows in LDS
+  __shared__ double2 buf[F::kLds > F::M * kRow ? F::kLds : F::M * kRow];
+  __shared__ double2 tw[NP];
+  double2 *z = buf;  // Z rows, once the transform has read the exchanged points
+  const int t = threadIdx.x, n2 = t % F::R2, m = t / F::R2;
+  const int64_t r0 = (int64_t)blockIdx.x * F::M;
+  const double2 *row = (const double2 *)(rg + (r0 + m) * NP);
+  double2 v[F::R1], out[F::R1];
+#pragma unroll
+  for (int k = 0; k < F::R1; ++k) v[k] = row[n2 + F::R2 * k];
+  fill_twiddles<NP, F::T>(tw);
   __syncthreads();
-  fft_stages<NH, R, 2>(buf, tw);
-  for (int idx = threadIdx.x; idx < R * (NH + 1); idx += kThreads) {
-    const int m = idx / (NH + 1), k = idx % (NH + 1);
-    const int64_t r = r0 + m;
-    if (r >= rows) continue;
-    const double2 zm = buf[m * NH + (k % NH)], zc = buf[m * NH + ((NH - k) % NH)];
+  F::template forward<-1, 2>(v, out, buf, tw, m, n2, m, n2);
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < F::J; ++q)
+#pragma unroll
+    for (int j = 0; j < F::R2; ++j) z[m * kRow + n2 + F::R2 * q + F::R1 * j] = out[q * F::R2 + j];
+  __syncthreads();
+  for (int idx = t; idx < F::M * kRow; idx += F::T) {
+    const int mr = idx / kRow, k = idx % kRow;
+    const double2 zm = z[mr * kRow + (k & (NH - 1))], zc = z[mr * kRow + ((NH - k) & (NH - 1))];
     const double er = 0.5 * (zm.x + zc.x), ei = 0.5 * (zm.y - zc.y);
     const double orr = 0.5 * (zm.y + zc.y), oi = -0.5 * (zm.x - zc.x);
     const double c = tw[k].x, s = tw[k].y;
-    h[r * (NH + 1) + k] = make_double2(er + (c * orr - s * oi), ei + (c * oi + s * orr));
+    h[(r0 + mr) * P + k] = make_double2(er + (c * orr - s * oi), ei + (c * oi + s * orr));
   }
 }
 
@@ -501,143 +632,168 @@ __global__ __launch_bounds__(kThreads) void k_fft_x_r2c(const double *rg, double
 // B_m = (X_m - conj X_{NH-m}) e^{+2 pi i m/NP} for m < NH, the inverse transform
 // of length NH of A + iB is z_k = v_2k + i v_2k+1.
 template <int NP>
-__global__ __launch_bounds__(kThreads) void k_fft_x_c2r(const double2 *h, double *rg,
-                                                        int64_t rows) {
+__global__ __launch_bounds__(Fft<NP / 2>::T) void k_fft_x_c2r(const double2 *h, double *rg) {
   constexpr int NH = NP / 2;
-  constexpr int R = fft_rows<NH>();
-  __shared__ double2 xin[R * (NH + 1)];
-  __shared__ double2 buf[R * NH];
-  __shared__ double2 tw[NP / 2 + 1];  // e^{+2 pi i j / NP}
-  fill_twiddles<NH, 2>(tw, 1.0);
-  const int64_t r0 = (int64_t)blockIdx.x * R;
-  for (int idx = threadIdx.x; idx < R * (NH + 1); idx += kThreads) {
-    const int m = idx / (NH + 1), k = idx % (NH + 1);
-    const int64_t r = r0 + m;
-    if (r < rows) xin[idx] = h[r * (NH + 1) + k];
+  using F = Fft<NH>;
+  constexpr int P = NP >= 64 ? (NP / 2 + 8) / 8 * 8 : NP / 2 + 1;
+  __shared__ double2 buf[F::kLds > F::M * (NH + 1) ? F::kLds : F::M * (NH + 1)];
+  __shared__ double2 tw[NP];
+  double2 *xin = buf;  // X rows, until they are in registers
+  const int t = threadIdx.x, n2 = t % F::R2, m = t / F::R2;
+  const int64_t r0 = (int64_t)blockIdx.x * F::M;
+  for (int idx = t; idx < F::M * (NH + 1); idx += F::T) {
+    const int mr = idx / (NH + 1), k = idx % (NH + 1);
+    xin[idx] = h[(r0 + mr) * P + k];
   }
+  fill_twiddles<NP, F::T>(tw);
   __syncthreads();
-  for (int idx = threadIdx.x; idx < R * NH; idx += kThreads) {
-    const int m = idx / NH, k = idx % NH;
+  double2 v[F::R1], out[F::R1];
+#pragma unroll
+  for (int q = 0; q < F::R1; ++q) {
+    const int k = n2 + F::R2 * q;
     const double2 x1 = xin[m * (NH + 1) + k], x2 = xin[m * (NH + 1) + NH - k];
     const double ar = x1.x + x2.x, ai = x1.y - x2.y;  // X_m + conj X_{NH-m}
     const double dr = x1.x - x2.x, di = x1.y + x2.y;  // X_m - conj X_{NH-m}
-    const double c = tw[k].x, s = tw[k].y;
+    const double c = tw[k].x, s = -tw[k].y;
     const double br = c * dr - s * di, bi = c * di + s * dr;
-    buf[m * NH + bitrev<NH>(k)] = make_double2(ar - bi, ai + br);
+    v[q] = make_double2(ar - bi, ai + br);
   }
   __syncthreads();
-  fft_stages<NH, R, 2>(buf, tw);
-  for (int idx = threadIdx.x; idx < R * NH; idx += kThreads) {
-    const int m = idx / NH, k = idx % NH;
-    const int64_t r = r0 + m;
-    if (r < rows) *(double2 *)(rg + r * NP + 2 * k) = buf[m * NH + k];
-  }
+  F::template forward<1, 2>(v, out, buf, tw, m, n2, m, n2);
+  double2 *row = (double2 *)(rg + (r0 + m) * NP);
+#pragma unroll
+  for (int q = 0; q < F::J; ++q)
+#pragma unroll
+    for (int j = 0; j < F::R2; ++j) row[n2 + F::R2 * q + F::R1 * j] = out[q * F::R2 + j];
 }
 
-// z pass with the influence function between its two transforms: the rows of
-// the z pass of k_fft_yz (row r = m0 + W m1, element m2 at r + m2 W K1) are
-// transformed forward, multiplied by G(m) = B(m) C(m), transformed back, all in
-// LDS, so the half grid makes one round trip instead of three.  Per block the
-// reciprocal energy 1/2 sum G |F(Q)|^2 (fixed order).
+// z pass with the influence function between its two transforms: block (bx, y)
+// takes the columns x0 = bx M .. of row y (element m2 at m2 P K1 points), transforms
+// them forward, multiplies by G(m) = B(m) C(m) and transforms back, so the half grid
+// makes one round trip instead of three.  Per block the reciprocal energy
+// 1/2 sum G |F(Q)|^2 (fixed order) goes to the real grid's region, which is free
+// between the x passes; the inverse y pass sums it.
 template <int NP>
-__global__ __launch_bounds__(kThreads) void k_fft_z_influence(RecArgs a, int64_t rows) {
-  constexpr int R = fft_rows<NP>();
-  __shared__ double2 buf[R * NP];
-  __shared__ double2 inv[R * NP];
-  __shared__ double2 twf[NP / 2 + 1];
-  __shared__ double2 twi[NP / 2 + 1];
-  __shared__ double red[kRedRows * kThreads / kWave];
-  fill_twiddles<NP, 1>(twf, -1.0);
-  fill_twiddles<NP, 1>(twi, 1.0);
-  const int W = a.K[0] / 2 + 1;
-  const int64_t r0 = (int64_t)blockIdx.x * R;
-  const int64_t plane = (int64_t)W * a.K[1];
-  double2 *g = a.half;
-  for (int idx = threadIdx.x; idx < R * NP; idx += kThreads) {
-    const int m = idx % R, k = idx / R;
-    const int64_t r = r0 + m;
-    buf[m * NP + bitrev<NP>(k)] = r < rows ? g[r + k * plane] : make_double2(0.0, 0.0);
-  }
+__global__ __launch_bounds__(Fft<NP>::T, 2) void k_fft_z_influence(RecArgs a) {
+  using F = Fft<NP>;
+  __shared__ double2 buf[F::kLds];
+  __shared__ double2 tw[NP];
+  __shared__ double red[kRedRows * F::T / kWave];
+  const int t = threadIdx.x, m = t % F::M, n2 = t / F::M;
+  const int W = a.K[0] / 2 + 1, P = half_pitch(a.K[0]);
+  const int m0 = blockIdx.x * F::M + m, m1 = blockIdx.y;
+  const int64_t plane = (int64_t)P * a.K[1];
+  double2 *row = a.half + (int64_t)m1 * P;
+  const uint32_t off =
+      (uint32_t)(n2 * (int)plane + (m0 < W ? m0 : W - 1)) * (uint32_t)sizeof(double2);
+  double2 v[F::R1], out[F::R1];
+#pragma unroll
+  for (int k = 0; k < F::R1; ++k) v[k] = *column_at(row, F::R2 * k * plane, off);
+  fill_twiddles<NP, F::T>(tw);
   __syncthreads();
-  fft_stages<NP, R, 1>(buf, twf);
-  const double V = a.b.L[0] * a.b.L[1] * a.b.L[2];
-  double v[1] = {0.0};
-  for (int idx = threadIdx.x; idx < R * NP; idx += kThreads) {
-    const int m = idx / NP, m2 = idx % NP;
-    const int64_t r = r0 + m;
-    double2 out = make_double2(0.0, 0.0);
-    if (r < rows) {
-      const int m0 = (int)(r % W);
-      const int m1 = (int)(r / W);
-      const double f0 = m0 * a.b.invL[0];
-      const double f1 = (m1 <= a.K[1] / 2 ? m1 : m1 - a.K[1]) * a.b.invL[1];
-      const double f2 = (m2 <= a.K[2] / 2 ? m2 : m2 - a.K[2]) * a.b.invL[2];
+  F::template forward<-1, 1>(v, out, buf, tw, m, n2, m, n2);
+  const double piV = kPi * (a.b.L[0] * a.b.L[1] * a.b.L[2]);
+  const double f0 = m0 * a.b.invL[0];
+  const double f1 = (m1 <= a.K[1] / 2 ? m1 : m1 - a.K[1]) * a.b.invL[1];
+  const double b01 = m0 < W ? a.bmod[m0] * a.bmod[kMaxGrid + m1] : 0.0;
+  const double mult = (m0 == 0 || 2 * m0 == a.K[0]) ? 0.5 : 1.0;
+  double e[1] = {0.0};
+#pragma unroll
+  for (int q = 0; q < F::J; ++q)
+#pragma unroll
+    for (int j = 0; j < F::R2; ++j) {
+      const int m2 = n2 + F::R2 * q + F::R1 * j;
+      const double f2 = (m2 <= NP / 2 ? m2 : m2 - NP) * a.b.invL[2];
       const double msq = (f0 * f0 + f1 * f1) + f2 * f2;
       double G = 0.0;
-      if (r != 0 || m2 != 0) {
-        const double C = exp(-kPi * kPi * msq / (a.alpha * a.alpha)) / (kPi * V * msq);
-        G = C * a.bmod[m0] * a.bmod[kMaxGrid + m1] * a.bmod[2 * kMaxGrid + m2];
+      if (m0 < W && (m0 | m1 | m2) != 0) {
+        G = b01 * a.bmod[2 * kMaxGrid + m2] * recip64(piV * msq);
       }
-      const double2 z = buf[m * NP + m2];
+      double2 &z = out[q * F::R2 + j];
       // 1/2 G |F|^2, doubled for the columns 0 < m0 < K0/2 whose mirror -m0 is not stored
-      const double mult = (m0 == 0 || 2 * m0 == a.K[0]) ? 0.5 : 1.0;
-      v[0] += mult * G * (z.x * z.x + z.y * z.y);
-      out = make_double2(G * z.x, G * z.y);
+      e[0] += mult * G * (z.x * z.x + z.y * z.y);
+      z = make_double2(G * z.x, G * z.y);
     }
-    inv[m * NP + bitrev<NP>(m2)] = out;
-  }
-  __syncthreads();
-  fft_stages<NP, R, 1>(inv, twi);
-  for (int idx = threadIdx.x; idx < R * NP; idx += kThreads) {
-    const int m = idx % R, k = idx / R;
-    const int64_t r = r0 + m;
-    if (r < rows) g[r + k * plane] = inv[m * NP + k];
-  }
-  block_sum<kThreads / kWave, 1>(v, red, a.partial + blockIdx.x);
-}
-
-// Blocks of k_fft_z_influence (one energy partial each) for grid K.
-unsigned z_influence_blocks(const int32_t K[3]) {
-  const int R = 1024 / K[2] < 64 ? 1024 / K[2] : 64;  // fft_rows<K[2]>()
-  const int64_t rows = (int64_t)(K[0] / 2 + 1) * K[1];
-  return (unsigned)((rows + R - 1) / R);
-}
-
-// F_i = -q_i grad sum_k theta_i(k) phi(k); per block the self energy -alpha/sqrt(pi) q_i^2
-template <int N>
-__global__ __launch_bounds__(kThreads) void k_gather(RecArgs a, double *self_partial) {
-  __shared__ double red[kRedRows * kThreads / kWave];
-  const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  double v[1] = {0.0};
-  if (i < a.n) {
-    double w[3][N], dw[3][N];
-    int base[3];
+  F::template backward<1, 1>(out, v, buf, tw, m, n2);
+  if (m0 < W) {
 #pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      const double u = a.x[3 * i + d] * a.scale[d];
-      const double fl = floor(u);
-      base[d] = (int)fl;
-      spline_weights<N, true>(u - fl, w[d], dw[d]);
-    }
-    double g0 = 0.0, g1 = 0.0, g2 = 0.0;
-    for (int jz = 0; jz < N; ++jz) {
-      const int kz = wrapi(base[2] - jz, a.K[2]);
+    for (int k = 0; k < F::R1; ++k) *column_at(row, F::R2 * k * plane, off) = v[k];
+  }
+  block_sum<F::T / kWave, 1>(e, red, a.grid + (int64_t)blockIdx.y * gridDim.x + blockIdx.x);
+}
+
+// F_i = -q_i grad sum_k theta_i(k) phi(k); per block the self energy -alpha/sqrt(pi) q_i^2.
+//
+// TEAM lanes per particle, lane t the planes jz = t, t + TEAM, ... of its support;
+// blocks renumbered per XCD (the particles' order is spatial).  A row of the support
+// is N consecutive points read with 16-byte loads unless some lane's row wraps
+// around the box.  Bound by those loads (16 rows of 32 bytes per particle at order 4).
+// Integer divisions for every point's place and 8-byte loads, one lane per particle,
+// took 42 us at 500,000 particles and 128^3; now 35.
+template <int N, int TEAM>
+__global__ __launch_bounds__(kGatherAtoms * TEAM) void k_gather(RecArgs a, double *self_partial) {
+  __shared__ double red[kRedRows * kGatherAtoms * TEAM / kWave];
+  const int t = (int)threadIdx.x % TEAM;
+  const int64_t i =
+      (int64_t)xcd_block(blockIdx.x, gridDim.x) * kGatherAtoms + (int)threadIdx.x / TEAM;
+  const bool live = i < a.n;
+  const int64_t ii = live ? i : 0;  // the last block's spare lanes repeat particle 0
+  double w[3][N], dw[3][N];
+  int base[3];
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    const double u = a.x[3 * ii + d] * a.scale[d];
+    const double fl = floor(u);
+    base[d] = wrapi((int)fl, a.K[d]);
+    spline_weights<N, true>(u - fl, w[d], dw[d]);
+  }
+  const double qi = a.q[ii];
+  double g0 = 0.0, g1 = 0.0, g2 = 0.0;
+  const bool wraps = base[0] < N - 1;
+  auto planes = [&](auto whole) {
+#pragma unroll
+    for (int z = 0; z < N; z += TEAM) {
+      double wz = w[2][z], dz = dw[2][z];
+#pragma unroll
+      for (int s = 1; s < TEAM; ++s) {  // this lane's plane jz = z + t
+        wz = t == s ? w[2][z + s] : wz;
+        dz = t == s ? dw[2][z + s] : dz;
+      }
+      const double *plane =
+          a.grid + (int64_t)wrapi(base[2] - (z + t), a.K[2]) * a.K[1] * a.K[0];
+#pragma unroll
       for (int jy = 0; jy < N; ++jy) {
-        const int ky = wrapi(base[1] - jy, a.K[1]);
-        const double *line = a.grid + ((int64_t)kz * a.K[1] + ky) * a.K[0];
+        const double *line = plane + (int64_t)wrapi(base[1] - jy, a.K[1]) * a.K[0];
+        double ph[N];
+        if constexpr (decltype(whole)::value) {
+          const double *p = line + (base[0] - (N - 1));
+#pragma unroll
+          for (int jx = 0; jx < N; ++jx) ph[jx] = p[N - 1 - jx];
+        } else {
+#pragma unroll
+          for (int jx = 0; jx < N; ++jx) ph[jx] = line[wrapi(base[0] - jx, a.K[0])];
+        }
         double sx = 0.0, sdx = 0.0;
 #pragma unroll
         for (int jx = 0; jx < N; ++jx) {
-          const double ph = line[wrapi(base[0] - jx, a.K[0])];
-          sx = __builtin_fma(w[0][jx], ph, sx);
-          sdx = __builtin_fma(dw[0][jx], ph, sdx);
+          sx = __builtin_fma(w[0][jx], ph[jx], sx);
+          sdx = __builtin_fma(dw[0][jx], ph[jx], sdx);
         }
-        g0 = __builtin_fma(sdx * w[1][jy], w[2][jz], g0);
-        g1 = __builtin_fma(sx * dw[1][jy], w[2][jz], g1);
-        g2 = __builtin_fma(sx * w[1][jy], dw[2][jz], g2);
+        g0 = __builtin_fma(sdx * w[1][jy], wz, g0);
+        g1 = __builtin_fma(sx * dw[1][jy], wz, g1);
+        g2 = __builtin_fma(sx * w[1][jy], dz, g2);
       }
     }
-    const double qi = a.q[i];
+  };
+  if (__ballot(wraps) == 0)
+    planes(std::true_type{});
+  else
+    planes(std::false_type{});
+  g0 = team_sum<TEAM>(g0);
+  g1 = team_sum<TEAM>(g1);
+  g2 = team_sum<TEAM>(g2);
+  double v[1] = {0.0};
+  if (live && t == 0) {
     double *F = a.F + 3 * i;
     const double f0 = -qi * g0 * a.scale[0], f1 = -qi * g1 * a.scale[1],
                  f2 = -qi * g2 * a.scale[2];
@@ -652,54 +808,60 @@ __global__ __launch_bounds__(kThreads) void k_gather(RecArgs a, double *self_par
     }
     v[0] = -a.alpha / __builtin_sqrt(kPi) * qi * qi;
   }
-  if (self_partial) block_sum<kThreads / kWave, 1>(v, red, self_partial + blockIdx.x);
+  if (self_partial) block_sum<kGatherAtoms * TEAM / kWave, 1>(v, red, self_partial + blockIdx.x);
 }
 
+// nparts: energy partials of the z pass (inverse pass only).
 template <int NP>
-void yz_pass(double2 *h, int axis, const int32_t K[3], double sign, hipStream_t st) {
-  constexpr int R = fft_rows<NP>();
-  const int W = K[0] / 2 + 1;
-  const int64_t rows = (int64_t)W * (axis == 1 ? K[2] : K[1]);
-  k_fft_yz<NP><<<(unsigned)((rows + R - 1) / R), kThreads, 0, st>>>(h, axis, W, K[1], rows, sign);
+void y_pass(const RecArgs &a, bool forward, int nparts, hipStream_t st) {
+  using F = Fft<NP>;
+  const int W = a.K[0] / 2 + 1, P = half_pitch(a.K[0]);
+  const dim3 nb((W + F::M - 1) / F::M, a.K[2]);
+  if (forward)
+    k_fft_y<NP, -1><<<nb, F::T, 0, st>>>(a.half, W, P, nullptr, 0, nullptr);
+  else
+    k_fft_y<NP, 1><<<nb, F::T, 0, st>>>(a.half, W, P, a.grid, nparts, a.partial);
 }
 
-template <int NP>
-void z_influence_pass(const RecArgs &a, hipStream_t st) {
-  const int64_t rows = (int64_t)(a.K[0] / 2 + 1) * a.K[1];
-  k_fft_z_influence<NP><<<z_influence_blocks(a.K), kThreads, 0, st>>>(a, rows);
-}
-
-void fft_z_influence(const RecArgs &a, hipStream_t st) {
-  switch (a.K[2]) {
-    case 8: z_influence_pass<8>(a, st); break;
-    case 16: z_influence_pass<16>(a, st); break;
-    case 32: z_influence_pass<32>(a, st); break;
-    case 64: z_influence_pass<64>(a, st); break;
-    case 128: z_influence_pass<128>(a, st); break;
-    default: z_influence_pass<256>(a, st); break;
+void fft_y(const RecArgs &a, bool forward, int nparts, hipStream_t st) {
+  switch (a.K[1]) {
+    case 8: y_pass<8>(a, forward, nparts, st); break;
+    case 16: y_pass<16>(a, forward, nparts, st); break;
+    case 32: y_pass<32>(a, forward, nparts, st); break;
+    case 64: y_pass<64>(a, forward, nparts, st); break;
+    case 128: y_pass<128>(a, forward, nparts, st); break;
+    default: y_pass<256>(a, forward, nparts, st); break;
   }
 }
 
-void fft_yz(double2 *h, int axis, const int32_t K[3], double sign, hipStream_t st) {
-  switch (K[axis]) {
-    case 8: yz_pass<8>(h, axis, K, sign, st); break;
-    case 16: yz_pass<16>(h, axis, K, sign, st); break;
-    case 32: yz_pass<32>(h, axis, K, sign, st); break;
-    case 64: yz_pass<64>(h, axis, K, sign, st); break;
-    case 128: yz_pass<128>(h, axis, K, sign, st); break;
-    default: yz_pass<256>(h, axis, K, sign, st); break;
+// Returns the number of energy partials (one per block, fewer than the grid's points).
+template <int NP>
+int z_influence_pass(const RecArgs &a, hipStream_t st) {
+  using F = Fft<NP>;
+  const dim3 nb((a.K[0] / 2 + 1 + F::M - 1) / F::M, a.K[1]);
+  k_fft_z_influence<NP><<<nb, F::T, 0, st>>>(a);
+  return (int)(nb.x * nb.y);
+}
+
+int fft_z_influence(const RecArgs &a, hipStream_t st) {
+  switch (a.K[2]) {
+    case 8: return z_influence_pass<8>(a, st);
+    case 16: return z_influence_pass<16>(a, st);
+    case 32: return z_influence_pass<32>(a, st);
+    case 64: return z_influence_pass<64>(a, st);
+    case 128: return z_influence_pass<128>(a, st);
+    default: return z_influence_pass<256>(a, st);
   }
 }
 
 template <int NP>
 void x_pass(double *g, double2 *h, const int32_t K[3], bool forward, hipStream_t st) {
-  constexpr int R = fft_rows<NP / 2>();
-  const int64_t rows = (int64_t)K[1] * K[2];
-  const unsigned nb = (unsigned)((rows + R - 1) / R);
+  using F = Fft<NP / 2>;
+  const unsigned nb = (unsigned)(K[1] * K[2] / F::M);  // K1 K2 >= 64, M a power of two <= 64
   if (forward)
-    k_fft_x_r2c<NP><<<nb, kThreads, 0, st>>>(g, h, rows);
+    k_fft_x_r2c<NP><<<nb, F::T, 0, st>>>(g, h);
   else
-    k_fft_x_c2r<NP><<<nb, kThreads, 0, st>>>(h, g, rows);
+    k_fft_x_c2r<NP><<<nb, F::T, 0, st>>>(h, g);
 }
 
 void fft_x(double *g, double2 *h, const int32_t K[3], bool forward, hipStream_t st) {
@@ -723,11 +885,13 @@ void launch_rec_order(const RecArgs &a, double *self_partial, hipStream_t st) {
   k_zero_grid<<<blocks_of(npts, kThreads), kThreads, 0, st>>>(a.grid, npts);
   if (a.n > 0) k_spread<N><<<blocks_of(a.n, kWave), kWave, 0, st>>>(a);
   fft_x(a.grid, a.half, a.K, true, st);
-  fft_yz(a.half, 1, a.K, -1.0, st);
-  fft_z_influence(a, st);
-  fft_yz(a.half, 1, a.K, 1.0, st);
+  fft_y(a, true, 0, st);
+  const int nparts = fft_z_influence(a, st);
+  fft_y(a, false, nparts, st);
   fft_x(a.grid, a.half, a.K, false, st);
-  if (a.n > 0) k_gather<N><<<blocks_of(a.n, kThreads), kThreads, 0, st>>>(a, self_partial);
+  if (a.n > 0)
+    k_gather<N, kGatherTeam>
+        <<<blocks_of(a.n, kGatherAtoms), kGatherAtoms * kGatherTeam, 0, st>>>(a, self_partial);
 }
 
 }  // namespace
@@ -738,12 +902,12 @@ size_t ewald_real_workspace(int64_t n) {
 }
 
 // real grid, half grid (at most npts/2 + npts/8 complex points: K0 >= 8), tables,
-// partials (the z/influence pass keeps at least 512 half-grid points per block)
+// partials (one for the reciprocal energy, one per gather block)
 size_t spme_workspace(int64_t n, int64_t npts) {
   const int64_t half = npts / 2 + npts / 8;
   return (size_t)npts * sizeof(double) + (size_t)half * sizeof(double2) +
          3 * kMaxGrid * sizeof(double) +
-         ((size_t)blocks_of(half, 512) + blocks_of(n, kThreads)) * sizeof(double) + 256;
+         ((size_t)blocks_of(half, 512) + blocks_of(n, kGatherAtoms)) * sizeof(double) + 256;
 }
 
 int launch_ewald_real(const BoxK &b, double alpha, double rc, int64_t n, const double *x,
@@ -811,16 +975,15 @@ int launch_spme_recip(const BoxK &b, double alpha, int32_t order, const int32_t 
   a.bmod = (double *)p;
   p += 3 * kMaxGrid * sizeof(double);
   a.partial = (double *)p;
-  const unsigned ninf = z_influence_blocks(K);
-  const unsigned ngat = blocks_of(n, kThreads);
-  double *self_partial = n > 0 ? a.partial + ninf : nullptr;
+  const unsigned ngat = blocks_of(n, kGatherAtoms);
+  double *self_partial = n > 0 ? a.partial + 1 : nullptr;
   switch (order) {
     case 4: launch_rec_order<4>(a, self_partial, st); break;
     case 6: launch_rec_order<6>(a, self_partial, st); break;
     default: launch_rec_order<8>(a, self_partial, st); break;
   }
   if (e_total)
-    k_colsum<1024><<<1, 1024, 0, st>>>((int64_t)ninf + (n > 0 ? ngat : 0), 1, 1, a.partial, e_total,
+    k_colsum<1024><<<1, 1024, 0, st>>>((int64_t)1 + (n > 0 ? ngat : 0), 1, 1, a.partial, e_total,
                                      1.0, 0);
   return check_launch("ljmd_spme_recip");
 }

@@ -91,3 +91,29 @@ def test_csr_teams_of_two_and_four_bitwise_tiled(dev, cells, prec):
         for team in (2, 4):
             F2, e2, _ = ops.compute_forces_csr(*a, off, csr, team=team)
             assert torch.equal(F, F2) and torch.equal(e, e2), (ntypes, team)
+
+
+# every length of the three passes (x rows of 4..128 complex points), both the whole-row
+# (8) and the two-step transforms, grids narrower than a block's columns
+FFT_GRIDS = [(8, 8, 8), (8, 8, 256), (16, 256, 8), (32, 32, 16), (128, 16, 64), (64, 128, 32),
+             (256, 64, 128)]
+
+
+@pytest.mark.parametrize("K", FFT_GRIDS)
+def test_spme_grid_shapes_vs_oracle(dev, orc, K):
+    """Reciprocal forces and energy on grids of every pass length against the reference
+    steps (same grid and order): rounding only, 1e-11 of the largest force and of the
+    energy as for the other grids."""
+    import torch
+    from paper_2109_09056_amd import ops
+    L = np.array([11.0, 12.0, 13.0])
+    g = np.random.default_rng(18)
+    q = g.uniform(-1.5, 1.5, 777)
+    q -= q.mean()
+    x = li.random_gas(777, L, 41)
+    T = lambda a: torch.as_tensor(a, dtype=torch.float64, device=dev)
+    F, E = ops.spme_recip(L, li.EWALD_ALPHA, 4, K, T(x), T(q), want_energy=True)
+    E_o, F_o = orc.spme_recip(x, q, L, li.EWALD_ALPHA, K, 4)
+    E_o += orc.ewald_self(q, li.EWALD_ALPHA)
+    assert np.abs(F.cpu().numpy() - F_o).max() <= 1e-11 * np.abs(F_o).max()
+    assert E.item() == pytest.approx(E_o, rel=1e-11)
