@@ -506,7 +506,10 @@ int ljmd_sph_accel_step(const ljmd_box *box, double h, double mass, double c0, d
  *   the reciprocal-space forces (accumulate as above); e_total (or NULL)
  *   receives E_rec + E_self.  ws >= ljmd_workspace_bytes(LJMD_OP_SPME, n,
  *   K[0]*K[1]*K[2], 0), 32-byte aligned; it holds the real charge grid and its
- *   half-complex transform.  The charge
+ *   half-complex transform, and the particles sorted by grid tile with the tiles'
+ *   boxes of charge.  A workspace without the tiles' part (18 bytes per grid
+ *   point, 8 per 256 particles and 8 KB) is accepted too; the charge is then spread
+ *   onto the grid directly, which takes longer.  The charge
  *   spreading uses FP64 atomic additions: results agree run to run to rounding,
  *   not bit for bit.
  *   alpha > 0; rc as for the other pair kernels (LJMD_EBOX if too large).

@@ -69,12 +69,13 @@ int launch_sph_accel(const BoxK &b, double h, double mass, double c0, double rho
                      double *x_out, void *ws, hipStream_t st);
 size_t ewald_real_workspace(int64_t n);
 size_t spme_workspace(int64_t n, int64_t npts);
+size_t spme_min_workspace(int64_t n, int64_t npts);
 int launch_ewald_real(const BoxK &b, double alpha, double rc, int64_t n, const double *x,
                       const double *q, const int32_t *nbr, const int32_t *nnbr, int32_t maxn,
                       double *F, double *e_total, int accumulate, void *ws, hipStream_t st);
 int launch_spme_recip(const BoxK &b, double alpha, int32_t order, const int32_t K[3], int64_t n,
                       const double *x, const double *q, double *F, double *e_total,
-                      int accumulate, void *ws, hipStream_t st);
+                      int accumulate, void *ws, size_t ws_bytes, hipStream_t st);
 size_t stream_workspace(int64_t n);
 int launch_integrate(int stage, double dt, double mass, const BoxK &b, int64_t n, double *x,
                      double *v, const double *F, double *ke, void *ws, hipStream_t st);
@@ -489,10 +490,10 @@ int ljmd_spme_recip(const ljmd_box *box, double alpha, int32_t order, const int3
     return set_error(LJMD_EINVAL, "accumulate = %d must be 0 or 1", accumulate);
   if (n > 0 && (!x || !q || !F)) return set_error(LJMD_EINVAL, "x/q/F is NULL");
   const int64_t npts = (int64_t)K[0] * K[1] * K[2];
-  LJMD_TRY(check_ws(ws, ws_bytes, spme_workspace(n, npts)));
+  LJMD_TRY(check_ws(ws, ws_bytes, spme_min_workspace(n, npts)));
   if (((uintptr_t)ws & 31u) != 0) return set_error(LJMD_EINVAL, "ws must be aligned to 32 bytes");
   return launch_spme_recip(make_box(box), alpha, order, K, n, x, q, F, e_total, accumulate, ws,
-                           (hipStream_t)stream);
+                           ws_bytes, (hipStream_t)stream);
 }
 
 int ljmd_list_to_csr(int64_t n, const int32_t *nbr, const int32_t *nnbr, int32_t maxn,

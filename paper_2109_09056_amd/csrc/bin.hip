@@ -40,33 +40,14 @@ __global__ void k_fill_i32(int32_t *p, int64_t m, int32_t val) {
 }
 
 // Cell of every atom and its rank among the atoms of its cell that were
-// counted before it.  Lanes of a wavefront that fall in the same cell (the
-// common case: the input is usually the previous sorted order) are grouped by
-// a ballot loop, and each group's leader makes one atomic add for the group.
+// counted before it (count_ranks).
 __global__ void k_count(int64_t n, const double *__restrict__ x, GridK g,
                         int32_t *__restrict__ cell, int32_t *__restrict__ rank,
                         int32_t *__restrict__ counts) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const bool live = i < n;
   const int32_t c = live ? cell_of(x + 3 * i, g) : -1;
-  const int lane = threadIdx.x & (kWave - 1);
-  bool pending = live;
-  int32_t r = 0;
-  while (__ballot(pending) != 0) {
-    const uint64_t act = __ballot(pending);
-    const int leader = __builtin_ctzll(act);
-    const int32_t lc = __shfl(c, leader, kWave);
-    const bool mine = pending && c == lc;
-    const uint64_t grp = __ballot(mine);
-    int32_t base = 0;
-    if (lane == leader) base = atomicAdd(&counts[lc], (int32_t)__popcll(grp));
-    base = __shfl(base, leader, kWave);
-    if (mine) {
-      r = base + (int32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(grp >> 32),
-                                                   __builtin_amdgcn_mbcnt_lo((uint32_t)grp, 0u));
-      pending = false;
-    }
-  }
+  const int32_t r = count_ranks(live, c, counts);
   if (live) {
     cell[i] = c;
     rank[i] = r;
@@ -202,6 +183,11 @@ inline unsigned blocks_for(int64_t n, int threads) {
 
 }  // namespace
 
+// start[0..m] = exclusive prefix sums of counts[0..m) and their total.
+void launch_scan(int32_t m, const int32_t *counts, int32_t *start, hipStream_t st) {
+  k_scan<<<1, kScanThreads, 0, st>>>(m, counts, start);
+}
+
 size_t bin_workspace(int64_t n, int64_t ncells) {
   // counts[ncells] + cell[n] + rank[n] + src[n], int32, 256-byte aligned
   auto al = [](size_t b) { return (b + 255) & ~(size_t)255; };
@@ -224,7 +210,7 @@ int launch_bin(const GridK &g, int64_t n, const double *x_in, const double *v_in
 
   k_fill_i32<<<blocks_for(g.ncells, 256), 256, 0, st>>>(counts, g.ncells, 0);
   if (n > 0) k_count<<<blocks_for(n, 256), 256, 0, st>>>(n, x_in, g, cell, rank, counts);
-  k_scan<<<1, kScanThreads, 0, st>>>(g.ncells, counts, cell_start);
+  launch_scan(g.ncells, counts, cell_start, st);
   if (n > 0) {
     k_scatter<<<blocks_for(n, 256), 256, 0, st>>>(n, cell, rank, cell_start, src);
     k_permute<<<blocks_for(g.ncells, kPermWaves), kPermWaves * kWave, 0, st>>>(

@@ -241,6 +241,34 @@ __global__ __launch_bounds__(THREADS) void k_colsum(int64_t rows, int stride, in
   if (t < ncols) out[t] = accumulate ? out[t] + scale * part[t] : scale * part[t];
 }
 
+// One counting step of a counting sort for the lanes of a wavefront: counts[c] grows by
+// the number of live lanes with key c, and every live lane gets its rank among all
+// elements of its key counted so far.  Lanes with the same key (the common case: the
+// input is usually in some spatial order) share one atomic add.  The groups are found
+// first, in registers, and all their leaders add in one instruction: a wavefront waits
+// for one atomic round trip instead of one per group.
+__device__ __forceinline__ int32_t count_ranks(bool live, int32_t key, int32_t *counts) {
+  const int lane = threadIdx.x & (kWave - 1);
+  bool pending = live;
+  int lead = lane, size = 0;
+  int32_t r = 0;
+  for (uint64_t act = __ballot(pending); act != 0; act = __ballot(pending)) {
+    const int leader = __builtin_ctzll(act);
+    const bool mine = pending && key == __builtin_amdgcn_readlane(key, leader);
+    const uint64_t grp = __ballot(mine);
+    if (mine) {
+      lead = leader;
+      size = (int)__popcll(grp);
+      r = (int32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(grp >> 32),
+                                             __builtin_amdgcn_mbcnt_lo((uint32_t)grp, 0u));
+      pending = false;
+    }
+  }
+  int32_t base = 0;
+  if (live && lane == lead) base = atomicAdd(&counts[key], size);
+  return r + __shfl(base, lead, kWave);
+}
+
 // Workgroups are handed to the 8 XCDs round-robin (block b runs on XCD b % 8),
 // and each XCD has its own L2.  Renumbering so that XCD x gets one contiguous
 // run of logical blocks keeps spatially adjacent tiles -- and the neighbor

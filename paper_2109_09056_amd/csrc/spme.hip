@@ -20,8 +20,8 @@
 // Kernels: the real-space pair loop walks the tiled full list with two lanes
 // per particle over packed (x, y, z, q) records (the SPH and LJ traversal),
 // with erfc taken as e^{-x^2} times a tabulated polynomial for erfcx;
-// charge is spread onto a real grid (LDS-privatised per wavefront, then FP64
-// atomics); the 3-D transform is real-to-complex: the x pass turns each row of
+// charge is spread into boxes of grid tiles in LDS, which the x pass adds up as it
+// reads its rows (or onto the grid by FP64 atomics); the 3-D transform is real-to-complex: the x pass turns each row of
 // K0 reals into K0/2 + 1 coefficients through one complex FFT of length K0/2
 // plus a split step, and the y and z passes run on that half grid, each pass two
 // register transforms per row with one exchange through LDS (rows along y and z
@@ -29,12 +29,14 @@
 // lines).  The z pass multiplies by the influence function between its forward and
 // inverse transforms, each coefficient with 0 < m_0 < K0/2 counted twice in the
 // energy (Hermitian symmetry of a real input); the inverse mirrors it and leaves phi
-// real; the gather takes two lanes per particle.
+// real; the gather reads boxes of phi from LDS (or the grid).
 #include <type_traits>
 
 #include "common.h"
 
 namespace ljmd {
+
+void launch_scan(int32_t m, const int32_t *counts, int32_t *start, hipStream_t st);
 
 namespace {
 
@@ -282,8 +284,15 @@ __device__ __forceinline__ int wrapi(int k, int K) { return k & (K - 1); }
 // |b_a(m)|^2 e^{-pi^2 (m'/L_a)^2 / alpha^2} for every axis a, m < K_a (m' = m, or m - K_a
 // above K_a/2), with |b_a(m)|^2 = |sum_{k=0}^{n-2} M_n(k+1) e^{2 pi i m k / K_a}|^-2: the
 // influence function's factors of one axis (its Gaussian is a product over the axes).
+// The blocks beyond those of the tables set z[0..nz) to zero.
+constexpr int kBmodBlocks = 3 * kMaxGrid / kThreads;
 template <int N>
-__global__ __launch_bounds__(kThreads) void k_bmod(RecArgs a) {
+__global__ __launch_bounds__(kThreads) void k_bmod(RecArgs a, double *z, int64_t nz) {
+  if (blockIdx.x >= kBmodBlocks) {
+    const int64_t k = (int64_t)(blockIdx.x - kBmodBlocks) * kThreads + threadIdx.x;
+    if (k < nz) z[k] = 0.0;
+    return;
+  }
   const int t = blockIdx.x * blockDim.x + threadIdx.x;
   const int ax = t / kMaxGrid, m = t % kMaxGrid;
   if (ax >= 3 || m >= a.K[ax]) return;
@@ -301,20 +310,255 @@ __global__ __launch_bounds__(kThreads) void k_bmod(RecArgs a) {
       exp(-kPi * kPi * (f * f) / (a.alpha * a.alpha)) / (re * re + im * im);
 }
 
-__global__ __launch_bounds__(kThreads) void k_zero_grid(double *g, int64_t npts) {
-  const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (i < npts) g[i] = 0.0;
+// ------------------------------------------------- charge and force tiles --
+//
+// The grid is cut into tiles; a particle belongs to the tile of its base point
+// floor(u).  Its support reaches N - 1 points below the base in every dimension, so a
+// tile's particles touch a box of E = T + N - 1 points per dimension.  Particles are
+// sorted by tile (count, scan, scatter of their indices); one block per tile then
+// adds its particles' weights into the box in LDS and writes the box out, and the
+// x pass adds up the (one to eight) boxes that cover each point as it reads its rows:
+// no atomics on the grid, no clearing of it, and the same cost in whatever order the
+// particles come.  The gather takes the box of phi into LDS once per tile.
+//
+// Why: FP64 atomics on the grid run at about 190 per ns whatever their locality, and one
+// box per 64 consecutive particles needs 21 of them per particle (96 us at 500,000
+// particles and 128^3, 41 of them without the atomics); the gather's 16-byte reads of
+// single rows are bound at one lane per cycle.  Measured (us, 500,000 particles and
+// 128^3 / 32,000 and 64^3): clearing and spreading 102 / 41 -> count, scan, scatter,
+// boxes and their sums in the x pass 8.7 + 5.5 + 4.1 + 26.1 + 6.2 / 4.1 + 3.9 + 2.6 +
+// 6.9 + 2.7; gather 35 / 6.9 -> 22.8 / 5.6.  The boxes are bound by the LDS atomics
+// (about 30 cycles per 64 additions), the same with 1, 2 or 4 lanes per particle.
+struct TileK {
+  int32_t lg[3];  // log2 of the tile's edge T
+  int32_t nt[3];  // tiles per dimension
+  int32_t e[3];   // box edge T + N - 1
+  int32_t ntiles, box;  // box: points per box
+  int32_t *count, *start, *key, *rank, *order;
+  double *boxes;
+};
+
+// Tile of a base point, and the point's place in it.
+__device__ __forceinline__ int tile_of(const TileK &t, const int (&b)[3]) {
+  return ((b[2] >> t.lg[2]) * t.nt[1] + (b[1] >> t.lg[1])) * t.nt[0] + (b[0] >> t.lg[0]);
 }
 
-// Charge spreading, one wavefront of 64 consecutive (cell-sorted, hence
-// nearby) particles per block.  The wavefront first adds its n^3 weights per
-// particle into a private box of grid points in LDS (LDS atomics), then adds
-// every non-zero point of that box to the grid with one global FP64 atomic:
-// ~4x fewer global atomics than adding each weight directly, which is what
-// bounds this kernel.  Per axis the box is taken in whichever of two cyclic
-// frames (indices as they are, or shifted by K/2) gives the smaller extent,
-// so groups that straddle a periodic face stay compact.  A group whose box
-// exceeds the LDS capacity adds its weights straight to the grid.
+// Tile and rank in it (in order of counting) of every particle, tile counts, and per
+// block the self energy -alpha/sqrt(pi) q_i^2.  Lanes of a wavefront in the same tile
+// share one atomic add, as in the cell sort.
+__global__ __launch_bounds__(kGatherAtoms) void k_tile_count(RecArgs a, TileK tk,
+                                                            double *self_partial) {
+  __shared__ double red[kRedRows * kGatherAtoms / kWave];
+  const int64_t i = (int64_t)blockIdx.x * kGatherAtoms + threadIdx.x;
+  const bool live = i < a.n;
+  double v[1] = {0.0};
+  int tile = -1;
+  if (live) {
+    int b[3];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) b[d] = wrapi((int)floor(a.x[3 * i + d] * a.scale[d]), a.K[d]);
+    tile = tile_of(tk, b);
+    const double qi = a.q[i];
+    v[0] = -a.alpha / __builtin_sqrt(kPi) * qi * qi;
+  }
+  const int r = count_ranks(live, tile, tk.count);
+  if (live) {
+    tk.key[i] = tile;
+    tk.rank[i] = r;
+  }
+  block_sum<kGatherAtoms / kWave, 1>(v, red, self_partial + blockIdx.x);
+}
+
+__global__ __launch_bounds__(kThreads) void k_tile_scatter(int32_t n, TileK tk) {
+  const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+  if (i < n) tk.order[tk.start[tk.key[i]] + tk.rank[i]] = (int32_t)i;
+}
+
+// Origin of tile `tile` (first base point).
+__device__ __forceinline__ void tile_origin(const TileK &t, int tile, int (&o)[3]) {
+  const int q = tile / t.nt[0];
+  o[0] = (tile - q * t.nt[0]) << t.lg[0];
+  o[2] = (q / t.nt[1]) << t.lg[2];
+  o[1] = (q % t.nt[1]) << t.lg[1];
+}
+
+constexpr int kTileThreads = 512;
+constexpr int kTileTeam = 2;  // lanes per particle
+
+// TEAM lanes per particle, lane t the planes jz = t, t + TEAM, ...
+template <int N, int TX, int TY, int TZ, int TEAM>
+__global__ __launch_bounds__(kTileThreads) void k_spread_tile(RecArgs a, TileK tk) {
+  constexpr int EX = TX + N - 1, EY = TY + N - 1, EZ = TZ + N - 1;
+  __shared__ double box[EX * EY * EZ];
+  const int tile = xcd_block(blockIdx.x, gridDim.x);
+  const int t = (int)threadIdx.x % TEAM;
+  const int end = tk.start[tile + 1];
+  for (int k = threadIdx.x; k < EX * EY * EZ; k += kTileThreads) box[k] = 0.0;
+  __syncthreads();
+  for (int p = tk.start[tile] + (int)threadIdx.x / TEAM; p < end; p += kTileThreads / TEAM) {
+    const int64_t i = tk.order[p];
+    double w[3][N], dw[N];
+    int b[3];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      const double u = a.x[3 * i + d] * a.scale[d];
+      const double fl = floor(u);
+      b[d] = (int)fl & ((d == 0 ? TX : (d == 1 ? TY : TZ)) - 1);  // place in the tile
+      spline_weights<N, false>(u - fl, w[d], dw);
+    }
+    const double qi = a.q[i];
+#pragma unroll
+    for (int z = 0; z < N; z += TEAM) {
+      double wz = w[2][z];
+#pragma unroll
+      for (int s = 1; s < TEAM; ++s) wz = t == s ? w[2][z + s] : wz;
+      wz *= qi;
+#pragma unroll
+      for (int jy = 0; jy < N; ++jy) {
+        const double wyz = wz * w[1][jy];
+        double *row =
+            box + ((b[2] + N - 1 - (z + t)) * EY + (b[1] + N - 1 - jy)) * EX + b[0] + N - 1;
+#pragma unroll
+        for (int jx = 0; jx < N; ++jx) unsafeAtomicAdd(row - jx, wyz * w[0][jx]);
+      }
+    }
+  }
+  __syncthreads();
+  double *out = tk.boxes + (int64_t)tile * (EX * EY * EZ);
+  for (int k = threadIdx.x; k < EX * EY * EZ; k += kTileThreads) out[k] = box[k];
+}
+
+// The forces of a tile's particles from the box of phi (k_gather's sums).
+template <int N, int TX, int TY, int TZ, int TEAM>
+__global__ __launch_bounds__(kTileThreads) void k_gather_tile(RecArgs a, TileK tk) {
+  constexpr int EX = TX + N - 1, EY = TY + N - 1, EZ = TZ + N - 1;
+  __shared__ double box[EX * EY * EZ];
+  const int tile = xcd_block(blockIdx.x, gridDim.x);
+  const int p0 = tk.start[tile], end = tk.start[tile + 1];
+  if (p0 == end) return;  // block-uniform
+  const int t = (int)threadIdx.x % TEAM;
+  int o[3];
+  tile_origin(tk, tile, o);
+  for (int k = threadIdx.x; k < EX * EY * EZ; k += kTileThreads) {
+    const int r = k / EX, lx = k - r * EX, lz = r / EY, ly = r - lz * EY;
+    const int x = wrapi(o[0] + lx - (N - 1), a.K[0]), y = wrapi(o[1] + ly - (N - 1), a.K[1]),
+              z = wrapi(o[2] + lz - (N - 1), a.K[2]);
+    box[k] = a.grid[((int64_t)z * a.K[1] + y) * a.K[0] + x];
+  }
+  __syncthreads();
+  for (int p = p0 + (int)threadIdx.x / TEAM; p < end; p += kTileThreads / TEAM) {
+    const int64_t i = tk.order[p];
+    double w[3][N], dw[3][N];
+    int b[3];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      const double u = a.x[3 * i + d] * a.scale[d];
+      const double fl = floor(u);
+      b[d] = (int)fl & ((d == 0 ? TX : (d == 1 ? TY : TZ)) - 1);
+      spline_weights<N, true>(u - fl, w[d], dw[d]);
+    }
+    const double qi = a.q[i];
+    double g0 = 0.0, g1 = 0.0, g2 = 0.0;
+#pragma unroll
+    for (int z = 0; z < N; z += TEAM) {
+      double wz = w[2][z], dz = dw[2][z];
+#pragma unroll
+      for (int s = 1; s < TEAM; ++s) {
+        wz = t == s ? w[2][z + s] : wz;
+        dz = t == s ? dw[2][z + s] : dz;
+      }
+#pragma unroll
+      for (int jy = 0; jy < N; ++jy) {
+        const double *row =
+            box + ((b[2] + N - 1 - (z + t)) * EY + (b[1] + N - 1 - jy)) * EX + b[0] + N - 1;
+        double sx = 0.0, sdx = 0.0;
+#pragma unroll
+        for (int jx = 0; jx < N; ++jx) {
+          const double ph = row[-jx];
+          sx = __builtin_fma(w[0][jx], ph, sx);
+          sdx = __builtin_fma(dw[0][jx], ph, sdx);
+        }
+        g0 = __builtin_fma(sdx * w[1][jy], wz, g0);
+        g1 = __builtin_fma(sx * dw[1][jy], wz, g1);
+        g2 = __builtin_fma(sx * w[1][jy], dz, g2);
+      }
+    }
+    g0 = team_sum<TEAM>(g0);
+    g1 = team_sum<TEAM>(g1);
+    g2 = team_sum<TEAM>(g2);
+    if (t == 0) {
+      double *F = a.F + 3 * i;
+      const double f0 = -qi * g0 * a.scale[0], f1 = -qi * g1 * a.scale[1],
+                   f2 = -qi * g2 * a.scale[2];
+      if (a.accumulate) {
+        F[0] += f0;
+        F[1] += f1;
+        F[2] += f2;
+      } else {
+        F[0] = f0;
+        F[1] = f1;
+        F[2] = f2;
+      }
+    }
+  }
+}
+
+// Points (x, x + 1), x even, of row (y, z) of the charge grid from the boxes that
+// cover them: per dimension the point's own tile, and the next one when the point is
+// among the last N - 1 of its tile.
+template <int COUNT, int STRIDE>
+__device__ __forceinline__ void row_from_boxes(const TileK &t, int y, int z, int n2,
+                                               double2 (&v)[COUNT]) {
+  const int ty = 1 << t.lg[1], tz = 1 << t.lg[2], tx = 1 << t.lg[0];
+  const int h = t.e[0] - tx;  // N - 1
+  const int ry = y & (ty - 1), rz = z & (tz - 1);
+  const int my = ry >= ty - h ? 2 : 1, mz = rz >= tz - h ? 2 : 1;
+#pragma unroll
+  for (int k = 0; k < COUNT; ++k) v[k] = make_double2(0.0, 0.0);
+  for (int iz = 0; iz < mz; ++iz) {
+    const int qz = ((z >> t.lg[2]) + iz) & (t.nt[2] - 1), lz = rz + h - iz * tz;
+    for (int iy = 0; iy < my; ++iy) {
+      const int qy = ((y >> t.lg[1]) + iy) & (t.nt[1] - 1), ly = ry + h - iy * ty;
+      const double *rows = t.boxes + (int64_t)(qz * t.nt[1] + qy) * t.nt[0] * t.box +
+                           (lz * t.e[1] + ly) * t.e[0];
+      // every load before the first sum, so that all are in flight together
+      double own[COUNT][2], next[COUNT][2];
+#pragma unroll
+      for (int k = 0; k < COUNT; ++k) {
+        const int x = 2 * (n2 + STRIDE * k);
+        const double *p = rows + (x >> t.lg[0]) * t.box + (x & (tx - 1)) + h;
+        own[k][0] = p[0];
+        own[k][1] = p[1];
+      }
+#pragma unroll
+      for (int k = 0; k < COUNT; ++k) {
+        const int x = 2 * (n2 + STRIDE * k), rx = x & (tx - 1), qx = (x >> t.lg[0]) + 1;
+        next[k][0] = next[k][1] = 0.0;
+        if (rx + 1 >= tx - h) {  // x + 1, and x too except at the first such pair
+          const double *p = rows + (qx & (t.nt[0] - 1)) * t.box + rx + h - tx;
+          next[k][0] = p[rx >= tx - h ? 0 : 1];
+          next[k][1] = p[1];
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < COUNT; ++k) {
+        const int rx = (2 * (n2 + STRIDE * k)) & (tx - 1);
+        v[k].x += own[k][0] + (rx >= tx - h ? next[k][0] : 0.0);
+        v[k].y += own[k][1] + next[k][1];
+      }
+    }
+  }
+}
+
+// Charge spreading without tiles (order 8, the smaller workspace), one wavefront of 64
+// consecutive particles per block.  The wavefront first adds its n^3 weights per
+// particle into a private box of grid points in LDS (LDS atomics), then adds every
+// non-zero point of that box to the grid with one global FP64 atomic: ~4x fewer
+// global atomics than adding each weight directly, which is what bounds this kernel.
+// Per axis the box is taken in whichever of two cyclic frames (indices as they are, or
+// shifted by K/2) gives the smaller extent, so groups that straddle a periodic face
+// stay compact.  A group whose box exceeds the LDS capacity adds its weights straight
+// to the grid.
 constexpr int kSpreadCap = 2048;  // grid points (doubles) in the LDS box
 
 __device__ __forceinline__ int wave_min_i(int v) { return -wave_max(-v); }
@@ -342,7 +586,7 @@ __global__ __launch_bounds__(kWave) void k_spread(RecArgs a) {
 #pragma unroll
   for (int d = 0; d < 3; ++d) {
     const int K = a.K[d];
-    const int s0 = b[d], s1 = (b[d] + K / 2) % K;
+    const int s0 = b[d], s1 = wrapi(b[d] + K / 2, K);
     const int mn0 = wave_min_i(live ? s0 : 1 << 30), mx0 = wave_max(live ? s0 : -(1 << 30));
     const int mn1 = wave_min_i(live ? s1 : 1 << 30), mx1 = wave_max(live ? s1 : -(1 << 30));
     const bool shift = mx1 - mn1 < mx0 - mn0;
@@ -592,9 +836,11 @@ __global__ __launch_bounds__(Fft<NP>::T) void k_fft_y(double2 *g, int W, int P, 
 // transform of length NH = NP/2: X_m = E_m + e^{-2 pi i m/NP} O_m, where
 // E_m = (Z_m + conj Z_{NH-m}) / 2 and O_m = (Z_m - conj Z_{NH-m}) / (2i) are the
 // transforms of the even and odd samples (indices of Z mod NH).  rows is a multiple
-// of the M rows of a block (K1 K2 >= 64).
-template <int NP>
-__global__ __launch_bounds__(Fft<NP / 2>::T) void k_fft_x_r2c(const double *rg, double2 *h) {
+// of the M rows of a block (K1 K2 >= 64).  BOXES: the rows are read from the tiles'
+// boxes instead of the grid (lgK1 = log2 K1).
+template <int NP, bool BOXES>
+__global__ __launch_bounds__(Fft<NP / 2>::T) void k_fft_x_r2c(const double *rg, TileK tk, int lgK1,
+                                                             double2 *h) {
   constexpr int NH = NP / 2;
   using F = Fft<NH>;
   constexpr int P = NP >= 64 ? (NP / 2 + 8) / 8 * 8 : NP / 2 + 1;
@@ -604,10 +850,15 @@ __global__ __launch_bounds__(Fft<NP / 2>::T) void k_fft_x_r2c(const double *rg, 
   double2 *z = buf;  // Z rows, once the transform has read the exchanged points
   const int t = threadIdx.x, n2 = t % F::R2, m = t / F::R2;
   const int64_t r0 = (int64_t)blockIdx.x * F::M;
-  const double2 *row = (const double2 *)(rg + (r0 + m) * NP);
   double2 v[F::R1], out[F::R1];
+  if constexpr (BOXES) {
+    const int r = (int)r0 + m;
+    row_from_boxes<F::R1, F::R2>(tk, r & ((1 << lgK1) - 1), r >> lgK1, n2, v);
+  } else {
+    const double2 *row = (const double2 *)(rg + (r0 + m) * NP);
 #pragma unroll
-  for (int k = 0; k < F::R1; ++k) v[k] = row[n2 + F::R2 * k];
+    for (int k = 0; k < F::R1; ++k) v[k] = row[n2 + F::R2 * k];
+  }
   fill_twiddles<NP, F::T>(tw);
   __syncthreads();
   F::template forward<-1, 2>(v, out, buf, tw, m, n2, m, n2);
@@ -854,44 +1105,124 @@ int fft_z_influence(const RecArgs &a, hipStream_t st) {
   }
 }
 
+int log2_of(int k) { return __builtin_ctz((unsigned)k); }
+
+// tk: read the charge rows from the tiles' boxes (forward pass), or null.
 template <int NP>
-void x_pass(double *g, double2 *h, const int32_t K[3], bool forward, hipStream_t st) {
+void x_pass(const RecArgs &a, bool forward, const TileK *tk, hipStream_t st) {
   using F = Fft<NP / 2>;
-  const unsigned nb = (unsigned)(K[1] * K[2] / F::M);  // K1 K2 >= 64, M a power of two <= 64
-  if (forward)
-    k_fft_x_r2c<NP><<<nb, F::T, 0, st>>>(g, h);
+  // K1 K2 >= 64, M a power of two <= 64
+  const unsigned nb = (unsigned)((int64_t)a.K[1] * a.K[2] / F::M);
+  if (!forward)
+    k_fft_x_c2r<NP><<<nb, F::T, 0, st>>>(a.half, a.grid);
+  else if (tk)
+    k_fft_x_r2c<NP, true><<<nb, F::T, 0, st>>>(a.grid, *tk, log2_of(a.K[1]), a.half);
   else
-    k_fft_x_c2r<NP><<<nb, F::T, 0, st>>>(h, g);
+    k_fft_x_r2c<NP, false><<<nb, F::T, 0, st>>>(a.grid, TileK{}, 0, a.half);
 }
 
-void fft_x(double *g, double2 *h, const int32_t K[3], bool forward, hipStream_t st) {
-  switch (K[0]) {
-    case 8: x_pass<8>(g, h, K, forward, st); break;
-    case 16: x_pass<16>(g, h, K, forward, st); break;
-    case 32: x_pass<32>(g, h, K, forward, st); break;
-    case 64: x_pass<64>(g, h, K, forward, st); break;
-    case 128: x_pass<128>(g, h, K, forward, st); break;
-    default: x_pass<256>(g, h, K, forward, st); break;
+void fft_x(const RecArgs &a, bool forward, const TileK *tk, hipStream_t st) {
+  switch (a.K[0]) {
+    case 8: x_pass<8>(a, forward, tk, st); break;
+    case 16: x_pass<16>(a, forward, tk, st); break;
+    case 32: x_pass<32>(a, forward, tk, st); break;
+    case 64: x_pass<64>(a, forward, tk, st); break;
+    case 128: x_pass<128>(a, forward, tk, st); break;
+    default: x_pass<256>(a, forward, tk, st); break;
   }
 }
 
 int64_t grid_points(const int32_t K[3]) { return (int64_t)K[0] * K[1] * K[2]; }
 unsigned blocks_of(int64_t n, int per) { return (unsigned)((n + per - 1) / per > 0 ? (n + per - 1) / per : 1); }
 
+// Large tiles (16 x 16 x 8) where the grid has at least 512 of them -- two per compute
+// unit --, else 8 x 8 x 8; their boxes hold 1.94 and 2.60 points per grid point at
+// order 4.  Order 6 takes the large ones only (2.80; small ones 4.29), order 8 none
+// (3.87, 6.59): there, and in the smaller of the two workspaces that the call accepts,
+// charge is spread by wavefront boxes and atomics.
+constexpr double kBoxPoints = 2.8;  // largest box points per grid point of a shape taken
+
+bool large_tiles(const int32_t K[3]) {
+  return K[0] >= 16 && K[1] >= 16 && (int64_t)K[0] * K[1] * K[2] >= 512 * 2048;
+}
+bool tiled(int order, const int32_t K[3]) { return order == 4 || (order == 6 && large_tiles(K)); }
+
+size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
+
+// Bytes of the tiles' part of the workspace, at most.
+size_t tile_workspace(int64_t n, int64_t npts) {
+  const size_t ints = align256((size_t)(npts / 512 + 2) * sizeof(int32_t));
+  const size_t per = align256((size_t)(n > 0 ? n : 0) * sizeof(int32_t));
+  return 256 + 2 * ints + 3 * per + (size_t)(kBoxPoints * (double)npts) * sizeof(double);
+}
+
+TileK make_tiles(int order, const int32_t K[3], int64_t n, char *p) {
+  TileK t{};
+  const bool large = large_tiles(K);
+  t.ntiles = t.box = 1;
+  for (int d = 0; d < 3; ++d) {
+    t.lg[d] = large && d < 2 ? 4 : 3;
+    t.nt[d] = K[d] >> t.lg[d];
+    t.e[d] = (1 << t.lg[d]) + order - 1;
+    t.ntiles *= t.nt[d];
+    t.box *= t.e[d];
+  }
+  p = (char *)align256((size_t)p);
+  const size_t ints = align256((size_t)(t.ntiles + 2) * sizeof(int32_t));
+  const size_t per = align256((size_t)n * sizeof(int32_t));
+  t.count = (int32_t *)p, p += ints;
+  t.start = (int32_t *)p, p += ints;
+  t.key = (int32_t *)p, p += per;
+  t.rank = (int32_t *)p, p += per;
+  t.order = (int32_t *)p, p += per;
+  t.boxes = (double *)p;
+  return t;
+}
+
 template <int N>
-void launch_rec_order(const RecArgs &a, double *self_partial, hipStream_t st) {
+void spread_tiles(const RecArgs &a, const TileK &t, bool large, hipStream_t st) {
+  if (large)
+    k_spread_tile<N, 16, 16, 8, kTileTeam><<<t.ntiles, kTileThreads, 0, st>>>(a, t);
+  else if constexpr (N == 4)
+    k_spread_tile<N, 8, 8, 8, kTileTeam><<<t.ntiles, kTileThreads, 0, st>>>(a, t);
+}
+
+template <int N>
+void gather_tiles(const RecArgs &a, const TileK &t, bool large, hipStream_t st) {
+  if (large)
+    k_gather_tile<N, 16, 16, 8, kTileTeam><<<t.ntiles, kTileThreads, 0, st>>>(a, t);
+  else if constexpr (N == 4)
+    k_gather_tile<N, 8, 8, 8, kTileTeam><<<t.ntiles, kTileThreads, 0, st>>>(a, t);
+}
+
+// tk: the tiles, or null for spreading by atomics.
+template <int N>
+void launch_rec_order(const RecArgs &a, const TileK *tk, double *self_partial, hipStream_t st) {
   const int64_t npts = grid_points(a.K);
-  k_bmod<N><<<blocks_of(3 * kMaxGrid, kThreads), kThreads, 0, st>>>(a);
-  k_zero_grid<<<blocks_of(npts, kThreads), kThreads, 0, st>>>(a.grid, npts);
-  if (a.n > 0) k_spread<N><<<blocks_of(a.n, kWave), kWave, 0, st>>>(a);
-  fft_x(a.grid, a.half, a.K, true, st);
+  // one launch for the tables and the zeros: tile counts (in pairs), or the grid
+  double *zero = tk ? (double *)tk->count : a.grid;
+  const int64_t nzero = tk ? (tk->ntiles + 1) / 2 : npts;
+  k_bmod<N><<<kBmodBlocks + blocks_of(nzero, kThreads), kThreads, 0, st>>>(a, zero, nzero);
+  const bool large = large_tiles(a.K);
+  if (tk) {
+    k_tile_count<<<blocks_of(a.n, kGatherAtoms), kGatherAtoms, 0, st>>>(a, *tk, self_partial);
+    launch_scan(tk->ntiles, tk->count, tk->start, st);
+    k_tile_scatter<<<blocks_of(a.n, kThreads), kThreads, 0, st>>>(a.n, *tk);
+    if constexpr (N <= 6) spread_tiles<N>(a, *tk, large, st);
+  } else if (a.n > 0) {
+    k_spread<N><<<blocks_of(a.n, kWave), kWave, 0, st>>>(a);
+  }
+  fft_x(a, true, tk, st);
   fft_y(a, true, 0, st);
   const int nparts = fft_z_influence(a, st);
   fft_y(a, false, nparts, st);
-  fft_x(a.grid, a.half, a.K, false, st);
-  if (a.n > 0)
+  fft_x(a, false, nullptr, st);
+  if (tk) {
+    if constexpr (N <= 6) gather_tiles<N>(a, *tk, large, st);
+  } else if (a.n > 0) {
     k_gather<N, kGatherTeam>
         <<<blocks_of(a.n, kGatherAtoms), kGatherAtoms * kGatherTeam, 0, st>>>(a, self_partial);
+  }
 }
 
 }  // namespace
@@ -903,11 +1234,16 @@ size_t ewald_real_workspace(int64_t n) {
 
 // real grid, half grid (at most npts/2 + npts/8 complex points: K0 >= 8), tables,
 // partials (one for the reciprocal energy, one per gather block)
-size_t spme_workspace(int64_t n, int64_t npts) {
+// -- enough for every call, spreading by atomics; spme_workspace adds the tiles' part.
+size_t spme_min_workspace(int64_t n, int64_t npts) {
   const int64_t half = npts / 2 + npts / 8;
   return (size_t)npts * sizeof(double) + (size_t)half * sizeof(double2) +
          3 * kMaxGrid * sizeof(double) +
          ((size_t)blocks_of(half, 512) + blocks_of(n, kGatherAtoms)) * sizeof(double) + 256;
+}
+
+size_t spme_workspace(int64_t n, int64_t npts) {
+  return spme_min_workspace(n, npts) + tile_workspace(n, npts);
 }
 
 int launch_ewald_real(const BoxK &b, double alpha, double rc, int64_t n, const double *x,
@@ -953,7 +1289,7 @@ int launch_ewald_real(const BoxK &b, double alpha, double rc, int64_t n, const d
 
 int launch_spme_recip(const BoxK &b, double alpha, int32_t order, const int32_t K[3], int64_t n,
                       const double *x, const double *q, double *F, double *e_total,
-                      int accumulate, void *ws, hipStream_t st) {
+                      int accumulate, void *ws, size_t ws_bytes, hipStream_t st) {
   RecArgs a{};
   a.b = b;
   for (int d = 0; d < 3; ++d) {
@@ -977,10 +1313,16 @@ int launch_spme_recip(const BoxK &b, double alpha, int32_t order, const int32_t 
   a.partial = (double *)p;
   const unsigned ngat = blocks_of(n, kGatherAtoms);
   double *self_partial = n > 0 ? a.partial + 1 : nullptr;
+  TileK tiles{};
+  const TileK *tk = nullptr;
+  if (n > 0 && tiled(order, K) && ws_bytes >= spme_workspace(n, npts)) {
+    tiles = make_tiles(order, K, n, (char *)ws + spme_min_workspace(n, npts));
+    tk = &tiles;
+  }
   switch (order) {
-    case 4: launch_rec_order<4>(a, self_partial, st); break;
-    case 6: launch_rec_order<6>(a, self_partial, st); break;
-    default: launch_rec_order<8>(a, self_partial, st); break;
+    case 4: launch_rec_order<4>(a, tk, self_partial, st); break;
+    case 6: launch_rec_order<6>(a, tk, self_partial, st); break;
+    default: launch_rec_order<8>(a, tk, self_partial, st); break;
   }
   if (e_total)
     k_colsum<1024><<<1, 1024, 0, st>>>((int64_t)1 + (n > 0 ? ngat : 0), 1, 1, a.partial, e_total,

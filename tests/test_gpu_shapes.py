@@ -117,3 +117,72 @@ def test_spme_grid_shapes_vs_oracle(dev, orc, K):
     E_o += orc.ewald_self(q, li.EWALD_ALPHA)
     assert np.abs(F.cpu().numpy() - F_o).max() <= 1e-11 * np.abs(F_o).max()
     assert E.item() == pytest.approx(E_o, rel=1e-11)
+
+
+def _spme_min_bytes(n, npts):
+    half = npts // 2 + npts // 8
+    return npts * 8 + half * 16 + 3 * 256 * 8 + 8 * (-(-half // 512) + max(1, -(-n // 256))) + 256
+
+
+@pytest.mark.parametrize("order,K,n", [(4, (8, 8, 8), 1), (4, (8, 16, 8), 300),
+                                       (4, (64, 32, 64), 5000), (4, (128, 128, 64), 9000),
+                                       (6, (128, 64, 128), 3000), (6, (16, 32, 8), 500),
+                                       (8, (128, 64, 128), 2000)])
+def test_spme_tiles_against_direct_spreading(dev, order, K, n):
+    """Reciprocal forces and energy with the tiles' workspace (both tile shapes, empty and
+    crowded tiles, tiles that are their own neighbour, particles on cell corners, outside
+    the box and in any order) and with the smaller one (no tiles): rounding only, a few
+    hundred additions per point: 1e-13 of the largest force, 1e-12 of the energy."""
+    import torch
+    from paper_2109_09056_amd import _lib, ops
+    L = np.array([17.0, 16.0, 18.0])
+    g = np.random.default_rng(n)
+    x = g.uniform(0, 1, (n, 3)) * L
+    x[: n // 3] = L * 0.4 + g.uniform(0, 1, (n // 3, 3))  # a clump
+    x[n // 3: n // 3 + 20] = np.floor(x[n // 3: n // 3 + 20] / L * K) * (L / K)  # on grid points
+    x[-1] = L * np.array([1.02, -0.03, 0.5])
+    q = g.uniform(-1.0, 1.0, n)
+    T = lambda a: torch.as_tensor(a, dtype=torch.float64, device=dev).contiguous()
+    xt, qt = T(x), T(q)
+    npts = K[0] * K[1] * K[2]
+    full, small = ops.workspace_bytes(ops.OP_SPME, n, ncells=npts), _spme_min_bytes(n, npts)
+    assert small < full
+    lib, out = _lib.load(), []
+    import ctypes
+    Kc = (ctypes.c_int32 * 3)(*K)
+    for nbytes in (full, small, small - 8):
+        ws = torch.full((nbytes,), 255, dtype=torch.uint8, device=dev)  # NaN everywhere
+        F = torch.empty_like(xt)
+        e = torch.empty(1, dtype=torch.float64, device=dev)
+        rc = lib.ljmd_spme_recip(_lib.make_box(L), li.EWALD_ALPHA, order, Kc, n, xt.data_ptr(),
+                                 qt.data_ptr(), F.data_ptr(), e.data_ptr(), 0, ws.data_ptr(),
+                                 nbytes, torch.cuda.current_stream(dev).cuda_stream)
+        if nbytes < small:
+            assert rc == _lib.EWORKSPACE
+            continue
+        _lib.check(rc, "spme")
+        out.append((F.cpu().numpy(), e.item()))
+    (Fa, ea), (Fb, eb) = out
+    assert np.isfinite(Fa).all()
+    # the forces of a few particles are differences of terms about |q| alpha^2 large
+    scale = max(np.abs(Fb).max(), li.EWALD_ALPHA ** 2)
+    assert np.abs(Fa - Fb).max() <= 1e-13 * scale * max(1.0, n / 100.0)
+    assert ea == pytest.approx(eb, rel=1e-12)
+
+
+@pytest.mark.parametrize("n", [1, 63, 65, 1000])
+def test_bin_counts_any_order(dev, orc, n):
+    """Cell sort of atoms in random order (every lane of a wavefront its own cell) and of
+    atoms all in one cell."""
+    import torch
+    from paper_2109_09056_amd import ops
+    L = np.array([20.0, 23.0, 26.0])
+    for x in (li.random_gas(n, L, n), np.tile(L * 0.3, (n, 1))):
+        xs, _, _, ids, cs = ops.bin(L, 2.8, torch.as_tensor(x, device=dev))
+        nc = ops.grid(L, 2.8)
+        c = np.minimum(np.floor(x / (L / nc)).astype(int), np.array(nc) - 1)
+        cell = (c[:, 2] * nc[1] + c[:, 1]) * nc[0] + c[:, 0]
+        want = np.lexsort((np.arange(n), cell))
+        assert np.array_equal(ids.cpu().numpy(), want)
+        assert np.array_equal(xs.cpu().numpy(), x[want])
+        assert np.array_equal(cs.cpu().numpy()[:-1], np.searchsorted(cell[want], np.arange(np.prod(nc))))
