@@ -17,9 +17,9 @@
 //                F_i = -q_i sum_k grad_i[prod_a M_n(u_ai - k_a)] phi(k)
 //   self:        E_self = -alpha/sqrt(pi) sum_i q_i^2
 //
-// Kernels: the real-space pair loop walks the tiled full list with two lanes
-// per particle over packed (x, y, z, q) records (the SPH and LJ traversal),
-// with erfc taken as e^{-x^2} times a tabulated polynomial for erfcx;
+// Kernels: the real-space pair loop walks the tiled full list with four lanes
+// per particle over packed (x, y, z, q) records (the LJ traversal), the force's
+// kernel erfc(x) + 2/sqrt(pi) x e^{-x^2} taken from a table of polynomials;
 // charge is spread into boxes of grid tiles in LDS, which the x pass adds up as it
 // reads its rows (or onto the grid by FP64 atomics); the 3-D transform is real-to-complex: the x pass turns each row of
 // K0 reals into K0/2 + 1 coefficients through one complex FFT of length K0/2
@@ -46,16 +46,24 @@ constexpr int kThreads = 256;
 constexpr int kGatherAtoms = 256;  // particles per gather block
 constexpr int kGatherTeam = 2;     // lanes per particle
 constexpr int kEwAtoms = 128;  // real space: particles per block
-constexpr int kEwTeam = 2;
+constexpr int kEwTeam = 4;      // lanes per particle
 constexpr int kEwThreads = kEwAtoms * kEwTeam;
-constexpr int kEwUnroll = 6;
-// erfc(x) = e^{-x^2} erfcx(x) on [0, alpha rc]: erfcx by degree-10 Taylor polynomials
-// about the centres of 32 equal intervals (relative error ~1e-15); e^{-x^2} is
-// needed for the force anyway, so a pair costs ten FMAs instead of a library erfc.
-constexpr int kErfcIntervals = 32;
-constexpr int kErfcDegree = 10;
-constexpr int kErfcStride = 12;  // coefficients per interval, padded
-constexpr int kErfcTable = kErfcIntervals * kErfcStride;
+// Slots per group and lane: 2 without energies (63 VGPRs, 8 wavefronts per SIMD), 3
+// with (the second table's LDS limits residency first).  500,000 / 32,000 particles,
+// no energies (us): two lanes with 6 slots 107.6 / 15.8, with 4 and at most 80 VGPRs
+// 104.1 / 16.2; four lanes with 3 slots 118.2 / 13.2, with 2 100.0 / 14.3, with 1 104.6 /
+// 16.4; with energies and four lanes 3 slots 134, 2 slots 144.
+template <bool EV>
+constexpr int ew_unroll() { return EV ? 3 : 2; }
+// erfc and the force's kernel G on [0, alpha rc] by Taylor polynomials about the centres
+// of 128 equal intervals, in units of the interval's width: no exponential per pair.
+// 500,000 particles: 136.5 us with erfcx polynomials of degree 10 times exp, two lanes
+// per particle, now 102; the rest is gathers (of two 16-byte reads per entry) -- with
+// 5 or 2 coefficients instead of 9 it takes 5 % less.
+constexpr int kErfcIntervals = 128;
+constexpr int kErfcCoefs = 9;   // degree 8: G to 6e-16 absolute for alpha rc up to 6
+constexpr int kErfcStride = 10;  // doubles per interval in LDS: 16 of 80-byte rows share no bank
+constexpr int kErfcSeeds = 384;  // doubles of the workspace for G(c) and e^{-c^2} per interval
 
 // ------------------------------------------------------------ real space --
 
@@ -71,36 +79,62 @@ struct RealArgs {
   double *F;
   int accumulate;
   double *partial;  // per-block E_dir, or null
-  const double *erfcx_tab;  // [kErfcIntervals][kErfcStride] Taylor coefficients
-  double inv_dx, half_dx;   // intervals of width dx = alpha rc / kErfcIntervals
+  const double *seeds;  // [kErfcIntervals] G(c), then e^{-c^2}
+  double dx, u_scale;   // interval width in alpha r; intervals per unit length
 };
 
-// Packs (x, y, z, q) records; block 0 also writes the erfcx table: about each
-// interval centre c, a_n = erfcx^(n)(c) / n! from erfcx(c) = e^{c^2} erfc(c) and
-// the recurrence y' = 2 x y - 2/sqrt(pi), y^(n+1) = 2 x y^(n) + 2 n y^(n-1).
+// Packs (x, y, z, q) records; block 0 also writes the tables' seeds, G(c) and e^{-c^2}
+// at every interval's centre c, with
+//   G(x) = erfc(x) + 2/sqrt(pi) x e^{-x^2}   (the force is q_i q_j G(alpha r) / r^3 d).
 __global__ __launch_bounds__(kThreads) void k_pack_xq(int32_t n, const double *x, const double *q,
-                                                      double4 *xq, double half_dx,
-                                                      double *erfcx_tab) {
+                                                      double4 *xq, double alpha, double u_scale,
+                                                      double *seeds) {
   if (blockIdx.x == 0 && threadIdx.x < kErfcIntervals) {
-    const double c = (2 * threadIdx.x + 1) * half_dx;
-    double *a = erfcx_tab + threadIdx.x * kErfcStride;
-    double ym1 = exp(c * c) * erfc(c);
-    double y = 2.0 * c * ym1 - 2.0 / sqrt(kPi);
-    double fact = 1.0;
-    a[0] = ym1;
-    a[1] = y;
-    for (int k = 1; k < kErfcDegree; ++k) {
-      const double yn = 2.0 * c * y + 2.0 * k * ym1;
-      fact *= (k + 1);
-      a[k + 1] = yn / fact;
-      ym1 = y;
-      y = yn;
-    }
-    for (int k = kErfcDegree + 1; k < kErfcStride; ++k) a[k] = 0.0;
+    // c = alpha (k + 1/2) / u_scale with what its rounding leaves, lo, and c^2 likewise:
+    // G changes by 2 c^2 times a relative change of c
+    const double k = threadIdx.x + 0.5, h = k / u_scale;
+    const double c = alpha * h;
+    const double lo = __builtin_fma(alpha, h, -c) + alpha * (__builtin_fma(-h, u_scale, k) / u_scale);
+    const double cc = c * c;
+    const double e0 = exp(-cc), e = __builtin_fma(-e0, __builtin_fma(c, c, -cc), e0);
+    constexpr double two = 1.1283791670955126, two_lo = 1.533545961316588e-17;  // 2/sqrt(pi)
+    const double ce = c * e;
+    seeds[threadIdx.x] =
+        __builtin_fma(two, ce, erfc(c)) + (two_lo * ce - 2.0 * two * cc * e * lo);
+    seeds[kErfcIntervals + threadIdx.x] = __builtin_fma(-2.0 * c * lo, e, e);
   }
   const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (i >= n) return;
   xq[i] = make_double4(x[3 * i], x[3 * i + 1], x[3 * i + 2], q[i]);
+}
+
+// The block's tables in LDS from the seeds.  With e_n the Taylor coefficients of
+// e^{-x^2} about c, e_{n+1} = -2 (c e_n + e_{n-1}) / (n+1):
+//   G:    G(c), then -4/sqrt(pi) (c^2 e_{n-1} + 2 c e_{n-2} + e_{n-3}) / n  (G' = -4/sqrt(pi) x^2 e^{-x^2})
+//   erfc: G(c) - 2/sqrt(pi) c e^{-c^2}, then -2/sqrt(pi) e_{n-1} / n         (energies only)
+// each times dx^n.
+template <bool EV>
+__device__ __forceinline__ void erfc_tables(const RealArgs &a, double *tab) {
+  const int k0 = threadIdx.x;
+  if (k0 >= kErfcIntervals) return;
+  constexpr double two = 1.1283791670955126;  // 2 / sqrt(pi)
+  const double c = (k0 + 0.5) * a.dx;
+  double *g = tab + k0 * kErfcStride, *p = g + kErfcIntervals * kErfcStride;
+  double e0 = a.seeds[kErfcIntervals + k0], e1 = 0.0, e2 = 0.0;  // e_{n-1}, e_{n-2}, e_{n-3}
+  g[0] = a.seeds[k0];
+  if constexpr (EV) p[0] = g[0] - two * c * e0;
+  double pw = -two;
+#pragma unroll
+  for (int k = 1; k < kErfcCoefs; ++k) {
+    pw *= a.dx;
+    const double f = pw * (1.0 / k);
+    if constexpr (EV) p[k] = f * e0;
+    g[k] = 2.0 * f * ((c * c) * e0 + 2.0 * c * e1 + e2);
+    const double en = (-2.0 / k) * (c * e0 + e1);
+    e2 = e1;
+    e1 = e0;
+    e0 = en;
+  }
 }
 
 template <bool WIDE>
@@ -111,8 +145,15 @@ __device__ __forceinline__ const double4 *xq_of(const double4 *p, int32_t j) {
     return (const double4 *)((const char *)p + ((uint32_t)j << 5));
 }
 
-// One pair: adds q_j-weighted force scalar times d and the energy kernel.
-template <bool WRAP>
+__device__ __forceinline__ double horner(const double *cf, double t) {
+  double p = cf[kErfcCoefs - 1];
+#pragma unroll
+  for (int k = kErfcCoefs - 2; k >= 0; --k) p = __builtin_fma(p, t, cf[k]);
+  return p;
+}
+
+// One pair: adds q_j-weighted force scalar times d and (EV) the energy kernel.
+template <bool WRAP, bool EV>
 __device__ __forceinline__ void real_pair(const RealArgs &a, const double *tab, const double4 &me,
                                           const double4 &o, bool ok, double &fx, double &fy,
                                           double &fz, double &e) {
@@ -124,71 +165,54 @@ __device__ __forceinline__ void real_pair(const RealArgs &a, const double *tab, 
   }
   const double r2 = dist2(dx, dy, dz);
   const bool in = ok && r2 < a.rc2;
-  const double rr2 = in ? r2 : 1.0;  // keeps padding and far pairs finite
+  // r^2 with fewer roundings than the cutoff's: a relative error of it enters the
+  // force (alpha r)^2 times over; 1 keeps padding and far pairs finite
+  const double rr2 = in ? __builtin_fma(dz, dz, __builtin_fma(dy, dy, dx * dx)) : 1.0;
   // 1/r from one refined reciprocal square root of r^2 and r = r^2 / r: about
   // 9 % faster at 500k atoms than a square root followed by a reciprocal
   const double ir = rsqrt64(rr2);
-  const double r = rr2 * ir;
-  const double xa = a.alpha * r;
-  int it = (int)(xa * a.inv_dx);
+  double r = rr2 * ir;
+  // energies add up without the forces' cancellation of common errors: r to half a unit
+  if constexpr (EV) r = __builtin_fma(0.5 * ir, __builtin_fma(-r, r, rr2), r);
+  const double u = a.u_scale * r;
+  int it = (int)u;
   it = it < kErfcIntervals - 1 ? it : kErfcIntervals - 1;
-  const double t = xa - (2 * it + 1) * a.half_dx;
+  const double t = __builtin_fma(a.u_scale, r, -((double)it + 0.5));
   const double *cf = tab + it * kErfcStride;
-  double p = cf[kErfcDegree];
-#pragma unroll
-  for (int k = kErfcDegree - 1; k >= 0; --k) p = __builtin_fma(p, t, cf[k]);
-  const double ex = exp(-a.a2 * rr2);
-  const double er = ex * p * ir;  // erfc(alpha r) / r
-  const double s = (er + a.c2a * ex) * (ir * ir);
-  const double qs = in ? o.w * s : 0.0;
+  const double qi = in ? o.w * ir : 0.0;
+  const double qs = qi * (ir * ir) * horner(cf, t);
   fx = __builtin_fma(qs, dx, fx);
   fy = __builtin_fma(qs, dy, fy);
   fz = __builtin_fma(qs, dz, fz);
-  e += in ? o.w * er : 0.0;
+  if constexpr (EV) e = __builtin_fma(qi, horner(cf + kErfcIntervals * kErfcStride, t), e);
 }
 
-template <bool WRAP, bool WIDE>
+// Lane t's entries of the row, in masked groups of U (slots beyond cnt repeat the
+// lane's first entry).
+template <bool WRAP, bool WIDE, bool EV>
 __device__ __forceinline__ void real_row(const RealArgs &a, const double *tab, const int32_t *row,
                                          int32_t cnt, const double4 &me, double &fx, double &fy,
                                          double &fz, double &e) {
-  constexpr int U = kEwUnroll;
+  constexpr int U = ew_unroll<EV>();
   constexpr int kStep = kEwTeam * kWave;
-  const int32_t whole = cnt - cnt % U;
-  int32_t k = 0;
-  for (; k < whole; k += U, row += U * kStep) {
+#pragma unroll 1
+  for (int32_t k = 0; k < cnt; k += U, row += U * kStep) {
     int32_t j[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) j[u] = row[u * kStep];
+    for (int u = 0; u < U; ++u) j[u] = row[(k + u < cnt ? u : 0) * kStep];
     double4 o[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) o[u] = *xq_of<WIDE>(a.xq, j[u]);
 #pragma unroll
-    for (int u = 0; u < U; ++u) real_pair<WRAP>(a, tab, me, o[u], true, fx, fy, fz, e);
-  }
-  if (k < cnt) {
-    int32_t j[U];
-    bool ok[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      ok[u] = k + u < cnt;
-      j[u] = row[(ok[u] ? u : 0) * kStep];
-    }
-    double4 o[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      o[u] = me;
-      if (ok[u]) o[u] = *xq_of<WIDE>(a.xq, j[u]);
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) real_pair<WRAP>(a, tab, me, o[u], ok[u], fx, fy, fz, e);
+    for (int u = 0; u < U; ++u) real_pair<WRAP, EV>(a, tab, me, o[u], k + u < cnt, fx, fy, fz, e);
   }
 }
 
 template <bool WIDE, bool EV>
 __global__ __launch_bounds__(kEwThreads) void k_ewald_real(RealArgs a) {
   __shared__ double red[kRedRows * kEwThreads / kWave];
-  __shared__ double tab[kErfcTable];
-  for (int k = threadIdx.x; k < kErfcTable; k += kEwThreads) tab[k] = a.erfcx_tab[k];
+  __shared__ __align__(16) double tab[(EV ? 2 : 1) * kErfcIntervals * kErfcStride];
+  erfc_tables<EV>(a, tab);
   __syncthreads();
   const int t = (int)threadIdx.x % kEwTeam;
   const int32_t i = xcd_block(blockIdx.x, gridDim.x) * kEwAtoms + (int)threadIdx.x / kEwTeam;
@@ -206,25 +230,17 @@ __global__ __launch_bounds__(kEwThreads) void k_ewald_real(RealArgs a) {
     const int32_t *row =
         a.nbr + (int64_t)(i >> 6) * a.maxn * kWave + (i & (kWave - 1)) + (int64_t)t * kWave;
     if (interior)
-      real_row<false, WIDE>(a, tab, row, cnt, me, fx, fy, fz, e);
+      real_row<false, WIDE, EV>(a, tab, row, cnt, me, fx, fy, fz, e);
     else
-      real_row<true, WIDE>(a, tab, row, cnt, me, fx, fy, fz, e);
+      real_row<true, WIDE, EV>(a, tab, row, cnt, me, fx, fy, fz, e);
   }
   fx = team_sum<kEwTeam>(fx);
   fy = team_sum<kEwTeam>(fy);
   fz = team_sum<kEwTeam>(fz);
-  if (live && t == 0) {
-    double *F = a.F + 3 * (int64_t)i;
-    const double q = me.w;
-    if (a.accumulate) {
-      F[0] += q * fx;
-      F[1] += q * fy;
-      F[2] += q * fz;
-    } else {
-      F[0] = q * fx;
-      F[1] = q * fy;
-      F[2] = q * fz;
-    }
+  if (live && t < 3) {  // lane t of the team writes component t
+    double *F = a.F + 3 * (int64_t)i + t;
+    const double f = me.w * (t == 0 ? fx : (t == 1 ? fy : fz));
+    *F = a.accumulate ? *F + f : f;
   }
   if constexpr (EV) {
     double v[1] = {live ? 0.5 * me.w * e : 0.0};  // per lane: the team's lanes add up
@@ -1229,7 +1245,7 @@ void launch_rec_order(const RecArgs &a, const TileK *tk, double *self_partial, h
 
 size_t ewald_real_workspace(int64_t n) {
   return (size_t)(n > 0 ? n : 0) * sizeof(double4) +
-         (size_t)blocks_of(n, kEwAtoms) * sizeof(double) + kErfcTable * sizeof(double) + 256;
+         (size_t)blocks_of(n, kEwAtoms) * sizeof(double) + kErfcSeeds * sizeof(double) + 256;
 }
 
 // real grid, half grid (at most npts/2 + npts/8 complex points: K0 >= 8), tables,
@@ -1265,14 +1281,17 @@ int launch_ewald_real(const BoxK &b, double alpha, double rc, int64_t n, const d
   a.accumulate = accumulate;
   const unsigned nblk = blocks_of(n, kEwAtoms);
   a.partial = (double *)((char *)ws + (size_t)(n > 0 ? n : 0) * sizeof(double4));
-  double *tab = a.partial + nblk;
-  a.erfcx_tab = tab;
-  const double dx = alpha * rc / kErfcIntervals;
-  a.inv_dx = 1.0 / dx;
-  a.half_dx = 0.5 * dx;
+  double *seeds = a.partial + nblk;
+  a.seeds = seeds;
+  // intervals per unit length, cut to 24 bits: r in interval widths then carries no
+  // error common to all pairs (G's relative sensitivity to it is ~2 (alpha r)^2)
+  float per = (float)(kErfcIntervals / rc);
+  if ((double)per * rc > kErfcIntervals) per = nextafterf(per, 0.0f);
+  a.u_scale = per;
+  a.dx = alpha / a.u_scale;
   if (n > 0) {
     k_pack_xq<<<blocks_of(n, kThreads), kThreads, 0, st>>>((int32_t)n, x, q, (double4 *)ws,
-                                                           a.half_dx, tab);
+                                                           alpha, a.u_scale, seeds);
     const bool wide = n > kNarrowAtoms;
     if (e_total) {
       if (wide) k_ewald_real<true, true><<<nblk, kEwThreads, 0, st>>>(a);

@@ -186,3 +186,30 @@ def test_bin_counts_any_order(dev, orc, n):
         assert np.array_equal(ids.cpu().numpy(), want)
         assert np.array_equal(xs.cpu().numpy(), x[want])
         assert np.array_equal(cs.cpu().numpy()[:-1], np.searchsorted(cell[want], np.arange(np.prod(nc))))
+
+
+@pytest.mark.parametrize("alpha", [0.05, 1.2, 2.4])
+@pytest.mark.parametrize("n", [2, 65, 1000])
+def test_ewald_real_tables(dev, orc, alpha, n):
+    """Real-space forces and energy for alpha rc from 0.125 to 6 (the tables' intervals from
+    a 1000th to a 20th of a unit), pairs from 1e-3 apart to the cutoff, against the direct
+    sum at the pair kernels' bar (1e-12 of the largest), with and without energies."""
+    import torch
+    from paper_2109_09056_amd import md, ops
+    L = np.array([11.0, 12.0, 13.0])
+    x = li.random_gas(n, L, 7 + n)
+    x[1] = x[0] + np.array([1e-3, 0.0, 0.0])
+    x = np.mod(x, L)
+    g = np.random.default_rng(n)
+    q = g.uniform(-1.5, 1.5, n)
+    T = lambda a: torch.as_tensor(a, dtype=torch.float64, device=dev).contiguous()
+    xs, _, _, ids, cs = ops.bin(L, 2.8, T(x))
+    qs = ops.gather_rows(ids, T(q))
+    nl = md.NeighborList(L, 2.8, ops.FULL, device=dev).build(xs, cs)
+    F, E = ops.ewald_real(L, alpha, 2.5, xs, qs, nl.nbr, nl.nnbr, nl.maxn, want_energy=True)
+    F2, _ = ops.ewald_real(L, alpha, 2.5, xs, qs, nl.nbr, nl.nnbr, nl.maxn)
+    e_o, F_o = orc.ewald_direct(x, q, L, alpha, 2.5)
+    for f in (F, F2):
+        fg = ops.scatter_rows(ids, f).cpu().numpy()
+        assert np.abs(fg - F_o).max() <= 1e-12 * np.abs(F_o).max()
+    assert abs(E.item() - e_o.sum()) <= 1e-12 * np.abs(e_o).sum()
