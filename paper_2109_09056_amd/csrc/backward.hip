@@ -10,7 +10,7 @@
 //   ds/deps  = t (48 sr6 - 24)
 //   ds/dsig  = t (576 eps/sigma sr6 - 144 eps/sigma)
 // K_ij is symmetric in (i, j), so the position gradient is a gather over the
-// row of atom i -- one lane per atom, no atomics.  Parameter gradients are
+// row of atom i -- a team of lanes per atom, no atomics.  Parameter gradients are
 // accumulated per lane by the neighbor's type, reduced per block by the
 // lane's own type in a fixed order, and summed over blocks by one column-sum
 // launch: the whole adjoint is bitwise reproducible.
@@ -24,12 +24,15 @@ namespace {
 
 constexpr int kThreads = 128;  // atoms per block
 constexpr int kWaves = kThreads / kWave;
-constexpr int kTeam = 2;       // lanes per atom for one or two types
-// Up to this many atoms (at most 512 blocks, two per compute unit at kTeam
-// lanes) one or two types take four lanes per atom: more waves in flight for a
-// grid that would leave the chip half idle (32k atoms: 26.6 -> 22.1 us; at
-// 256k atoms the four-lane form is 5 % slower).
-constexpr int64_t kSmallVjp = 65536;
+// One or two types: four lanes per atom with two slots per group and lane.  Bound by the
+// gathers (x_j and g_j in two loads each, and the type, gathered with them instead of
+// after the cutoff test).  256,000 atoms two types FP64 / 500,000 one type mixed (us): two
+// lanes with 3 slots in whole and partial groups 93.8 / 139.6; masked groups and two
+// lanes with 3 slots 92.7 / 145.7; four lanes with 3, 2, 1 slots 84.9 / 131.9, 83.1 / 131.5,
+// 88.0 / 140.1.  32,000 two types mixed: 19.4 -> 16.1.  More types: one lane, 3 slots.
+constexpr int kTeam = 4;
+constexpr int kSlots = 2;
+constexpr int kManySlots = 3;
 
 struct BwdArgs {
   BoxK b;
@@ -148,7 +151,7 @@ __global__ __launch_bounds__(kThreads * TEAM) void k_vjp(BwdArgs a) {
         a.nbr + (int64_t)(i >> 6) * a.maxn * kWave + (i & (kWave - 1)) + (int64_t)tm * kWave;
     double ax = 0.0, ay = 0.0, az = 0.0;
     // one list entry: j with its position and cotangent
-    auto entry = [&](auto wrap, int32_t j, const double *xj, const double *gj, bool valid) {
+    auto entry = [&](auto wrap, int tj, const double *xj, const double *gj, bool valid) {
       double dx = xi - xj[0], dy = yi - xj[1], dz = zi - xj[2];
       if constexpr (decltype(wrap)::value) {
         dx = min_image(dx, a.b.L[0], a.b.invL[0]);
@@ -157,12 +160,10 @@ __global__ __launch_bounds__(kThreads * TEAM) void k_vjp(BwdArgs a) {
       }
       const double r2 = dist2(dx, dy, dz);
       if (valid && r2 < a.rc2) {
-        int tj = 0;
         BCoef c;
         if constexpr (TT == 1) {
           c = c1;
         } else {
-          tj = a.type[j];
           const double *t = tab + 7 * (ti * T + tj);
           c = BCoef{t[0], t[1], t[2], t[3], t[4], t[5], t[6]};
         }
@@ -195,23 +196,19 @@ __global__ __launch_bounds__(kThreads * TEAM) void k_vjp(BwdArgs a) {
         }
       }
     };
-    // Groups of U slots: the U index loads, then the gathers of x_j and g_j, then
-    // the U entries.  Whole groups read indices at fixed offsets from one row
-    // pointer; the last, partial group gathers only slots below cnt.  Row order
-    // throughout, so the sums match one slot at a time.
+    // Masked groups of U slots, as in the forces: the U index loads, then the gathers of
+    // x_j, g_j and the type, then the U entries; slots beyond cnt repeat the lane's first
+    // entry.  Row order throughout, so the sums match one slot at a time.
     auto walk = [&](auto wrap) {
-      // 3 slots per group: 99 VGPRs against 112-118 with 4, and at 256,000 atoms
-      // (two types) 96.2 -> 92.4 us mixed, 95.3 -> 92.1 us FP64; 2 slots or
-      // occupancy hints (5-6 waves per SIMD) gained nothing or spilled.
-      constexpr int U = 3;
-      const int32_t whole = cnt - cnt % U;
-      const int32_t *rp = row;
-      int32_t k = 0;
+      constexpr int U = TT == 0 ? kManySlots : kSlots;
       constexpr int kStep = TEAM * kWave;  // ints between this lane's consecutive entries
-      for (; k < whole; k += U, rp += U * kStep) {
+      const int32_t *rp = row;
+#pragma unroll 1
+      for (int32_t k = 0; k < cnt; k += U, rp += U * kStep) {
         int32_t jj[U];
+        int tj[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) jj[u] = rp[u * kStep];
+        for (int u = 0; u < U; ++u) jj[u] = rp[(k + u < cnt ? u : 0) * kStep];
         double xj[U][3], gj[U][3];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -222,31 +219,10 @@ __global__ __launch_bounds__(kThreads * TEAM) void k_vjp(BwdArgs a) {
             xj[u][q] = px[q];
             gj[u][q] = pg[q];
           }
+          tj[u] = TT == 1 ? 0 : a.type[jj[u]];
         }
 #pragma unroll
-        for (int u = 0; u < U; ++u) entry(wrap, jj[u], xj[u], gj[u], true);
-      }
-      if (k < cnt) {
-        int32_t jj[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) jj[u] = rp[(k + u < cnt ? u : 0) * kStep];
-        double xj[U][3], gj[U][3];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-#pragma unroll
-          for (int q = 0; q < 3; ++q) xj[u][q] = gj[u][q] = 0.0;
-          if (k + u < cnt) {
-            const double *px = pos_of<WIDE>(a.x, jj[u]);
-            const double *pg = pos_of<WIDE>(a.g, jj[u]);
-#pragma unroll
-            for (int q = 0; q < 3; ++q) {
-              xj[u][q] = px[q];
-              gj[u][q] = pg[q];
-            }
-          }
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) entry(wrap, jj[u], xj[u], gj[u], k + u < cnt);
+        for (int u = 0; u < U; ++u) entry(wrap, tj[u], xj[u], gj[u], k + u < cnt);
       }
     };
     if (interior)
@@ -375,19 +351,10 @@ int launch_backward(const BoxK &b, int precision, double rc, int32_t ntypes, con
     else                                                                     \
       k_vjp<M, TT, true, TEAM><<<nblk, kThreads * TEAM, 0, st>>>(a);        \
   } while (0)
-  const bool small = n <= kSmallVjp;
   if (ntypes == 1) {
-    if (small) {
-      if (mixed) LJMD_VJP(true, 1, 4); else LJMD_VJP(false, 1, 4);
-    } else {
-      if (mixed) LJMD_VJP(true, 1, kTeam); else LJMD_VJP(false, 1, kTeam);
-    }
+    if (mixed) LJMD_VJP(true, 1, kTeam); else LJMD_VJP(false, 1, kTeam);
   } else if (ntypes == 2) {
-    if (small) {
-      if (mixed) LJMD_VJP(true, 2, 4); else LJMD_VJP(false, 2, 4);
-    } else {
-      if (mixed) LJMD_VJP(true, 2, kTeam); else LJMD_VJP(false, 2, kTeam);
-    }
+    if (mixed) LJMD_VJP(true, 2, kTeam); else LJMD_VJP(false, 2, kTeam);
   } else {
     if (mixed) LJMD_VJP(true, 0, 1); else LJMD_VJP(false, 0, 1);
   }
