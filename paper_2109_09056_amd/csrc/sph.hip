@@ -12,8 +12,8 @@
 //   acceleration:  a_i = -sum_j m (P_i + P_j) G(r_ij) d_ij,  d_ij = x_i - x_j
 //                  (Monaghan 1992, no artificial viscosity)
 //
-// Traversal as in the LJ force kernel: two lanes per particle over its row of
-// the 64-particle tile (entries t, t + 2, ...), six gathers in flight per
+// Traversal as in the LJ force kernel: four lanes per particle over its row of
+// the 64-particle tile (entries t, t + 4, ...), four gathers in flight per
 // lane, a butterfly to combine the team, 128 particles per block, blocks
 // renumbered per XCD; no atomics, so results are bitwise reproducible.  The
 // acceleration pass first packs (x, y, z, P) per particle into 32-byte
@@ -26,17 +26,23 @@ namespace ljmd {
 namespace {
 
 constexpr int kSphAtoms = 128;  // particles per block
-constexpr int kSphTeam = 2;     // lanes per particle
+// Lanes per particle and slots per group and lane: four lanes gather from nearby
+// addresses, as in the LJ kernel.  Density and acceleration with its packing (us): two
+// lanes with 6 slots in whole and partial groups 117.7 + 152.0 at 512,000 particles near
+// the lattice, 127.9 + 166.0 once melted, 12.5 + 18.0 at 32,768 melted; now 107.9 + 137.7,
+// 129.8 + 160.6, 10.1 + 14.1 (with a square root 110.7 + 146.1, 132.4 + 166.9, 10.8 +
+// 15.4).  Blocks of 64 particles, 2, 3, 5, 6 slots or eight lanes are slower or no faster.
+constexpr int kSphTeam = 4;
+constexpr int kSphUnroll = 4;
 constexpr int kSphThreads = kSphAtoms * kSphTeam;
 constexpr int kSphWaves = kSphThreads / kWave;
-constexpr int kSphUnroll = 6;   // gathers in flight per lane
 constexpr double kPi = 3.14159265358979323846;
 
 struct SphArgs {
   BoxK b;
   double sup2;    // (2h)^2
   double margin;  // 2h: particles this far from every face need no minimum image
-  double inv_h;
+  double h, inv_h;
   double wnorm;   // m / (pi h^3)
   double gnorm;   // m / (pi h^5)
   double mass, c0sq, rho0;
@@ -62,12 +68,13 @@ __device__ __forceinline__ const double4 *rec_of(const double4 *xp, int32_t j) {
     return (const double4 *)((const char *)xp + ((uint32_t)j << 5));
 }
 
-// q = r/h and 1/q (only used where q >= 1).  Measured against r^-1 from the
-// hardware reciprocal square root with Newton steps, this form was as fast for
-// the density pass and faster for the acceleration pass.
+// q = r/h and 1/q (only used where q >= 1) from one refined reciprocal square root; r^2 =
+// 0 (coincident particles) gives q = 0.  Densities' and accelerations' errors against
+// long double 2 % and 9 % below those with a square root and a reciprocal of q.
 __device__ __forceinline__ void q_of(double r2, const SphArgs &a, double &q, double &hq) {
-  q = __builtin_sqrt(r2) * a.inv_h;
-  hq = recip64(q);
+  const double ir = rsqrt64(__builtin_fmax(r2, 1e-290));
+  q = (r2 * ir) * a.inv_h;
+  hq = ir * a.h;
 }
 
 // w(q) inside the support, 0 outside or on padding slots
@@ -106,20 +113,19 @@ __device__ __forceinline__ void disp(const SphArgs &a, double xi, double yi, dou
   }
 }
 
-// Sum of w over lane t's entries of the row (cnt of them, kStep ints apart):
-// whole groups of U without masks, then one masked group.
+// Sum of w over lane t's entries of the row (cnt of them, kStep ints apart), in masked
+// groups of U: slots beyond cnt repeat the lane's first entry.
 template <bool WRAP, bool WIDE>
 __device__ __forceinline__ double density_row(const SphArgs &a, const int32_t *row, int32_t cnt,
                                               double xi, double yi, double zi) {
   constexpr int U = kSphUnroll;
   constexpr int kStep = kSphTeam * kWave;
   double s = 0.0;
-  const int32_t whole = cnt - cnt % U;
-  int32_t k = 0;
-  for (; k < whole; k += U, row += U * kStep) {
+#pragma unroll 1
+  for (int32_t k = 0; k < cnt; k += U, row += U * kStep) {
     int32_t j[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) j[u] = row[u * kStep];
+    for (int u = 0; u < U; ++u) j[u] = row[(k + u < cnt ? u : 0) * kStep];
     double xj[U], yj[U], zj[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -132,35 +138,7 @@ __device__ __forceinline__ double density_row(const SphArgs &a, const int32_t *r
     for (int u = 0; u < U; ++u) {
       double dx, dy, dz;
       disp<WRAP>(a, xi, yi, zi, xj[u], yj[u], zj[u], dx, dy, dz);
-      s += spline_w(dist2(dx, dy, dz), true, a);
-    }
-  }
-  if (k < cnt) {
-    int32_t j[U];
-    bool ok[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      ok[u] = k + u < cnt;
-      j[u] = row[(ok[u] ? u : 0) * kStep];
-    }
-    double xj[U], yj[U], zj[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      xj[u] = xi;
-      yj[u] = yi;
-      zj[u] = zi;
-      if (ok[u]) {  // no gathers for the padding slots
-        const double *p = pos_of<WIDE>(a.x, j[u]);
-        xj[u] = p[0];
-        yj[u] = p[1];
-        zj[u] = p[2];
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      double dx, dy, dz;
-      disp<WRAP>(a, xi, yi, zi, xj[u], yj[u], zj[u], dx, dy, dz);
-      s += spline_w(dist2(dx, dy, dz), ok[u], a);
+      s += spline_w(dist2(dx, dy, dz), k + u < cnt, a);
     }
   }
   return s;
@@ -229,41 +207,23 @@ __device__ __forceinline__ void accel_pair(const SphArgs &a, const double4 &me, 
   az = __builtin_fma(c, dz, az);
 }
 
-// Lane t's entries of the row: whole groups of U without masks, then one masked group.
+// Lane t's entries of the row in masked groups of U, as density_row.
 template <bool WRAP, bool WIDE>
 __device__ __forceinline__ void accel_row(const SphArgs &a, const int32_t *row, int32_t cnt,
                                           const double4 &me, double &ax, double &ay,
                                           double &az) {
   constexpr int U = kSphUnroll;
   constexpr int kStep = kSphTeam * kWave;
-  const int32_t whole = cnt - cnt % U;
-  int32_t k = 0;
-  for (; k < whole; k += U, row += U * kStep) {
+#pragma unroll 1
+  for (int32_t k = 0; k < cnt; k += U, row += U * kStep) {
     int32_t j[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) j[u] = row[u * kStep];
+    for (int u = 0; u < U; ++u) j[u] = row[(k + u < cnt ? u : 0) * kStep];
     double4 o[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) o[u] = *rec_of<WIDE>(a.xp, j[u]);
 #pragma unroll
-    for (int u = 0; u < U; ++u) accel_pair<WRAP, WIDE>(a, me, o[u], true, ax, ay, az);
-  }
-  if (k < cnt) {
-    int32_t j[U];
-    bool ok[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      ok[u] = k + u < cnt;
-      j[u] = row[(ok[u] ? u : 0) * kStep];
-    }
-    double4 o[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      o[u] = me;
-      if (ok[u]) o[u] = *rec_of<WIDE>(a.xp, j[u]);
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) accel_pair<WRAP, WIDE>(a, me, o[u], ok[u], ax, ay, az);
+    for (int u = 0; u < U; ++u) accel_pair<WRAP, WIDE>(a, me, o[u], k + u < cnt, ax, ay, az);
   }
 }
 
@@ -295,28 +255,21 @@ __global__ __launch_bounds__(kSphThreads) void k_sph_accel(SphArgs a) {
   ax = team_sum<kSphTeam>(ax);
   ay = team_sum<kSphTeam>(ay);
   az = team_sum<kSphTeam>(az);
-  if (live && t == 0) {
-    const double f[3] = {-a.gnorm * ax, -a.gnorm * ay, -a.gnorm * az};
-    if (!STEP || a.acc) {
-      a.acc[3 * (int64_t)i] = f[0];
-      a.acc[3 * (int64_t)i + 1] = f[1];
-      a.acc[3 * (int64_t)i + 2] = f[2];
-    }
+  if (live && t < 3) {  // lane t of the team finishes component t
+    const int k = t;
+    const int64_t q = 3 * (int64_t)i + k;
+    const double f = -a.gnorm * (k == 0 ? ax : (k == 1 ? ay : az));
+    if (!STEP || a.acc) a.acc[q] = f;
     if constexpr (STEP) {
-      const double xo[3] = {me.x, me.y, me.z};  // the packed copy of x_i
-#pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        const int64_t q = 3 * (int64_t)i + k;
-        const double L = a.b.L[k];
-        const double kick = a.hdt * f[k];
-        const double vh = (a.v[q] + kick) + kick;
-        double xq = xo[k] + a.dt * vh;
-        if (xq >= L) xq -= L;
-        else if (xq < 0.0) xq += L;
-        if (xq >= L) xq -= L;
-        a.v[q] = vh;
-        a.x_out[q] = xq;
-      }
+      const double L = k == 0 ? a.b.L[0] : (k == 1 ? a.b.L[1] : a.b.L[2]);
+      const double kick = a.hdt * f;
+      const double vh = (a.v[q] + kick) + kick;
+      double xq = (k == 0 ? me.x : (k == 1 ? me.y : me.z)) + a.dt * vh;  // me: packed x_i
+      if (xq >= L) xq -= L;
+      else if (xq < 0.0) xq += L;
+      if (xq >= L) xq -= L;
+      a.v[q] = vh;
+      a.x_out[q] = xq;
     }
   }
 }
@@ -332,6 +285,7 @@ SphArgs make_args(const BoxK &b, double h, double mass, double c0, double rho0, 
   a.b = b;
   a.sup2 = (2.0 * h) * (2.0 * h);
   a.margin = 2.0 * h;
+  a.h = h;
   a.inv_h = 1.0 / h;
   a.wnorm = mass / (kPi * h * h * h);
   a.gnorm = mass / (kPi * h * h * h * h * h);

@@ -213,3 +213,34 @@ def test_ewald_real_tables(dev, orc, alpha, n):
         fg = ops.scatter_rows(ids, f).cpu().numpy()
         assert np.abs(fg - F_o).max() <= 1e-12 * np.abs(F_o).max()
     assert abs(E.item() - e_o.sum()) <= 1e-12 * np.abs(e_o).sum()
+
+@pytest.mark.parametrize("n,ntypes", [(1, 1), (127, 2), (129, 1), (1000, 2), (1000, 3)])
+def test_vjp_and_sph_at_block_edges(dev, orc, n, ntypes):
+    """VJP of the forces (teams of four; one lane for three types) and the SPH passes on
+    sizes around a block, rows of 0 to a few dozen entries: gradients against the oracle's
+    (1e-12 of the largest), densities and accelerations against its sums."""
+    import torch
+    from paper_2109_09056_amd import md, ops
+    L = np.array([11.0, 12.0, 13.0])
+    x, ty = _gas(n, L, 3 + n, ntypes)
+    p = ntypes * (ntypes + 1) // 2
+    eps, sig = np.linspace(0.9, 1.1, p), np.linspace(0.9, 1.0, p)
+    T = lambda a, d=torch.float64: torch.as_tensor(np.ascontiguousarray(a), dtype=d, device=dev)
+    xs, _, ts, ids, cs = ops.bin(L, 2.8, T(x), None, T(ty, torch.int32))
+    nl = md.NeighborList(L, 2.8, ops.FULL, device=dev).build(xs, cs)
+    g = np.random.default_rng(n).normal(size=(n, 3))
+    gs = ops.gather_rows(ids, T(g))
+    gx, ge, gsig = ops.force_backward(L, ops.FP64, 2.5, T(eps), T(sig), xs, ts, nl.nbr, nl.nnbr,
+                                      nl.maxn, gs)
+    gx_o, ge_o, gs_o = orc.force_vjp(x, L, 2.5, g, eps, sig, ty if ntypes > 1 else None)
+    near = lambda a, b: np.abs(a - b).max() <= 1e-12 * max(np.abs(b).max(), 1e-30)
+    assert near(ops.scatter_rows(ids, gx).cpu().numpy(), gx_o)
+    assert near(ge.cpu().numpy(), ge_o) and near(gsig.cpu().numpy(), gs_o)
+    if ntypes > 1:
+        return
+    rho, _ = ops.sph_density(L, 1.2, 1.0, 10.0, 1.0, xs, nl.nbr, nl.nnbr, nl.maxn)
+    acc = ops.sph_accel(L, 1.2, 1.0, 10.0, 1.0, xs, rho, nl.nbr, nl.nnbr, nl.maxn)
+    rho_o = orc.sph_density(x, L, 1.2, 1.0)
+    acc_o = orc.sph_accel(x, L, 1.2, 1.0, 10.0, 1.0, rho_o)
+    assert near(ops.scatter_rows(ids, rho).cpu().numpy(), rho_o)
+    assert near(ops.scatter_rows(ids, acc).cpu().numpy(), acc_o)
