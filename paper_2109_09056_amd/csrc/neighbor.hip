@@ -33,10 +33,9 @@ constexpr int kRowCap = 128;
 constexpr int kDenseSlots = 16;
 constexpr int kDenseRowCap = 256;
 // Home atoms whose rows are buffered in LDS at once.  8 rather than 16 halves
-// the one-wavefront block's LDS, so more blocks fit on a compute unit: the
-// integer-tested build at 500,000 atoms went 230.5 -> 207.0 us (full list),
-// 200.9 -> 173.3 (half), 388.9 -> 240.2 (dense shape); 4 gave 213.7 / 178.4 /
-// 231.6.
+// the one-wavefront block's LDS, so more blocks fit on a compute unit: at 500,000
+// atoms 189.4 -> 171.2 us (full list), 159.3 -> 143.6 (half), 362.6 -> 261.3 (dense
+// shape, 512,000 particles); batches that end at multiples of 8 atoms 174.1 / 145.8 / 265.6.
 constexpr int kBatch = 8;
 constexpr int kFlushRows = kWave / kBatch;  // list rows of a batch written per store instruction
 // LDS row stride ROWCAP + 1 (odd): lanes reading entry k of different rows hit distinct banks
@@ -67,7 +66,7 @@ struct BuildOut {
 // sqrt(3) q, and with R = rlist / q the integer r2q = |u_i - u_j|^2 decides
 //   r2q < t_in  = floor((R - 1.75)^2): inside rlist,
 //   r2q > t_out = ceil((R + 1.75)^2):  outside rlist,
-// and only the pairs between (about 0.15 per atom in the dense liquid) take
+// and only the pairs between (about 0.08 per atom in the dense liquid) take
 // the FP64 test with the minimum image.  The image of a candidate nearest the
 // centre is the one nearest the home atom for every pair within rlist when
 // the home atom lies within L/2 - rlist of the centre per axis (the pair is
@@ -81,10 +80,13 @@ struct QuantK {
   int32_t t_out;   // r2q above: outside rlist
   double home[3];  // bound on |home atom - centre| per axis: L/2 - rlist, rounded down
 };
-constexpr double kQuantSpan = 8000.0;  // lattice steps per 1.5 cell edges
-constexpr int32_t kQuantMax = 8190;    // |u| of a staged coordinate
-// z of an empty slot: |dz| <= 33,190, so r2q stays below 2^31 and above t_out
-constexpr int32_t kQuantEmpty = 25000;
+constexpr double kQuantSpan = 16000.0;  // lattice steps per 1.5 cell edges
+constexpr int32_t kQuantMax = 16380;    // |u| of a staged coordinate
+// r2q <= 3 * 32,760^2 = 3.22e9 and t_in <= (10,667 - 1.75)^2 = 1.14e8: r2q - t_in modulo
+// 2^32 is at or above 2^32 - t_in exactly when r2q < t_in.
+// z of an empty slot: 15,620 <= |dz| <= 48,380, so r2q is between 2.4e8 (above t_out)
+// and 2.9e9
+constexpr int32_t kQuantEmpty = 32000;
 
 typedef short short2v __attribute__((ext_vector_type(2)));
 
@@ -280,27 +282,153 @@ __device__ __forceinline__ void build_staged(const BoxK &b, double rl2, const do
   }
 }
 
-// Store a hit of the lanes' ballot m: entry base + (hits in lower lanes) of the
-// home atom's row (LDS buffer, tiled row or compressed row).
-// room: base + popcount(m) <= maxn (uniform), so no lane needs its own test.
-template <bool BUF, int ROWCAP, int MODE>
-__device__ __forceinline__ void store_hit(const BuildOut &o, int32_t *row, int32_t *rowbuf, int bi,
-                                          int64_t off, int32_t base, uint64_t m, bool room,
-                                          int32_t j, int32_t maxn) {
-  const int32_t k = (int32_t)__builtin_amdgcn_mbcnt_hi(
-      (uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, (uint32_t)base));
-  if constexpr (MODE == kCsr) {
-    if (off + k < o.cap) o.csr[off + k] = j;
-  } else if (room) {
-    if (BUF)
-      rowbuf[bi * (ROWCAP + 1) + k] = j;
-    else
-      row[(int64_t)k * kWave] = j;
-  } else if (k < maxn) {
-    if (BUF)
-      rowbuf[bi * (ROWCAP + 1) + k] = j;
-    else
-      row[(int64_t)k * kWave] = j;
+// The rows of the cell's home atoms from NS staged slots (slots from nslot on are
+// empty: they never hit).  Per home atom, in two passes over the slots:
+//   1. the integer test of every candidate; the lane masks of the hits stay in scalar
+//      registers, and one running minimum notes whether any pair fell between the two
+//      thresholds (then, about once in thirteen atoms, those pairs take the FP64 test);
+//   2. with every mask known, and so the row's length and every slot's place in it, the
+//      stores, without a capacity test per slot.
+// What bounds it: the scalar unit, one instruction per cycle for the compute unit's
+// four SIMDs, issued 100 M instructions against 76 M vector ones when each slot was
+// tested, corrected, counted, checked against maxn and stored before the next (22
+// scalar instructions per slot, now about 10).  Tiled lists (us), that -> this with the
+// grouped staging of build_quant: 500,000 atoms full 211.8 -> 171.1, half 176.9 -> 144.4,
+// 110,447 70.4 -> 56.1, 32,000 39.3 -> 31.3, 512,000 SPH particles (dense shape) 323 -> 263;
+// compressed rows of 131,072 atoms (count and fill) 119 -> 99.5.
+template <bool HALF, bool BUF, int NS, int SLOTS, int ROWCAP, int MODE>
+__device__ __forceinline__ void quant_rows(const BoxK &b, const QuantK &q, const double *cc,
+                                           double rl2, const double *__restrict__ x, int32_t h0,
+                                           int32_t h1, int32_t tc, const int32_t (&qxy)[SLOTS],
+                                           const int32_t (&qz)[SLOTS],
+                                           const int32_t (&qj)[SLOTS], const BuildOut &o,
+                                           int32_t *rowbuf, int32_t *rowcnt, int32_t &maxc) {
+  const int32_t maxn = o.maxn;
+  int32_t *__restrict__ nbr = o.nbr;
+  int32_t *__restrict__ nnbr = o.nnbr;
+  const int lane = threadIdx.x & (kWave - 1);
+  constexpr int kRowStride = ROWCAP + 1;
+  const uint32_t band = (uint32_t)(q.t_out - q.t_in), inside = 0u - (uint32_t)q.t_in;
+  int32_t hxy = 0, huz = 0;  // lattice coordinates of home atom c0 + lane
+  int32_t c0 = h0 - kWave;
+  for (int32_t b0 = h0; b0 < h1; b0 += kBatch) {
+    const int nb = h1 - b0 < kBatch ? h1 - b0 : kBatch;
+    if (b0 + kBatch - c0 > kWave) {
+      c0 = b0;
+      const int32_t ih = b0 + lane;
+      if (ih < h1)  // a staged candidate: in range
+        quantize(x + 3 * (int64_t)ih, cc, b, q.invq, hxy, huz);
+    }
+    for (int bi = 0; bi < nb; ++bi) {
+      const int32_t i = b0 + bi;
+      const int src = i - c0;
+      const short2v ui = __builtin_bit_cast(short2v, __builtin_amdgcn_readlane(hxy, src));
+      const int32_t uzi = __builtin_amdgcn_readlane(huz, src);
+      const int32_t tself = tc + (i - h0);  // candidate number of atom i
+      const uint64_t self = 1ull << (tself & (kWave - 1));
+      // squared lattice distance of slot r's candidate minus t_in (modulo 2^32)
+      auto above_in = [&](int r) {
+        const short2v d = __builtin_bit_cast(short2v, qxy[r]) - ui;
+        const int32_t dz = qz[r] - uzi;
+        return (uint32_t)__builtin_amdgcn_sdot2(d, d, __mul24(dz, dz) - q.t_in, false);
+      };
+      uint64_t m[NS];
+      uint32_t least = ~0u;
+#pragma unroll
+      for (int r = 0; r < NS; ++r) {
+        const uint32_t v = above_in(r);
+        m[r] = __builtin_amdgcn_ballot_w64(v >= inside);
+        least = v < least ? v : least;
+      }
+      if (__builtin_amdgcn_ballot_w64(least <= band) != 0) {
+        // the FP64 test with the minimum image for the pairs near rlist: each lane's
+        // such slots, one per round (a second round is rare)
+        uint32_t left = 0, hit = 0;
+#pragma unroll
+        for (int r = 0; r < NS; ++r) left |= above_in(r) <= band ? 1u << r : 0u;
+        const double xi = x[3 * (int64_t)i], yi = x[3 * (int64_t)i + 1],
+                     zi = x[3 * (int64_t)i + 2];
+        do {
+          const uint32_t bit = left & (0u - left);
+          int32_t j = i;
+#pragma unroll
+          for (int r = 0; r < NS; ++r) j = bit == 1u << r ? qj[r] : j;
+          const double *p = x + 3 * (int64_t)j;
+          const double dx = min_image(xi - p[0], b.L[0], b.invL[0]);
+          const double dy = min_image(yi - p[1], b.L[1], b.invL[1]);
+          const double dzz = min_image(zi - p[2], b.L[2], b.invL[2]);
+          hit |= dist2(dx, dy, dzz) < rl2 ? bit : 0u;
+          left ^= bit;
+        } while (__builtin_amdgcn_ballot_w64(left != 0) != 0);
+#pragma unroll
+        for (int r = 0; r < NS; ++r) m[r] |= __builtin_amdgcn_ballot_w64((hit & 1u << r) != 0);
+      }
+      // the candidates that may be neighbours at all: j > i, or all but atom i itself
+#pragma unroll
+      for (int r = 0; r < NS; ++r) {
+        if constexpr (HALF)
+          m[r] &= __builtin_amdgcn_ballot_w64(qj[r] > i);
+        else
+          m[r] &= r == (tself >> 6) ? ~self : ~0ull;
+      }
+      int32_t total = 0;
+#pragma unroll
+      for (int r = 0; r < NS; ++r) total += (int32_t)__popcll(m[r]);
+      if constexpr (MODE != kCount) {
+        int32_t *row = MODE == kTiled ? nbr + (int64_t)(i >> 6) * maxn * kWave + (i & (kWave - 1))
+                                      : nullptr;
+        const int64_t off = MODE == kCsr ? o.offsets[i] : 0;
+        // entry of this lane's hit in slot r of a row that starts at `first`
+        auto entry = [&](int r, int32_t first) {
+          return (int32_t)__builtin_amdgcn_mbcnt_hi(
+              (uint32_t)(m[r] >> 32),
+              __builtin_amdgcn_mbcnt_lo((uint32_t)m[r], (uint32_t)first));
+        };
+        const bool room = MODE == kCsr ? off + total <= o.cap : total <= maxn;  // uniform
+        int32_t base = 0;
+        if (room) {
+          int32_t *out = BUF ? rowbuf + bi * kRowStride : (MODE == kCsr ? o.csr + off : row);
+#pragma unroll
+          for (int r = 0; r < NS; ++r) {
+            if (__builtin_amdgcn_inverse_ballot_w64(m[r])) {
+              const int32_t k = entry(r, base);
+              out[BUF || MODE == kCsr ? (int64_t)k : (int64_t)k * kWave] = qj[r];
+            }
+            base += (int32_t)__popcll(m[r]);
+          }
+        } else {
+#pragma unroll
+          for (int r = 0; r < NS; ++r) {
+            if (__builtin_amdgcn_inverse_ballot_w64(m[r])) {
+              const int32_t k = entry(r, base);
+              if constexpr (MODE == kCsr) {
+                if (off + k < o.cap) o.csr[off + k] = qj[r];
+              } else if (k < maxn) {
+                if (BUF)
+                  rowbuf[bi * kRowStride + k] = qj[r];
+                else
+                  row[(int64_t)k * kWave] = qj[r];
+              }
+            }
+            base += (int32_t)__popcll(m[r]);
+          }
+        }
+      }
+      if (lane == 0) rowcnt[bi] = MODE == kTiled ? (total < maxn ? total : maxn) : total;
+      maxc = total > maxc ? total : maxc;
+    }
+    __syncthreads();  // rowbuf / rowcnt written by other lanes of this one-wavefront block
+    if (MODE != kCsr && lane < nb) nnbr[b0 + lane] = rowcnt[lane];
+    if (BUF) {
+      const int a = lane % kBatch;
+      const int32_t mine = a < nb ? rowcnt[a] : 0;
+      const int32_t kmax = wave_max(mine);
+      const int32_t i = b0 + a;
+      int32_t *row = nbr + (int64_t)(i >> 6) * maxn * kWave + (i & (kWave - 1));
+      for (int32_t k = lane / kBatch; k < kmax; k += kFlushRows)
+        if (k < mine) row[(int64_t)k * kWave] = rowbuf[a * kRowStride + k];
+    }
+    __syncthreads();  // before the next batch overwrites rowbuf / rowcnt
   }
 }
 
@@ -317,25 +445,49 @@ __device__ __forceinline__ bool build_quant(const BoxK &b, const QuantK &q, cons
                                             const int32_t *rs, const int32_t *pre,
                                             const BuildOut &o, int32_t *rowbuf, int32_t *rowcnt,
                                             int32_t &maxc) {
-  const int32_t maxn = o.maxn;
-  int32_t *__restrict__ nbr = o.nbr;
-  int32_t *__restrict__ nnbr = o.nnbr;
   static_assert(!BUF || MODE == kTiled, "rows are buffered only for the tiled list");
   const int lane = threadIdx.x & (kWave - 1);
-  constexpr int kRowStride = ROWCAP + 1;
   int32_t qxy[SLOTS], qz[SLOTS], qj[SLOTS];
   bool good = true;
+  // Slots are staged in groups of four, the loads of a group in flight together; a
+  // lane's candidate numbers grow by 64 per slot, so its range is found from the last one.
+  constexpr int kGroup = 4;
+  int sr = 0;
 #pragma unroll
-  for (int r = 0; r < SLOTS; ++r) {
-    const int32_t t = r * kWave + lane;
-    qj[r] = -1;
-    qxy[r] = 0;
-    qz[r] = kQuantEmpty;
-    if (r < nslot && t < total) {
-      const int32_t j = locate(t, rs, pre);
-      qj[r] = j;
-      good = quantize(x + 3 * (int64_t)j, cc, b, q.invq, qxy[r], qz[r]) && good;
+  for (int r0 = 0; r0 < SLOTS; r0 += kGroup) {
+    if (r0 < nslot) {  // uniform
+      double p[kGroup][3];
+#pragma unroll
+      for (int u = 0; u < kGroup; ++u) {
+        const int32_t t = (r0 + u) * kWave + lane;
+        const int32_t tt = t < total ? t : total - 1;
+        while (tt >= pre[sr + 1]) ++sr;
+        const int32_t j = rs[sr] + (tt - pre[sr]);
+        const double *xj = x + 3 * (int64_t)j;
+        p[u][0] = xj[0];
+        p[u][1] = xj[1];
+        p[u][2] = xj[2];
+        qj[r0 + u] = t < total ? j : -1;
+      }
+#pragma unroll
+      for (int u = 0; u < kGroup; ++u) {
+        const int r = r0 + u;
+        const bool in = quantize(p[u], cc, b, q.invq, qxy[r], qz[r]);
+        good = good && in;  // spare lanes repeat the last candidate
+        qz[r] = qj[r] >= 0 ? qz[r] : kQuantEmpty;
+        qxy[r] = qj[r] >= 0 ? qxy[r] : 0;
+      }
+    } else {
+#pragma unroll
+      for (int u = 0; u < kGroup; ++u) {
+        qj[r0 + u] = -1;
+        qxy[r0 + u] = 0;
+        qz[r0 + u] = kQuantEmpty;
+      }
     }
+#pragma unroll
+    for (int u = 0; u < kGroup; ++u)  // keep the groups apart: fewer registers
+      asm volatile("" : "+v"(qxy[r0 + u]), "+v"(qz[r0 + u]), "+v"(qj[r0 + u]));
   }
   for (int32_t c0 = h0; c0 < h1; c0 += kWave) {
     const int32_t ih = c0 + lane;
@@ -352,99 +504,45 @@ __device__ __forceinline__ bool build_quant(const BoxK &b, const QuantK &q, cons
   int32_t tc = 0;
   for (int sr = 0; pre[sr] < total; ++sr)
     if (rs[sr] <= h0 && h0 < rs[sr] + (pre[sr + 1] - pre[sr])) tc = pre[sr] + (h0 - rs[sr]);
-  double hx = 0.0, hy = 0.0, hz = 0.0;
-  int32_t hxy = 0, huz = 0;
-  for (int32_t b0 = h0; b0 < h1; b0 += kBatch) {
-    const int nb = h1 - b0 < kBatch ? h1 - b0 : kBatch;
-    if ((b0 - h0) % kWave == 0) {
-      const int32_t ih = b0 + lane;
-      if (ih < h1) {
-        const double *p = x + 3 * (int64_t)ih;
-        hx = p[0];
-        hy = p[1];
-        hz = p[2];
-        quantize(p, cc, b, q.invq, hxy, huz);  // a staged candidate: in range
-      }
-    }
-    for (int bi = 0; bi < nb; ++bi) {
-      const int32_t i = b0 + bi;
-      const int src = (b0 - h0) % kWave + bi;
-      const short2v ui = __builtin_bit_cast(short2v, __builtin_amdgcn_readlane(hxy, src));
-      const int32_t uzi = __builtin_amdgcn_readlane(huz, src);
-      int32_t *row = MODE == kTiled ? nbr + (int64_t)(i >> 6) * maxn * kWave + (i & (kWave - 1))
-                                    : nullptr;
-      const int64_t off = MODE == kCsr ? o.offsets[i] : 0;
-      const int32_t tself = tc + (i - h0);  // candidate number of atom i
-      int32_t base = 0;
-#pragma unroll
-      for (int r = 0; r < SLOTS; ++r) {
-        if (r < nslot) {
-          const short2v d = __builtin_bit_cast(short2v, qxy[r]) - ui;
-          const int32_t dz = qz[r] - uzi;
-          const int32_t r2q = __builtin_amdgcn_sdot2(d, d, __mul24(dz, dz), false);
-          // lane masks of single compares (one v_cmp each) combined in scalar
-          // registers; the full list drops atom i itself by its lane bit
-          uint64_t keep;
-          if constexpr (HALF)
-            keep = __builtin_amdgcn_ballot_w64(qj[r] > i);
-          else
-            keep = r == (tself >> 6) ? ~(1ull << (tself & (kWave - 1))) : ~0ull;
-          uint64_t m = __builtin_amdgcn_ballot_w64(r2q < q.t_in) & keep;
-          const uint64_t m_near = __builtin_amdgcn_ballot_w64(r2q <= q.t_out) & keep & ~m;
-          if (m_near != 0) {
-            // the FP64 test with the minimum image for the pairs near rlist, on
-            // every lane (lanes not near read atom i)
-            const bool near = __builtin_amdgcn_inverse_ballot_w64(m_near);
-            const double xi = readlane_f64(hx, src), yi = readlane_f64(hy, src),
-                         zi = readlane_f64(hz, src);
-            const double *p = x + 3 * (int64_t)(near ? qj[r] : i);
-            const double dx = min_image(xi - p[0], b.L[0], b.invL[0]);
-            const double dy = min_image(yi - p[1], b.L[1], b.invL[1]);
-            const double dzz = min_image(zi - p[2], b.L[2], b.invL[2]);
-            m |= __builtin_amdgcn_ballot_w64(dist2(dx, dy, dzz) < rl2) & m_near;
-          }
-          const int32_t k0 = base;  // row entries before this slot's hits
-          base += (int32_t)__popcll(m);
-          const bool room = base <= maxn;
-          if (MODE != kCount && __builtin_amdgcn_inverse_ballot_w64(m))
-            store_hit<BUF, ROWCAP, MODE>(o, row, rowbuf, bi, off, k0, m, room, qj[r], maxn);
-        }
-      }
-      if (lane == 0) rowcnt[bi] = MODE == kTiled ? (base < maxn ? base : maxn) : base;
-      maxc = base > maxc ? base : maxc;
-    }
-    __syncthreads();  // rowbuf / rowcnt written by other lanes of this one-wavefront block
-    if (MODE != kCsr && lane < nb) nnbr[b0 + lane] = rowcnt[lane];
-    if (BUF) {
-      const int a = lane % kBatch;
-      const int32_t mine = a < nb ? rowcnt[a] : 0;
-      const int32_t kmax = wave_max(mine);
-      const int32_t i = b0 + a;
-      int32_t *row = nbr + (int64_t)(i >> 6) * maxn * kWave + (i & (kWave - 1));
-      for (int32_t k = lane / kBatch; k < kmax; k += kFlushRows)
-        if (k < mine) row[(int64_t)k * kWave] = rowbuf[a * kRowStride + k];
-    }
-    __syncthreads();  // before the next batch overwrites rowbuf / rowcnt
-  }
+  tc = __builtin_amdgcn_readfirstlane(tc);
+  // the code for the fewest slots that hold the stencil: no test of every slot's number
+#define LJMD_ROWS(NS)                                                                          \
+  quant_rows<HALF, BUF, NS, SLOTS, ROWCAP, MODE>(b, q, cc, rl2, x, h0, h1, tc, qxy, qz, qj, o, \
+                                                 rowbuf, rowcnt, maxc)
+  if (nslot <= SLOTS - 6)
+    LJMD_ROWS(SLOTS - 6);
+  else if (nslot <= SLOTS - 4)
+    LJMD_ROWS(SLOTS - 4);
+  else if (nslot == SLOTS - 3)
+    LJMD_ROWS(SLOTS - 3);
+  else if (nslot == SLOTS - 2)
+    LJMD_ROWS(SLOTS - 2);
+  else
+    LJMD_ROWS(SLOTS);
+#undef LJMD_ROWS
   return true;
 }
 
 // Block -> (home cell, part): part p of nsplit takes the cell's home atoms
 // [len p / nsplit, len (p + 1) / nsplit) (each part stages the whole stencil).
-// QUANT: integer pre-test (grids of 3 or more cells per dimension); 76-93
-// VGPRs, so residency is set by the LDS row buffer.  Against the FP64-staged
-// kernel on the same lists at 500,000 atoms: 259 -> 207 us (full), 243 -> 173
-// us (half), 390 -> 240 us (dense shape).
+// QUANT: integer pre-test (grids of 3 or more cells per dimension).
 // FP64-staged kernel (smaller grids): the standard shape asks for 4 resident
 // wavefronts per SIMD (at most 128 VGPRs: the full-list build needs 131 and
 // keeps 3 otherwise; 2 registers spill), which took the 500k build from 299.5
 // to 259.6 us when this kernel served every grid; the dense shape asks for 3
 // (179 VGPRs otherwise, no spills at 166).
+// QUANT asks for 6 (80 VGPRs instead of 84), its count-only and compressed-row passes for
+// 7, the dense shape for 5: 500,000 atoms full 181.6 -> 172.7 us, dense 274.7 -> 267;
+// counting and filling 131,072 atoms 110 -> 99; 7 for the tiled rows spills and loses on
+// small grids.
+constexpr int quant_occupancy(int slots, int mode) {
+  return slots > kSlots ? 5 : (mode == kTiled ? 6 : 7);
+}
 template <int SLOTS>
 constexpr int build_occupancy() { return SLOTS <= kSlots ? 4 : 3; }
 
 template <bool HALF, int SLOTS, int ROWCAP, int MODE = kTiled, bool QUANT = false>
-__global__ __launch_bounds__(kWave, QUANT ? 1 : build_occupancy<SLOTS>())
+__global__ __launch_bounds__(kWave, QUANT ? quant_occupancy(SLOTS, MODE) : build_occupancy<SLOTS>())
 void k_build(GridK g, BoxK b, double rl2, const double *__restrict__ x,
              const int32_t *__restrict__ cell_start, BuildOut o, int32_t *__restrict__ max_count,
              int nsplit, QuantK q) {

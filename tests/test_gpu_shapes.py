@@ -244,3 +244,56 @@ def test_vjp_and_sph_at_block_edges(dev, orc, n, ntypes):
     acc_o = orc.sph_accel(x, L, 1.2, 1.0, 10.0, 1.0, rho_o)
     assert near(ops.scatter_rows(ids, rho).cpu().numpy(), rho_o)
     assert near(ops.scatter_rows(ids, acc).cpu().numpy(), acc_o)
+
+
+@pytest.mark.parametrize("kind", ["full", "half"])
+@pytest.mark.parametrize("per_cell", [3, 9, 17, 20, 21, 24, 29, 36, 60])
+def test_lists_by_slot_count(dev, kind, per_cell):
+    """Lists over stencils of 2 to 13 and more register slots (every slot count the build
+    has code for, and the unstaged one), with pairs at the cutoff to rounding and coincident
+    atoms, rows cut at half their length, and the compressed rows: against all pairs in
+    FP64; compressed rows equal to the tiled ones entry by entry."""
+    import torch
+    from helpers import decode_rows
+    from paper_2109_09056_amd import ops
+    rl = 2.8
+    L = np.full(3, 3 * rl * 1.01)
+    n = per_cell * 27
+    g = np.random.default_rng(per_cell)
+    x = g.uniform(0, 1, (n, 3)) * L
+    x[1] = x[0] + np.array([rl, 0.0, 0.0])  # at the cutoff, to rounding
+    x[2] = x[0] + np.array([0.0, rl * (1 - 1e-9), 0.0])
+    x[3] = x[0]  # coincident atoms are neighbours
+    x = np.mod(x, L)
+    k = ops.FULL if kind == "full" else ops.HALF
+    xs, _, _, ids, cs = ops.bin(L, rl, torch.as_tensor(x, device=dev))
+    X = xs.cpu().numpy()
+    d = X[:, None, :] - X[None, :, :]
+    d = np.where(d > L / 2, d - L, np.where(d < -L / 2, d + L, d))
+    r2 = (d[..., 0] * d[..., 0] + d[..., 1] * d[..., 1]) + d[..., 2] * d[..., 2]
+    hit = r2 < rl * rl
+    np.fill_diagonal(hit, False)
+    if kind == "half":
+        hit = np.triu(hit)
+    most = int(hit.sum(1).max())
+    for maxn in (most, max(1, most // 2), most + 200):
+        nbr, nnbr, mc = ops.build_neighbors(L, rl, k, xs, cs, maxn)
+        assert int(mc.item()) == most
+        rows = decode_rows(nbr.cpu().numpy(), nnbr.cpu().numpy(), maxn)
+        for i, row in enumerate(rows):
+            want = np.flatnonzero(hit[i])
+            assert row.size == min(want.size, maxn)
+            assert np.isin(row, want).all() and np.unique(row).size == row.size
+        if maxn >= most:
+            full = rows
+    off, csr = ops.build_neighbors_csr(L, rl, k, xs, cs)
+    off, csr = off.cpu().numpy(), csr.cpu().numpy()
+    assert off[-1] == hit.sum()
+    for i, row in enumerate(full):
+        assert np.array_equal(csr[off[i]:off[i + 1]], row)
+    # too small a capacity: the entries below it are the same
+    cap = int(off[-1]) // 2
+    off2, csr2 = ops.build_neighbors_csr(L, rl, k, xs, cs, cap=cap,
+                                         csr=torch.full((cap,), -7, dtype=torch.int32, device=dev))
+    assert np.array_equal(off2.cpu().numpy(), off)
+    assert np.array_equal(csr2.cpu().numpy(), csr[:cap])
