@@ -19,6 +19,7 @@
  *   ljmd_md_step_chained, ljmd_md_step_sums
  *                         the same step with its energy sums formed during the
  *                         next step's launch (one launch per step)
+ *   ljmd_md_steps         several chained steps issued by one call
  *   ljmd_md_step_noalloc  the fused step for callers that cannot allocate
  *   ljmd_max_displacement largest displacement since a list was built (the
  *                         dangerous-build check of a fixed rebuild cadence)
@@ -384,6 +385,29 @@ int ljmd_md_step_chained(const ljmd_box *box, int precision, double rc, int32_t 
                          const int32_t *nnbr, int32_t maxn, double dt, double mass, double *v,
                          double *x_next, int open_next, double *F, double *e_atom, int half,
                          double *ev_prev, void *ws, size_t ws_bytes, void *stream);
+
+/*
+ * ljmd_md_steps -- nsteps calls of ljmd_md_step_chained on one neighbor list, in one
+ * call: step s reads x (s even) or x_alt (s odd), writes the next step's positions to
+ * the other, and uses half (half + s) mod 2.  For small systems, whose steps take the
+ * GPU less time than a caller's loop takes to issue them.  Same launches, so the
+ * same results, bitwise.
+ *   nsteps     >= 1; after the call the newest positions are in x if nsteps is even
+ *              and open_last is set, or nsteps is odd and it is not; else in x_alt
+ *   open_last  1: every step opens the next one; 0: the last step only closes
+ *   chained    1: half (half + 1) mod 2 holds the rows of a previous chained step
+ *              (their sums go to ev first); 0: it is not read
+ *   ev         [8] the sums of the step before the last issued one (left alone when
+ *              nsteps = 1 and chained = 0); ljmd_md_step_sums gives the last one's
+ *   F, e_atom  of the last step, or NULL
+ * Other arguments as in ljmd_md_step_chained.
+ */
+int ljmd_md_steps(const ljmd_box *box, int precision, double rc, int32_t ntypes,
+                  const double *eps_packed, const double *sigma_packed, int64_t n, double *x,
+                  double *x_alt, const int32_t *type, const int32_t *nbr, const int32_t *nnbr,
+                  int32_t maxn, double dt, double mass, double *v, int32_t nsteps, int open_last,
+                  double *F, double *e_atom, int half, int chained, double *ev, void *ws,
+                  size_t ws_bytes, void *stream);
 
 /*
  * ljmd_md_step_sums -- ev [8] (E, W (6), kinetic energy) of the ljmd_md_step_chained

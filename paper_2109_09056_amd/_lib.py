@@ -61,6 +61,8 @@ SIGNATURES = {
                                     _i32, _dbl, _dbl, _p, _p, _int, _p, _p, _p, _p]),
     "ljmd_md_step_chained": (_int, [_box, _int, _dbl, _i32, _p, _p, _i64, _p, _p, _p, _p, _i32,
                                     _dbl, _dbl, _p, _p, _int, _p, _p, _int, _p, _p, _sz, _p]),
+    "ljmd_md_steps": (_int, [_box, _int, _dbl, _i32, _p, _p, _i64, _p, _p, _p, _p, _p, _i32,
+                             _dbl, _dbl, _p, _i32, _int, _p, _p, _int, _int, _p, _p, _sz, _p]),
     "ljmd_md_step_sums": (_int, [_i64, _int, _p, _sz, _p, _p]),
     "ljmd_list_to_csr": (_int, [_i64, _p, _p, _i32, _p, _p, _i64, _p, _sz, _p]),
     "ljmd_compute_forces_csr": (_int, [_box, _int, _dbl, _i32, _p, _p, _i64, _p, _p, _p, _p,

@@ -609,6 +609,36 @@ int ljmd_md_step_chained(const ljmd_box *box, int precision, double rc, int32_t 
                         (hipStream_t)stream);
 }
 
+int ljmd_md_steps(const ljmd_box *box, int precision, double rc, int32_t ntypes,
+                  const double *eps_packed, const double *sigma_packed, int64_t n, double *x,
+                  double *x_alt, const int32_t *type, const int32_t *nbr, const int32_t *nnbr,
+                  int32_t maxn, double dt, double mass, double *v, int32_t nsteps, int open_last,
+                  double *F, double *e_atom, int half, int chained, double *ev, void *ws,
+                  size_t ws_bytes, void *stream) {
+  LJMD_TRY(check_md_step(box, precision, rc, ntypes, eps_packed, sigma_packed, n, x, type, nbr,
+                         nnbr, maxn, dt, mass, v, x_alt, open_last));
+  if (nsteps < 1) return set_error(LJMD_EINVAL, "nsteps = %d must be >= 1", nsteps);
+  if (half != 0 && half != 1) return set_error(LJMD_EINVAL, "half = %d must be 0 or 1", half);
+  if (chained != 0 && chained != 1)
+    return set_error(LJMD_EINVAL, "chained = %d must be 0 or 1", chained);
+  if (n > 0 && (!x_alt || x_alt == x))
+    return set_error(LJMD_EINVAL, "x_alt is NULL or aliases x");
+  if (!ev) return set_error(LJMD_EINVAL, "ev is NULL");
+  LJMD_TRY(check_ws(ws, ws_bytes, 2 * force_workspace(n)));
+  double *rows[2] = {(double *)ws, (double *)ws + chain_half(n, ws_bytes)};
+  const int atoms = chain_atoms(n, ws_bytes);
+  const BoxK b = make_box(box);
+  for (int32_t s = 0; s < nsteps; ++s) {
+    const int h = (half + s) & 1;
+    const int open = s < nsteps - 1 ? 1 : open_last;
+    double *from = s & 1 ? x_alt : x, *to = s & 1 ? x : x_alt;
+    LJMD_TRY(launch_md_step(b, precision, rc, ntypes, eps_packed, sigma_packed, n, from, type, nbr,
+                            nnbr, maxn, dt, mass, v, to, open, F, e_atom, nullptr, rows[h], atoms,
+                            rows[1 - h], s > 0 || chained ? ev : nullptr, (hipStream_t)stream));
+  }
+  return LJMD_OK;
+}
+
 int ljmd_md_step_sums(int64_t n, int half, const void *ws, size_t ws_bytes, double *ev,
                       void *stream) {
   LJMD_TRY(check_n(n));

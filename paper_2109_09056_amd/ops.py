@@ -374,6 +374,39 @@ def md_step_chained(L, precision, rc, eps, sigma, x, types, nbr, nnbr, maxn, dt,
     return x_next
 
 
+def md_steps(L, precision, rc, eps, sigma, x, x_alt, types, nbr, nnbr, maxn, dt, mass, v, nsteps,
+             half, ws, ev, chained=False, open_last=True, F=None, e_atom=None):
+    """nsteps chained steps issued by one call, the positions going back and forth between
+    x and x_alt; half and ws as in md_step_chained (step s writes half (half + s) % 2),
+    chained: the other half holds a previous step's rows.  ev receives the sums of every
+    step but the last (md_step_sums).  Returns (positions, other buffer)."""
+    n = x.shape[0]
+    dev = x.device
+    ntypes = _ntypes(eps)
+    _need(x, "x", torch.float64, (n, 3))
+    _need(x_alt, "x_alt", torch.float64, (n, 3), dev)
+    _need(v, "v", torch.float64, (n, 3), dev)
+    _need(eps, "eps", torch.float64, None, dev)
+    _need(sigma, "sigma", torch.float64, tuple(eps.shape), dev)
+    _need(types, "types", torch.int32, (n,), dev)
+    _need(nbr, "nbr", torch.int32, None, dev)
+    _need(nnbr, "nnbr", torch.int32, (n,), dev)
+    if nbr.numel() < list_shape(n, maxn)[0]:
+        raise ValueError("nbr is smaller than the tiled list of n rows x maxn")
+    _need(F, "F", torch.float64, (n, 3), dev)
+    _need(e_atom, "e_atom", torch.float64, (n,), dev)
+    _need(ev, "ev", torch.float64, (8,), dev)
+    need = _chain_ws(n, ws, dev)
+    b = make_box(L)
+    _lib.check(_lib.load().ljmd_md_steps(
+        ctypes.byref(b), int(precision), float(rc), ntypes, _ptr(eps), _ptr(sigma), n, _ptr(x),
+        _ptr(x_alt), _ptr(types), _ptr(nbr), _ptr(nnbr), int(maxn), float(dt), float(mass), _ptr(v),
+        int(nsteps), 1 if open_last else 0, _ptr(F), _ptr(e_atom), int(half), 1 if chained else 0,
+        _ptr(ev), _ptr(ws), need, _stream(dev)), "ljmd_md_steps")
+    moved = nsteps if open_last else nsteps - 1
+    return (x_alt, x) if moved % 2 else (x, x_alt)
+
+
 def md_step_sums(n, half, ws, ev=None):
     """ev[8] (E, W, KE) of the md_step_chained call that wrote half `half` of ws."""
     dev = ws.device

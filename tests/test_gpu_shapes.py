@@ -297,3 +297,44 @@ def test_lists_by_slot_count(dev, kind, per_cell):
                                          csr=torch.full((cap,), -7, dtype=torch.int32, device=dev))
     assert np.array_equal(off2.cpu().numpy(), off)
     assert np.array_equal(csr2.cpu().numpy(), csr[:cap])
+
+
+@pytest.mark.parametrize("nsteps", [1, 2, 3, 6])
+@pytest.mark.parametrize("open_last", [True, False])
+def test_md_steps_match_single_calls(dev, nsteps, open_last):
+    """One call of several chained steps gives bitwise the positions, velocities, forces and
+    sums of as many single ones, started fresh and after a chained step, and leaves the
+    newest positions where it says."""
+    import torch
+    from paper_2109_09056_amd import md, ops
+    L = np.array([11.0, 12.0, 13.0])
+    n = 700
+    x, ty = _gas(n, L, 77)
+    T = lambda a, d=torch.float64: torch.as_tensor(a, dtype=d, device=dev).contiguous()
+    xs, _, ts, _, cs = ops.bin(L, 2.8, T(x), None, T(ty, torch.int32))
+    nl = md.NeighborList(L, 2.8, ops.FULL, device=dev).build(xs, cs)
+    one = T([1.0])
+    v0 = T(np.random.default_rng(1).normal(size=(n, 3)))
+    a = lambda xx: (L, ops.MIXED, 2.5, one, one, xx)
+    b = (ts, nl.nbr, nl.nnbr, nl.maxn, 0.005, 1.0)
+    nb = ops.workspace_bytes(ops.OP_MD_CHAIN, n)
+    out = []
+    for native in (False, True):
+        cur, alt, v, F = xs.clone(), torch.empty_like(xs), v0.clone(), torch.empty_like(xs)
+        ws, ev = torch.empty(nb, dtype=torch.uint8, device=dev), T(np.zeros(8))
+        ops.md_step_chained(*a(cur), *b, v, 1, ws, x_next=alt)  # half 1
+        cur, alt = alt, cur
+        if native:
+            cur, alt = ops.md_steps(*a(cur), alt, *b, v, nsteps, 0, ws, ev, chained=True,
+                                    open_last=open_last, F=F)
+        else:
+            for s in range(nsteps):
+                op = open_last or s < nsteps - 1
+                ops.md_step_chained(*a(cur), *b, v, s % 2, ws, x_next=alt, open_next=op, F=F,
+                                    ev_prev=ev)
+                if op:
+                    cur, alt = alt, cur
+        out.append((cur, v, F, ev, ops.md_step_sums(n, (nsteps - 1) % 2, ws)))
+    assert all(torch.equal(p, q) for p, q in zip(*out))
+    with pytest.raises(Exception):
+        ops.md_steps(*a(xs), xs, *b, v0, 1, 0, ws, ev)  # aliased buffers
