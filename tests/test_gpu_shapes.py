@@ -338,3 +338,25 @@ def test_md_steps_match_single_calls(dev, nsteps, open_last):
     assert all(torch.equal(p, q) for p, q in zip(*out))
     with pytest.raises(Exception):
         ops.md_steps(*a(xs), xs, *b, v0, 1, 0, ws, ev)  # aliased buffers
+
+
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 1023, 1024, 1025, 3000])
+@pytest.mark.parametrize("maxn", [1, 15, 16, 17, 33])
+def test_list_to_csr_shapes(dev, n, maxn):
+    """Tiled rows of every length (also counted past their capacity) to compressed ones,
+    whole and with half the room: equal entry by entry, nothing written past the room."""
+    import torch
+    from paper_2109_09056_amd import ops
+    g = np.random.default_rng(n + 1000 * maxn)
+    nbr = g.integers(0, n, ((n + 63) // 64, maxn, 64)).astype(np.int32)
+    nnbr = g.integers(0, maxn + 4, n).astype(np.int32)
+    c = np.minimum(nnbr, maxn)
+    off = np.concatenate([[0], np.cumsum(c)])
+    rows = np.concatenate([nbr[i // 64, :c[i], i % 64] for i in range(n)])
+    for cap in (rows.size, rows.size // 2):
+        out = torch.full((rows.size + 8,), -7, dtype=torch.int32, device=dev)
+        o, _ = ops.list_to_csr(torch.as_tensor(nbr, device=dev).reshape(-1),
+                               torch.as_tensor(nnbr, device=dev), maxn, cap=cap, csr=out)
+        assert np.array_equal(o.cpu().numpy(), off)
+        got = out.cpu().numpy()
+        assert np.array_equal(got[:cap], rows[:cap]) and (got[cap:] == -7).all()
