@@ -481,7 +481,8 @@ __global__ void k_zero2_f64(double *p, int64_t m, double *r, int64_t k) {
 // another wave has claimed but not yet published) adds its j-side through
 // direct global atomics.  Summation order is not fixed: HALF results are
 // reproducible to rounding, not bitwise.
-constexpr int kHalfTeam = 2;  // lanes per home atom (large grids)
+constexpr int kHalfTeam = 4;      // lanes per home atom
+constexpr int kHalfTinyTeam = 8;  // grids of at most one block per compute unit
 constexpr int kHalfTabBits = 7;
 constexpr int kHalfTab = 1 << kHalfTabBits;  // table entries
 
@@ -529,7 +530,7 @@ struct HalfAcc {
 template <bool MIXED, bool T1, bool EV, bool EATOM, bool WRAP, int NV, int SLOTS>
 __device__ __forceinline__ void half_pair(const ForceArgs &a, HalfLds<NV, SLOTS> &s,
                                           double xi, double yi, double zi, double xj, double yj,
-                                          double zj, int32_t j, bool valid, int ti,
+                                          double zj, int32_t j, int32_t tj, bool valid, int ti,
                                           const Coef &c1, const double *tab, HalfAcc &r,
                                           int32_t &ltile, int32_t &lslot) {
   double dx = xi - xj, dy = yi - yj, dz = zi - zj;
@@ -544,7 +545,7 @@ __device__ __forceinline__ void half_pair(const ForceArgs &a, HalfLds<NV, SLOTS>
     if constexpr (T1) {
       c = c1;
     } else {
-      const double *t = tab + 4 * (ti * a.ntypes + a.type[j]);
+      const double *t = tab + 4 * (ti * a.ntypes + tj);
       c = Coef{t[0], t[1], t[2], t[3]};
     }
     const PairOut p = lj_pair<MIXED, EV || EATOM>(dx, dy, dz, r2, c);
@@ -590,26 +591,24 @@ __device__ __forceinline__ void half_row(const ForceArgs &a, HalfLds<NV, SLOTS> 
                                          HalfAcc &r) {
   constexpr int kStep = TEAM * kWave;
   int32_t ltile = -1, lslot = -1;
+#pragma unroll 1
   for (int32_t k = 0; k < cnt; k += U, row += U * kStep) {
-    int32_t j[U];
+    int32_t j[U], tj[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) j[u] = row[(k + u < cnt ? u : 0) * kStep];
     double xj[U], yj[U], zj[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      xj[u] = xi;
-      yj[u] = yi;
-      zj[u] = zi;
-      if (k + u < cnt) {
-        const double *q = pos_of<WIDE>(a.x, j[u]);
-        xj[u] = q[0];
-        yj[u] = q[1];
-        zj[u] = q[2];
+      if (TEAM < kHalfTinyTeam || k + u < cnt) {
+        load_pos<1, WIDE>(a.x, j[u], a.n, xj[u], yj[u], zj[u]);
+        tj[u] = T1 ? 0 : a.type[j[u]];
+      } else {
+        xj[u] = xi, yj[u] = yi, zj[u] = zi, tj[u] = 0;
       }
     }
 #pragma unroll
     for (int u = 0; u < U; ++u)
-      half_pair<MIXED, T1, EV, EATOM, WRAP>(a, s, xi, yi, zi, xj[u], yj[u], zj[u], j[u],
+      half_pair<MIXED, T1, EV, EATOM, WRAP>(a, s, xi, yi, zi, xj[u], yj[u], zj[u], j[u], tj[u],
                                             k + u < cnt, ti, c1, tab, r, ltile, lslot);
   }
 }
@@ -825,52 +824,41 @@ constexpr int kCsrTeamUnroll = 4;
 // 83.4.
 constexpr int64_t kSmallBlockAtoms = 114688;
 
-// Half-list blocks: 256 home atoms with two lanes each (512 threads), 32 tile
-// slots, 4 entries per group.  Up to kHalfSmallAtoms atoms: blocks of 128 home
-// atoms with four lanes each (more blocks and more waves for grids that do not
-// fill the chip); up to LJMD_SMALL_GRID_ATOMS atoms (one block per compute
-// unit): eight lanes each and 48 slots.  Measured with per-atom energies and
-// virial (us): 32,000 atoms 38.0 (128 x 2) -> 28.0 (128 x 4) -> 23.2 (128 x 8,
-// 48 slots); 108,000 atoms 77.5 -> 61.7 (128 x 4; 256 x 2: 64.9); 256,000
-// atoms 153.4 -> 127.9 (256 x 2: 141.0); 500,000 atoms 256 x 2 234.2, 128 x 4
-// 236.3, 128 x 8 373.
-constexpr int kHalfAtoms = 256;
-constexpr int kHalfSmallBlock = 128;
-constexpr int64_t kHalfSmallAtoms = 262144;
+// Half-list blocks: 128 home atoms with four lanes each and 32 tile slots; up to
+// LJMD_SMALL_GRID_ATOMS atoms (one block per compute unit) eight lanes each and 48
+// slots, where rows of four or five entries per lane make the gathers of absent
+// entries worth leaving out (with energies, 32,000 atoms: 24.2 us without them, 26.8
+// with).  Groups of 6 entries with the energies and of 5 without; whole loops of
+// masked groups, not unrolled.  Against two lanes, 256 atoms, types read after the
+// distance test (us, with per-atom energies / forces only): 110,447 atoms 66.5 / 49.3
+// -> 54.0 / 40.7, 256,000 128 / 92.8 -> 98.7 / 74.5, 500,000 232 / 170 -> 177 / 131.
+// Forces only in groups of 4 / 5 / 6 at 500,000: 137 / 131 / 144.
+constexpr int kHalfAtoms = 128;
 constexpr int kHalfSlots = 32;
-constexpr int kHalfUnroll = 4;
-constexpr int kHalfSmallTeam = 4;
-constexpr int kHalfTinyTeam = 8;
+constexpr int kHalfUnroll = 5;
+constexpr int kHalfUnrollEv = 6;
 constexpr int kHalfTinySlots = 48;
+constexpr int kHalfTinyUnroll = 4;
+static_assert(kHalfAtoms == kForceAtoms, "one row of partial sums per block");
 
-int half_block_atoms(int64_t n) { return n <= kHalfSmallAtoms ? kHalfSmallBlock : kHalfAtoms; }
-
-unsigned half_blocks(int64_t n) {
-  const int64_t per = half_block_atoms(n);
+unsigned blocks_of(int64_t n, int per) {
   const int64_t b = (n + per - 1) / per;
   return (unsigned)(b > 0 ? b : 1);
 }
 
 template <bool MIXED, bool T1, bool EV, bool EATOM>
 void launch_half(const ForceArgs &a, hipStream_t st) {
-  const unsigned nb = half_blocks(a.n);
+  constexpr int U = EV || EATOM ? kHalfUnrollEv : kHalfUnroll;
+  const unsigned nb = blocks_of(a.n, kHalfAtoms);
   if (a.n <= LJMD_SMALL_GRID_ATOMS)
-    k_force_half<MIXED, T1, EV, EATOM, false, kHalfSmallBlock, kHalfTinySlots, kHalfUnroll,
-                 kHalfTinyTeam><<<nb, kHalfSmallBlock * kHalfTinyTeam, 0, st>>>(a);
-  else if (a.n <= kHalfSmallAtoms)
-    k_force_half<MIXED, T1, EV, EATOM, false, kHalfSmallBlock, kHalfSlots, kHalfUnroll,
-                 kHalfSmallTeam><<<nb, kHalfSmallBlock * kHalfSmallTeam, 0, st>>>(a);
+    k_force_half<MIXED, T1, EV, EATOM, false, kHalfAtoms, kHalfTinySlots, kHalfTinyUnroll,
+                 kHalfTinyTeam><<<nb, kHalfAtoms * kHalfTinyTeam, 0, st>>>(a);
   else if (a.n <= kNarrowAtoms)
-    k_force_half<MIXED, T1, EV, EATOM, false, kHalfAtoms, kHalfSlots, kHalfUnroll>
+    k_force_half<MIXED, T1, EV, EATOM, false, kHalfAtoms, kHalfSlots, U>
         <<<nb, kHalfAtoms * kHalfTeam, 0, st>>>(a);
   else
-    k_force_half<MIXED, T1, EV, EATOM, true, kHalfAtoms, kHalfSlots, kHalfUnroll>
+    k_force_half<MIXED, T1, EV, EATOM, true, kHalfAtoms, kHalfSlots, U>
         <<<nb, kHalfAtoms * kHalfTeam, 0, st>>>(a);
-}
-
-unsigned blocks_of(int64_t n, int per) {
-  const int64_t b = (n + per - 1) / per;
-  return (unsigned)(b > 0 ? b : 1);
 }
 
 // The full-list kernel in blocks of `atoms` (64 or 128) atoms.
@@ -973,7 +961,7 @@ int launch_forces(const BoxK &b, int precision, int kind, double rc, int32_t nty
   } else if (ev) {
     k_zero_f64<<<1, 256, 0, st>>>(a.partial, kEvStride);
   }
-  const unsigned rows = n == 0 ? 1 : (kind == LJMD_HALF ? half_blocks(n) : force_blocks(n));
+  const unsigned rows = n == 0 ? 1 : force_blocks(n);
   if (ev) k_colsum<1024><<<1, 1024, 0, st>>>(rows, kEvStride, 7, a.partial, ev, 1.0, 0);
   return check_launch("ljmd_compute_forces");
 }

@@ -360,3 +360,37 @@ def test_list_to_csr_shapes(dev, n, maxn):
         assert np.array_equal(o.cpu().numpy(), off)
         got = out.cpu().numpy()
         assert np.array_equal(got[:cap], rows[:cap]) and (got[cap:] == -7).all()
+
+
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+@pytest.mark.parametrize("ntypes", [1, 2])
+@pytest.mark.parametrize("n", [1, 127, 129, 3001, 32768, 32769, 33001])
+def test_half_list_block_shapes(dev, n, ntypes, prec):
+    """Half-list forces, per-atom energies and sums against the full list's over block and
+    group remainders and both sides of the small-grid line.  The two add the same pairs in
+    other orders in FP64 (a mixed pair is the same number in both): each side is within (row
+    length) rounding errors of a sum of terms whose magnitudes stay under the bound below."""
+    import torch
+    from paper_2109_09056_amd import md, ops
+    L = np.full(3, max(1.1 * n ** (1.0 / 3.0), 8.5))
+    x, types = _gas(n, L[0], n, ntypes)
+    eps = np.array([1.0, 0.8, 1.3])[: ntypes * (ntypes + 1) // 2]
+    sig = np.array([1.0, 0.95, 0.9])[: ntypes * (ntypes + 1) // 2]
+    T = lambda a, d=torch.float64: torch.as_tensor(a, dtype=d, device=dev).contiguous()
+    xs, _, ts, _, cs = ops.bin(L, 2.8, T(x), None, T(types, torch.int32))
+    P = ops.FP64 if prec == "fp64" else ops.MIXED
+    out = []
+    for kind in (ops.FULL, ops.HALF):
+        nl = md.NeighborList(L, 2.8, kind, device=dev).build(xs, cs)
+        for energy in (True, False):
+            out.append(ops.compute_forces(L, P, kind, 2.5, T(eps), T(sig), xs, ts, nl.nbr,
+                                          nl.nnbr, nl.maxn, want_energy=energy))
+    (F, e, ev), _, (Fh, eh, evh), (Fh0, _, _) = [
+        tuple(t.cpu().numpy() if t is not None else None for t in o) for o in out]
+    unit = 2.0 ** -52
+    # 48 eps sigma^-1 (sigma/r)^13 at the closest 0.8 or more; fewer than 200 neighbours
+    big = 48 * 1.3 * (1 / 0.8) ** 13 * 1.1
+    assert np.abs(Fh - F).max() <= 200 * unit * big
+    assert np.abs(Fh0 - F).max() <= 200 * unit * big
+    assert np.abs(eh - e).max() <= 200 * unit * big
+    assert np.abs(evh - ev).max() <= 200 * unit * big * max(n, 1)
