@@ -394,3 +394,21 @@ def test_half_list_block_shapes(dev, n, ntypes, prec):
     assert np.abs(Fh0 - F).max() <= 200 * unit * big
     assert np.abs(eh - e).max() <= 200 * unit * big
     assert np.abs(evh - ev).max() <= 200 * unit * big * max(n, 1)
+
+
+@pytest.mark.parametrize("cells", [(3, 3, 3), (16, 16, 15), (16, 16, 16), (17, 16, 16),
+                                   (32, 16, 16), (29, 29, 29)])
+def test_bin_starts_over_scan_chunks(dev, cells):
+    """Row starts of grids below, at and above one and several scan chunks."""
+    import torch
+    from paper_2109_09056_amd import ops
+    L = 2.8 * 1.001 * np.array(cells, float)
+    x = np.random.default_rng(cells[0]).uniform(0, 1, (5000, 3)) * L
+    _, _, _, ids, cs = ops.bin(L, 2.8, torch.as_tensor(x, device=dev))
+    assert tuple(ops.grid(L, 2.8)) == cells
+    c = np.minimum(np.floor(x / (L / cells)).astype(int), np.array(cells) - 1)
+    cell = (c[:, 2] * cells[1] + c[:, 1]) * cells[0] + c[:, 0]
+    want = np.lexsort((np.arange(5000), cell))
+    assert np.array_equal(ids.cpu().numpy(), want)
+    assert np.array_equal(cs.cpu().numpy(),
+                          np.searchsorted(cell[want], np.arange(np.prod(cells) + 1)))
