@@ -200,7 +200,10 @@ int ljmd_build_neighbors(const ljmd_box *box, double rlist, int kind, int64_t n,
  *   nbr      int32 [cap] output; entries at positions >= cap are not written,
  *            so a too-small cap is seen as offsets[n] > cap once the call
  *            completes (the caller builds again with cap >= offsets[n])
- *   ws       >= ljmd_workspace_bytes(LJMD_OP_BUILD_CSR, n, 0, 0)
+ *   ws       >= ljmd_workspace_bytes(LJMD_OP_BUILD_CSR, n, 0, 0), for one test of
+ *            every candidate; with less, down to 4 n bytes rounded up to 256 plus
+ *            ljmd_workspace_bytes(LJMD_OP_CSR, n, 0, 0), the candidates are tested in
+ *            both passes (the same rows)
  * Other arguments and errors as in ljmd_build_neighbors.
  */
 int ljmd_build_neighbors_csr(const ljmd_box *box, double rlist, int kind, int64_t n,

@@ -16,9 +16,10 @@ int launch_bin(const GridK &g, int64_t n, const double *x_in, const double *v_in
                const int32_t *type_in, const int64_t *id_in, double *x_out, double *v_out,
                int32_t *type_out, int64_t *id_out, int32_t *cell_start, void *ws, hipStream_t st);
 size_t build_csr_workspace(int64_t n);
+size_t build_csr_min_workspace(int64_t n);
 int launch_build_csr(const GridK &g, const BoxK &b, double rlist, int kind, int64_t n,
                      const double *x, const int32_t *cell_start, int64_t *offsets, int32_t *csr,
-                     int64_t cap, void *ws, hipStream_t st);
+                     int64_t cap, void *ws, size_t ws_bytes, hipStream_t st);
 int launch_build(const GridK &g, const BoxK &b, double rlist, int kind, int64_t n, const double *x,
                  const int32_t *cell_start, int32_t maxn, int32_t *nbr, int32_t *nnbr,
                  int32_t *max_count, hipStream_t st);
@@ -336,11 +337,11 @@ int ljmd_build_neighbors_csr(const ljmd_box *box, double rlist, int kind, int64_
   if (!cell_start || !offsets) return set_error(LJMD_EINVAL, "cell_start/offsets is NULL");
   if (cap < 0) return set_error(LJMD_EINVAL, "cap = %lld must be >= 0", (long long)cap);
   if (n > 0 && (!x || (cap > 0 && !nbr))) return set_error(LJMD_EINVAL, "x/nbr is NULL");
-  LJMD_TRY(check_ws(ws, ws_bytes, build_csr_workspace(n)));
+  LJMD_TRY(check_ws(ws, ws_bytes, build_csr_min_workspace(n)));
   GridK g;
   LJMD_TRY(make_grid(box, rlist, &g));
   return launch_build_csr(g, make_box(box), rlist, kind, n, x, cell_start, offsets, nbr, cap, ws,
-                          (hipStream_t)stream);
+                          ws_bytes, (hipStream_t)stream);
 }
 
 int ljmd_compute_forces(const ljmd_box *box, int precision, int kind, double rc,

@@ -412,3 +412,41 @@ def test_bin_starts_over_scan_chunks(dev, cells):
     assert np.array_equal(ids.cpu().numpy(), want)
     assert np.array_equal(cs.cpu().numpy(),
                           np.searchsorted(cell[want], np.arange(np.prod(cells) + 1)))
+
+
+@pytest.mark.parametrize("kind", ["full", "half"])
+@pytest.mark.parametrize("per_cell", [1, 9, 17, 24, 29, 45])
+@pytest.mark.parametrize("nc", [2, 3, 4])
+def test_compressed_rows_with_and_without_hits(dev, kind, per_cell, nc):
+    """Compressed rows with the full workspace (the filling pass reads the counting pass's
+    hits) and with the smallest (it tests again): equal, also where cap cuts them; atoms
+    outside the box and empty cells too (stencils that the integer test does not take)."""
+    import torch
+    from paper_2109_09056_amd import _lib, ops
+    rl, k = 2.8, ops.FULL if kind == "full" else ops.HALF
+    L = np.full(3, nc * rl * 1.01)
+    n = per_cell * nc ** 3
+    x = np.random.default_rng(per_cell).uniform(0, 1, (n, 3)) * L
+    for outside in (False, True):
+        xs, _, _, _, cs = ops.bin(L, rl, torch.as_tensor(x, device=dev))
+        if outside:
+            xs[n // 2] += torch.as_tensor(1.5 * L, device=dev)
+        small = -(-4 * n // 256) * 256 + ops.workspace_bytes(ops.OP_CSR, n)
+        full = ops.workspace_bytes(ops.OP_BUILD_CSR, n)
+        assert small < full
+        got = []
+        for nbytes in (full, small):
+            for part in (1, 2):
+                off = torch.empty(n + 1, dtype=torch.int64, device=dev)
+                csr = torch.full((n * n // part + 1,), -7, dtype=torch.int32, device=dev)
+                cap = csr.numel() if part == 1 else int(got[0][0][-1]) // 2
+                ws = torch.empty(nbytes, dtype=torch.uint8, device=dev)
+                _lib.check(_lib.load().ljmd_build_neighbors_csr(
+                    _lib.make_box(L), rl, k, n, xs.data_ptr(), cs.data_ptr(), off.data_ptr(),
+                    csr.data_ptr(), cap, ws.data_ptr(), nbytes,
+                    torch.cuda.current_stream(dev).cuda_stream), "build")
+                got.append((off.cpu().numpy(), csr.cpu().numpy(), cap))
+        for off, csr, cap in got:
+            assert np.array_equal(off, got[0][0])
+            m = min(cap, off[-1])
+            assert np.array_equal(csr[:m], got[2][1][:m]) and (csr[m:] == -7).all()
