@@ -26,12 +26,20 @@ namespace {
 
 // Two shapes of the build kernel.  Standard: 12 register slots (up to 768
 // candidates staged) and rows of up to 128 entries buffered in LDS.  Dense
-// (chosen when maxn > 128, i.e. long rows and so crowded stencils): 16 slots
-// (1024 candidates) and rows of up to 256 entries, at twice the LDS.
+// (chosen when maxn > 128, i.e. long rows and so crowded stencils, or when the mean
+// stencil has more than 11 slots' candidates): 16 slots (1024 candidates) and rows of up
+// to 256 entries, at twice the LDS.
+// Stencils beyond the slots read every candidate from memory for every home atom.  Small
+// boxes reach that at liquid densities, as their cells are up to 4/3 of the cutoff wide:
+// tiled lists (us), standard -> dense, 864 atoms (27 cells) 59.0 -> 16.7, 2,048 59.3 ->
+// 17.1, 4,000 69.6 -> 18.4, 13,500 (mean stencil of 11.1 slots, some cells above 12)
+// 65.8 -> 21.0; where the standard shape holds all, the dense one costs 20 %
+// (110,447 atoms 56.1 -> 68.5).
 constexpr int kSlots = 12;
 constexpr int kRowCap = 128;
 constexpr int kDenseSlots = 16;
 constexpr int kDenseRowCap = 256;
+constexpr int64_t kStandardCandidates = (kSlots - 1) * kWave;
 // Home atoms whose rows are buffered in LDS at once.  8 rather than 16 halves
 // the one-wavefront block's LDS, so more blocks fit on a compute unit: at 500,000
 // atoms 189.4 -> 171.2 us (full list), 159.3 -> 143.6 (half), 362.6 -> 261.3 (dense
@@ -536,7 +544,8 @@ __device__ __forceinline__ bool build_quant(const BoxK &b, const QuantK &q, cons
 
 // Compressed rows from the hits that the counting pass noted: no positions, no tests.
 // Count, scan and fill together (us), testing twice -> this: 32,000 atoms 55.7 -> 46.3,
-// 131,072 99.2 -> 86.3, 500,000 282 -> 229.  With a capacity test at every store instead
+// 131,072 99.2 -> 86.3, 500,000 282 -> 229 (4,000, whose stencils take the dense
+// shape, 125 -> 28.5).  With a capacity test at every store instead
 // of ROOM 91.7 and 248.
 // ROOM: all rows of the block end within cap.
 template <int NS, bool ROOM, int SLOTS>
@@ -775,11 +784,12 @@ void launch_shape(const GridK &g, const BoxK &b, double rl2, const double *x,
 }
 
 template <int MODE>
-void launch_mode(const GridK &g, const BoxK &b, double rl2, bool half, const double *x,
+void launch_mode(const GridK &g, const BoxK &b, double rl2, bool half, int64_t n, const double *x,
                  const int32_t *cell_start, const BuildOut &o, int32_t *max_count,
                  hipStream_t st) {
   const int ns = build_split(g.ncells);
-  if (MODE != kTiled || o.maxn <= kRowCap) {
+  const bool few = 27 * n <= (int64_t)g.ncells * kStandardCandidates;
+  if (few && (MODE != kTiled || o.maxn <= kRowCap)) {
     if (half)
       launch_shape<true, kSlots, kRowCap, MODE>(g, b, rl2, x, cell_start, o, max_count, ns, st);
     else
@@ -831,14 +841,14 @@ int launch_build_csr(const GridK &g, const BoxK &b, double rlist, int kind, int6
   o.maxn = 1;
   if (ws_bytes >= build_csr_workspace(n))
     o.hits = (uint16_t *)((char *)ws + align256(build_csr_min_workspace(n)));
-  if (n > 0) launch_mode<kCount>(g, b, rl2, half, x, cell_start, o, nullptr, st);
+  if (n > 0) launch_mode<kCount>(g, b, rl2, half, n, x, cell_start, o, nullptr, st);
   const int rc = launch_offsets(n, counts, offsets, scan_ws, st);
   if (rc != LJMD_OK) return rc;
   if (n > 0) {
     o.offsets = offsets;
     o.csr = csr;
     o.cap = cap;
-    launch_mode<kCsr>(g, b, rl2, half, x, cell_start, o, nullptr, st);
+    launch_mode<kCsr>(g, b, rl2, half, n, x, cell_start, o, nullptr, st);
   }
   return check_launch("ljmd_build_neighbors_csr");
 }
@@ -852,7 +862,7 @@ int launch_build(const GridK &g, const BoxK &b, double rlist, int kind, int64_t 
     o.nbr = nbr;
     o.nnbr = nnbr;
     o.maxn = maxn;
-    launch_mode<kTiled>(g, b, rlist * rlist, kind == LJMD_HALF, x, cell_start, o, max_count, st);
+    launch_mode<kTiled>(g, b, rlist * rlist, kind == LJMD_HALF, n, x, cell_start, o, max_count, st);
   }
   return check_launch("ljmd_build_neighbors");
 }
