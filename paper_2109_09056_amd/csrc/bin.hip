@@ -54,17 +54,6 @@ __global__ void k_count(int64_t n, const double *__restrict__ x, GridK g,
   }
 }
 
-// Inclusive prefix sum of v over the lanes of the wavefront (shuffles only).
-__device__ __forceinline__ int32_t wave_inclusive_scan(int32_t v) {
-  const int lane = threadIdx.x & (kWave - 1);
-#pragma unroll
-  for (int off = 1; off < kWave; off <<= 1) {
-    const int32_t o = __shfl_up(v, off, kWave);
-    if (lane >= off) v += o;
-  }
-  return v;
-}
-
 // Exclusive scan of counts[0..m) into start[0..m] (start[m] = total), one launch, no
 // flags between blocks: every block sums the counts before its chunk of kScanChunk by
 // itself (coalesced, before the one barrier) and scans its own, four consecutive counts

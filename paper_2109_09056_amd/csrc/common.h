@@ -241,6 +241,17 @@ __global__ __launch_bounds__(THREADS) void k_colsum(int64_t rows, int stride, in
   if (t < ncols) out[t] = accumulate ? out[t] + scale * part[t] : scale * part[t];
 }
 
+// Inclusive prefix sum of v over the lanes of the wavefront (shuffles only).
+__device__ __forceinline__ int32_t wave_inclusive_scan(int32_t v) {
+  const int lane = threadIdx.x & (kWave - 1);
+#pragma unroll
+  for (int off = 1; off < kWave; off <<= 1) {
+    const int32_t o = __shfl_up(v, off, kWave);
+    if (lane >= off) v += o;
+  }
+  return v;
+}
+
 // One counting step of a counting sort for the lanes of a wavefront: counts[c] grows by
 // the number of live lanes with key c, and every live lane gets its rank among all
 // elements of its key counted so far.  Lanes with the same key (the common case: the

@@ -450,3 +450,9 @@ def test_compressed_rows_with_and_without_hits(dev, kind, per_cell, nc):
             assert np.array_equal(off, got[0][0])
             m = min(cap, off[-1])
             assert np.array_equal(csr[:m], got[2][1][:m]) and (csr[m:] == -7).all()
+
+
+@pytest.mark.parametrize("K", [(256, 256, 128), (256, 256, 256)])
+def test_spme_tiles_of_large_grids(dev, K):
+    """4,096 tiles (ordered in one launch) and 8,192 (scanned first)."""
+    test_spme_tiles_against_direct_spreading(dev, 4, K, 3000)
