@@ -318,7 +318,7 @@ def rebuild_time(sim, reps=20):
 
 def traversal_study(w, sim, reps=50):
     """Forces + energy/virial of the 500k workload (mixed) over the same pairs: the dense
-    tiled list walked by two lanes per atom (the production kernel) against its CSR copy
+    tiled list walked by four lanes per atom (the production kernel) against its CSR copy
     walked by 1, 2, 4, 8 and 16 lanes per atom, positions in AoSoA layouts (SoA, 8, 64),
     and the half list; plus the tiled -> CSR conversion."""
     import torch
@@ -675,8 +675,8 @@ def main():
                    "natoms": n, "precision": "mixed", "list": "full",
                    "mean_list_length": round(nbar, 3), "maxn": sim.nl.maxn},
         "roofline": {"bound": "hbm",
-                     "kernel": "k_force_full<mixed, step, team 2> fused force+integration "
-                               "(block 0 also sums the previous step's energy/virial/KE rows)",
+                     "kernel": "k_force_full<mixed, step, team 4> fused force+integration "
+                               "(one more block sums the previous step's energy/virial/KE rows)",
                      "achieved": round(achieved, 2), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(achieved / HBM_PEAK_GBS, 4),
                      "traffic": round(FORCE_TRAFFIC) if FORCE_TRAFFIC else None,
