@@ -27,16 +27,16 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
-# Counter figures of the fused step kernel k_force_full<mixed, one type, EV, 6, interior,
-# step, narrow, team 2, [n][3]> on the 500,000-atom workload, from the rocprofv3 summaries
+# Counter figures of the fused step kernel k_force_full<mixed, one type, EV, step,
+# narrow, 128 atoms, team 4, [n][3]> on the 500,000-atom workload, from the rocprofv3 summaries
 # committed in profiles/ (k_force_full_step_lj500k_hbm_counters.txt, ..._pipeline_counters.txt):
 # HBM bytes per dispatch = FETCH_SIZE x 2 + WRITE_SIZE x 1 (the scales a 512 MiB copy
 # gives the two counters); set to None whenever the kernel changes until re-measured.
 FORCE_COUNTERS_FROM = ("profiles/k_force_full_step_lj500k_hbm_counters.txt and "
                        "..._pipeline_counters.txt (rocprofv3 --pmc on this kernel build)")
-FORCE_TRAFFIC = 234.56e6
-FORCE_VALU_BUSY = 0.540
-FORCE_TA_BUSY = 0.766
+FORCE_TRAFFIC = 243.56e6
+FORCE_VALU_BUSY = 0.658
+FORCE_TA_BUSY = 0.793
 
 
 def log(msg):
