@@ -331,7 +331,8 @@ __global__ __launch_bounds__(kThreads) void k_bmod(RecArgs a, double *z, int64_t
 // The grid is cut into tiles; a particle belongs to the tile of its base point
 // floor(u).  Its support reaches N - 1 points below the base in every dimension, so a
 // tile's particles touch a box of E = T + N - 1 points per dimension.  Particles are
-// sorted by tile (count, scan, scatter of their indices); one block per tile then
+// sorted by tile (count, then scan and scatter of their indices, one launch for up to
+// 4,096 tiles); one block per tile then
 // adds its particles' weights into the box in LDS and writes the box out, and the
 // x pass adds up the (one to eight) boxes that cover each point as it reads its rows:
 // no atomics on the grid, no clearing of it, and the same cost in whatever order the
