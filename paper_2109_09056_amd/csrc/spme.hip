@@ -18,8 +18,8 @@
 //   self:        E_self = -alpha/sqrt(pi) sum_i q_i^2
 //
 // Kernels: the real-space pair loop walks the tiled full list with four lanes
-// per particle over packed (x, y, z, q) records (the LJ traversal), the force's
-// kernel erfc(x) + 2/sqrt(pi) x e^{-x^2} taken from a table of polynomials;
+// per particle over packed (x, y, z, q) records (the LJ traversal), erfc(x) and e^{-x^2}
+// from polynomials (two forms, by alpha rc and by whether energies are wanted);
 // charge is spread into boxes of grid tiles in LDS, which the x pass adds up as it
 // reads its rows (or onto the grid by FP64 atomics); the 3-D transform is real-to-complex: the x pass turns each row of
 // K0 reals into K0/2 + 1 coefficients through one complex FFT of length K0/2
@@ -48,28 +48,42 @@ constexpr int kGatherTeam = 2;     // lanes per particle
 constexpr int kEwAtoms = 128;  // real space: particles per block
 constexpr int kEwTeam = 4;      // lanes per particle
 constexpr int kEwThreads = kEwAtoms * kEwTeam;
-// Slots per group and lane: 2 without energies (63 VGPRs, 8 wavefronts per SIMD), 3
-// with (the second table's LDS limits residency first).  500,000 / 32,000 particles,
-// no energies (us): two lanes with 6 slots 107.6 / 15.8, with 4 and at most 80 VGPRs
-// 104.1 / 16.2; four lanes with 3 slots 118.2 / 13.2, with 2 100.0 / 14.3, with 1 104.6 /
-// 16.4; with energies and four lanes 3 slots 134, 2 slots 144.
-template <bool EV>
-constexpr int ew_unroll() { return EV ? 3 : 2; }
-// erfc and the force's kernel G on [0, alpha rc] by Taylor polynomials about the centres
-// of 128 equal intervals, in units of the interval's width: no exponential per pair.
-// 500,000 particles: 136.5 us with erfcx polynomials of degree 10 times exp, two lanes
-// per particle, now 102; the rest is gathers (of two 16-byte reads per entry) -- with
-// 5 or 2 coefficients instead of 9 it takes 5 % less.
+// Two forms of the pair's erfc(x) and e^{-x^2}, x = alpha r:
+//   table   (forces without energies, alpha rc up to kTableReach) the force's kernel
+//           G(x) = erfc(x) + 2/sqrt(pi) x e^{-x^2} by Taylor polynomials about the centres of
+//           128 equal intervals of [0, alpha rc]: no exponential per pair;
+//   erfcx   (everything else) erfc(x) = e^{-x^2} erfcx(x), erfcx by degree-10 Taylor
+//           polynomials about the centres of 32 equal intervals, relative error ~1e-15: as
+//           accurate for each pair's own value wherever the pair lies.
+// Why the line lies there: a polynomial's remainder is a fraction of G(0) = 1, not of the
+// far pairs' G.  Largest relative error of a pair's force over (0.2 rc, rc), erfcx / table:
+// alpha rc = 3 1.4e-15 / 1.2e-15, 3.5 1.4e-15 / 1.5e-15, 4 2.4e-15 / 3.4e-15, 5 5.8e-16 /
+// 4.2e-13, 6 4.9e-15 / 1.8e-11, 10 8.8e-16 / 4.5e-7; of a pair's energy at 3 1.5e-15 / 5.4e-15.
+constexpr double kTableReach = 3.5;
 constexpr int kErfcIntervals = 128;
-constexpr int kErfcCoefs = 9;   // degree 8: G to 6e-16 absolute for alpha rc up to 6
+constexpr int kErfcCoefs = 9;   // degree 8
 constexpr int kErfcStride = 10;  // doubles per interval in LDS: 16 of 80-byte rows share no bank
-constexpr int kErfcSeeds = 384;  // doubles of the workspace for G(c) and e^{-c^2} per interval
+constexpr int kErfcSeeds = 384;  // doubles of the workspace: G(c) and e^{-c^2} per interval, or
+                                 // the erfcx polynomials
+constexpr int kErfcxIntervals = 32;
+constexpr int kErfcxDegree = 10;
+constexpr int kErfcxStride = 12;  // coefficients per interval, padded
+static_assert(kErfcxIntervals * kErfcxStride <= kErfcSeeds, "erfcx polynomials");
+static_assert(2 * kErfcIntervals <= kErfcSeeds, "seeds of G");
+
+// Slots per group and lane, four lanes per particle.  500,000 / 32,000 particles (us): table
+// 103.8 / 15.0 (with r rounded once more, which doubles the error, 101.7 / 14.8; erfcx with two
+// lanes per particle and 6 slots 136.5 / 21.1); erfcx without energies 2, 3, 4 slots 140 / 16.4,
+// 136 / 15.8, 140 / 15.9; with energies 2, 3, 4 slots 137 / 19.2, 145 / 18.6, 142 / 19.4 (two
+// lanes and 6 slots 145 / 23.4; the table and one for erfc 150 / 19.8).
+template <bool EV, bool TABLE>
+constexpr int ew_unroll() { return EV || TABLE ? 2 : 3; }
 
 // ------------------------------------------------------------ real space --
 
 struct RealArgs {
   BoxK b;
-  double alpha, a2, c2a;  // alpha, alpha^2, 2 alpha / sqrt(pi)
+  double alpha, a2, c2a;  // alpha, alpha^2, 2 alpha / sqrt(pi) (the last two: erfcx)
   double rc2, margin;
   int32_t n;
   const int32_t *nbr;
@@ -79,22 +93,25 @@ struct RealArgs {
   double *F;
   int accumulate;
   double *partial;  // per-block E_dir, or null
-  const double *seeds;  // [kErfcIntervals] G(c), then e^{-c^2}
-  double dx, u_scale;   // interval width in alpha r; intervals per unit length
+  const double *seeds;  // [kErfcIntervals] G(c), then e^{-c^2}; or [kErfcxIntervals][kErfcxStride]
+  double dx, u_scale;   // table: interval width in alpha r; intervals per unit length
+  double inv_dx, half_dx;  // erfcx: intervals of width dx = alpha rc / kErfcxIntervals
 };
 
-// Packs (x, y, z, q) records; block 0 also writes the tables' seeds, G(c) and e^{-c^2}
-// at every interval's centre c, with
-//   G(x) = erfc(x) + 2/sqrt(pi) x e^{-x^2}   (the force is q_i q_j G(alpha r) / r^3 d).
-__global__ __launch_bounds__(kThreads) void k_pack_xq(int32_t n, const double *x, const double *q,
-                                                      double4 *xq, double alpha, double u_scale,
-                                                      double *seeds) {
-  if (blockIdx.x == 0 && threadIdx.x < kErfcIntervals) {
+// Packs (x, y, z, q) records; block 0 also writes, for the form TABLE or not,
+//   the table's seeds G(c) and e^{-c^2} at every interval's centre c, or
+//   the erfcx polynomials: about each centre c, a_n = erfcx^(n)(c) / n! from erfcx(c) =
+//   e^{c^2} erfc(c) and y' = 2 x y - 2/sqrt(pi), y^(n+1) = 2 x y^(n) + 2 n y^(n-1).
+template <bool TABLE>
+__global__ __launch_bounds__(kThreads) void k_pack_xq(RealArgs a, const double *x, const double *q,
+                                                      double4 *xq, double *seeds) {
+  if (TABLE && blockIdx.x == 0 && threadIdx.x < kErfcIntervals) {
     // c = alpha (k + 1/2) / u_scale with what its rounding leaves, lo, and c^2 likewise:
     // G changes by 2 c^2 times a relative change of c
-    const double k = threadIdx.x + 0.5, h = k / u_scale;
-    const double c = alpha * h;
-    const double lo = __builtin_fma(alpha, h, -c) + alpha * (__builtin_fma(-h, u_scale, k) / u_scale);
+    const double k = threadIdx.x + 0.5, h = k / a.u_scale;
+    const double c = a.alpha * h;
+    const double lo =
+        __builtin_fma(a.alpha, h, -c) + a.alpha * (__builtin_fma(-h, a.u_scale, k) / a.u_scale);
     const double cc = c * c;
     const double e0 = exp(-cc), e = __builtin_fma(-e0, __builtin_fma(c, c, -cc), e0);
     constexpr double two = 1.1283791670955126, two_lo = 1.533545961316588e-17;  // 2/sqrt(pi)
@@ -103,32 +120,50 @@ __global__ __launch_bounds__(kThreads) void k_pack_xq(int32_t n, const double *x
         __builtin_fma(two, ce, erfc(c)) + (two_lo * ce - 2.0 * two * cc * e * lo);
     seeds[kErfcIntervals + threadIdx.x] = __builtin_fma(-2.0 * c * lo, e, e);
   }
+  if (!TABLE && blockIdx.x == 0 && threadIdx.x < kErfcxIntervals) {
+    const double c = (2 * threadIdx.x + 1) * a.half_dx;
+    double *p = seeds + threadIdx.x * kErfcxStride;
+    double ym1 = exp(c * c) * erfc(c);
+    double y = 2.0 * c * ym1 - 2.0 / sqrt(kPi);
+    double fact = 1.0;
+    p[0] = ym1;
+    p[1] = y;
+    for (int k = 1; k < kErfcxDegree; ++k) {
+      const double yn = 2.0 * c * y + 2.0 * k * ym1;
+      fact *= (k + 1);
+      p[k + 1] = yn / fact;
+      ym1 = y;
+      y = yn;
+    }
+  }
   const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (i >= n) return;
+  if (i >= a.n) return;
   xq[i] = make_double4(x[3 * i], x[3 * i + 1], x[3 * i + 2], q[i]);
 }
 
-// The block's tables in LDS from the seeds.  With e_n the Taylor coefficients of
-// e^{-x^2} about c, e_{n+1} = -2 (c e_n + e_{n-1}) / (n+1):
-//   G:    G(c), then -4/sqrt(pi) (c^2 e_{n-1} + 2 c e_{n-2} + e_{n-3}) / n  (G' = -4/sqrt(pi) x^2 e^{-x^2})
-//   erfc: G(c) - 2/sqrt(pi) c e^{-c^2}, then -2/sqrt(pi) e_{n-1} / n         (energies only)
-// each times dx^n.
-template <bool EV>
+// The block's polynomials in LDS.  TABLE: from the seeds; with e_n the Taylor coefficients
+// of e^{-x^2} about c, e_{n+1} = -2 (c e_n + e_{n-1}) / (n+1), the coefficients are
+//   G(c), then -4/sqrt(pi) (c^2 e_{n-1} + 2 c e_{n-2} + e_{n-3}) / n  (G' = -4/sqrt(pi) x^2 e^{-x^2})
+// times dx^n.  Else a copy of the erfcx polynomials.
+template <bool TABLE>
 __device__ __forceinline__ void erfc_tables(const RealArgs &a, double *tab) {
+  if constexpr (!TABLE) {
+    for (int k = threadIdx.x; k < kErfcxIntervals * kErfcxStride; k += kEwThreads)
+      if (k % kErfcxStride <= kErfcxDegree) tab[k] = a.seeds[k];
+    return;
+  }
   const int k0 = threadIdx.x;
   if (k0 >= kErfcIntervals) return;
   constexpr double two = 1.1283791670955126;  // 2 / sqrt(pi)
   const double c = (k0 + 0.5) * a.dx;
-  double *g = tab + k0 * kErfcStride, *p = g + kErfcIntervals * kErfcStride;
+  double *g = tab + k0 * kErfcStride;
   double e0 = a.seeds[kErfcIntervals + k0], e1 = 0.0, e2 = 0.0;  // e_{n-1}, e_{n-2}, e_{n-3}
   g[0] = a.seeds[k0];
-  if constexpr (EV) p[0] = g[0] - two * c * e0;
   double pw = -two;
 #pragma unroll
   for (int k = 1; k < kErfcCoefs; ++k) {
     pw *= a.dx;
     const double f = pw * (1.0 / k);
-    if constexpr (EV) p[k] = f * e0;
     g[k] = 2.0 * f * ((c * c) * e0 + 2.0 * c * e1 + e2);
     const double en = (-2.0 / k) * (c * e0 + e1);
     e2 = e1;
@@ -145,18 +180,20 @@ __device__ __forceinline__ const double4 *xq_of(const double4 *p, int32_t j) {
     return (const double4 *)((const char *)p + ((uint32_t)j << 5));
 }
 
+template <int DEGREE>
 __device__ __forceinline__ double horner(const double *cf, double t) {
-  double p = cf[kErfcCoefs - 1];
+  double p = cf[DEGREE];
 #pragma unroll
-  for (int k = kErfcCoefs - 2; k >= 0; --k) p = __builtin_fma(p, t, cf[k]);
+  for (int k = DEGREE - 1; k >= 0; --k) p = __builtin_fma(p, t, cf[k]);
   return p;
 }
 
 // One pair: adds q_j-weighted force scalar times d and (EV) the energy kernel.
-template <bool WRAP, bool EV>
+template <bool WRAP, bool EV, bool TABLE>
 __device__ __forceinline__ void real_pair(const RealArgs &a, const double *tab, const double4 &me,
                                           const double4 &o, bool ok, double &fx, double &fy,
                                           double &fz, double &e) {
+  static_assert(!(EV && TABLE), "energies come from erfcx");
   double dx = me.x - o.x, dy = me.y - o.y, dz = me.z - o.z;
   if constexpr (WRAP) {
     dx = min_image(dx, a.b.L[0], a.b.invL[0]);
@@ -165,35 +202,45 @@ __device__ __forceinline__ void real_pair(const RealArgs &a, const double *tab, 
   }
   const double r2 = dist2(dx, dy, dz);
   const bool in = ok && r2 < a.rc2;
-  // r^2 with fewer roundings than the cutoff's: a relative error of it enters the
-  // force (alpha r)^2 times over; 1 keeps padding and far pairs finite
-  const double rr2 = in ? __builtin_fma(dz, dz, __builtin_fma(dy, dy, dx * dx)) : 1.0;
-  // 1/r from one refined reciprocal square root of r^2 and r = r^2 / r: about
-  // 9 % faster at 500k atoms than a square root followed by a reciprocal
-  const double ir = rsqrt64(rr2);
-  double r = rr2 * ir;
-  // energies add up without the forces' cancellation of common errors: r to half a unit
-  if constexpr (EV) r = __builtin_fma(0.5 * ir, __builtin_fma(-r, r, rr2), r);
-  const double u = a.u_scale * r;
-  int it = (int)u;
-  it = it < kErfcIntervals - 1 ? it : kErfcIntervals - 1;
-  const double t = __builtin_fma(a.u_scale, r, -((double)it + 0.5));
-  const double *cf = tab + it * kErfcStride;
-  const double qi = in ? o.w * ir : 0.0;
-  const double qs = qi * (ir * ir) * horner(cf, t);
+  double qs;
+  if constexpr (TABLE) {
+    // r^2 with fewer roundings than the cutoff's, and r to half a unit: a relative error
+    // of r enters the force 2 (alpha r)^2 times over; 1 keeps padding and far pairs finite
+    const double rr2 = in ? __builtin_fma(dz, dz, __builtin_fma(dy, dy, dx * dx)) : 1.0;
+    const double ir = rsqrt64(rr2);
+    double r = rr2 * ir;
+    const double u = a.u_scale * r;  // the interval, before r's last refinement
+    int it = (int)u;
+    it = it < kErfcIntervals - 1 ? it : kErfcIntervals - 1;
+    r = __builtin_fma(0.5 * ir, __builtin_fma(-r, r, rr2), r);
+    const double t = __builtin_fma(a.u_scale, r, -((double)it + 0.5));
+    qs = (in ? o.w * ir : 0.0) * (ir * ir) * horner<kErfcCoefs - 1>(tab + it * kErfcStride, t);
+  } else {
+    const double rr2 = in ? r2 : 1.0;  // keeps padding and far pairs finite
+    // 1/r from one refined reciprocal square root of r^2 and r = r^2 / r: about
+    // 9 % faster at 500k atoms than a square root followed by a reciprocal
+    const double ir = rsqrt64(rr2);
+    const double xa = a.alpha * (rr2 * ir);
+    int it = (int)(xa * a.inv_dx);
+    it = it < kErfcxIntervals - 1 ? it : kErfcxIntervals - 1;
+    const double t = xa - (2 * it + 1) * a.half_dx;
+    const double ex = exp(-a.a2 * rr2);
+    const double er = ex * horner<kErfcxDegree>(tab + it * kErfcxStride, t) * ir;  // erfc(alpha r) / r
+    qs = in ? o.w * ((er + a.c2a * ex) * (ir * ir)) : 0.0;
+    if constexpr (EV) e += in ? o.w * er : 0.0;
+  }
   fx = __builtin_fma(qs, dx, fx);
   fy = __builtin_fma(qs, dy, fy);
   fz = __builtin_fma(qs, dz, fz);
-  if constexpr (EV) e = __builtin_fma(qi, horner(cf + kErfcIntervals * kErfcStride, t), e);
 }
 
 // Lane t's entries of the row, in masked groups of U (slots beyond cnt repeat the
-// lane's first entry).
-template <bool WRAP, bool WIDE, bool EV>
+// group's first entry).
+template <bool WRAP, bool WIDE, bool EV, bool TABLE>
 __device__ __forceinline__ void real_row(const RealArgs &a, const double *tab, const int32_t *row,
                                          int32_t cnt, const double4 &me, double &fx, double &fy,
                                          double &fz, double &e) {
-  constexpr int U = ew_unroll<EV>();
+  constexpr int U = ew_unroll<EV, TABLE>();
   constexpr int kStep = kEwTeam * kWave;
 #pragma unroll 1
   for (int32_t k = 0; k < cnt; k += U, row += U * kStep) {
@@ -204,15 +251,17 @@ __device__ __forceinline__ void real_row(const RealArgs &a, const double *tab, c
 #pragma unroll
     for (int u = 0; u < U; ++u) o[u] = *xq_of<WIDE>(a.xq, j[u]);
 #pragma unroll
-    for (int u = 0; u < U; ++u) real_pair<WRAP, EV>(a, tab, me, o[u], k + u < cnt, fx, fy, fz, e);
+    for (int u = 0; u < U; ++u)
+      real_pair<WRAP, EV, TABLE>(a, tab, me, o[u], k + u < cnt, fx, fy, fz, e);
   }
 }
 
-template <bool WIDE, bool EV>
+template <bool WIDE, bool EV, bool TABLE>
 __global__ __launch_bounds__(kEwThreads) void k_ewald_real(RealArgs a) {
   __shared__ double red[kRedRows * kEwThreads / kWave];
-  __shared__ __align__(16) double tab[(EV ? 2 : 1) * kErfcIntervals * kErfcStride];
-  erfc_tables<EV>(a, tab);
+  __shared__ __align__(16) double
+      tab[TABLE ? kErfcIntervals * kErfcStride : kErfcxIntervals * kErfcxStride];
+  erfc_tables<TABLE>(a, tab);
   __syncthreads();
   const int t = (int)threadIdx.x % kEwTeam;
   const int32_t i = xcd_block(blockIdx.x, gridDim.x) * kEwAtoms + (int)threadIdx.x / kEwTeam;
@@ -230,9 +279,9 @@ __global__ __launch_bounds__(kEwThreads) void k_ewald_real(RealArgs a) {
     const int32_t *row =
         a.nbr + (int64_t)(i >> 6) * a.maxn * kWave + (i & (kWave - 1)) + (int64_t)t * kWave;
     if (interior)
-      real_row<false, WIDE, EV>(a, tab, row, cnt, me, fx, fy, fz, e);
+      real_row<false, WIDE, EV, TABLE>(a, tab, row, cnt, me, fx, fy, fz, e);
     else
-      real_row<true, WIDE, EV>(a, tab, row, cnt, me, fx, fy, fz, e);
+      real_row<true, WIDE, EV, TABLE>(a, tab, row, cnt, me, fx, fy, fz, e);
   }
   fx = team_sum<kEwTeam>(fx);
   fy = team_sum<kEwTeam>(fy);
@@ -1325,23 +1374,32 @@ int launch_ewald_real(const BoxK &b, double alpha, double rc, int64_t n, const d
   a.partial = (double *)((char *)ws + (size_t)(n > 0 ? n : 0) * sizeof(double4));
   double *seeds = a.partial + nblk;
   a.seeds = seeds;
-  // intervals per unit length, cut to 24 bits: r in interval widths then carries no
-  // error common to all pairs (G's relative sensitivity to it is ~2 (alpha r)^2)
-  float per = (float)(kErfcIntervals / rc);
-  if ((double)per * rc > kErfcIntervals) per = nextafterf(per, 0.0f);
-  a.u_scale = per;
-  a.dx = alpha / a.u_scale;
+  // rc within the range of the 24-bit intervals per unit length below
+  const bool table = !e_total && alpha * rc <= kTableReach && rc > 1e-30 && rc < 1e30;
+  if (table) {
+    // intervals per unit length, cut to 24 bits: r in interval widths then carries no
+    // error common to all pairs (G's relative sensitivity to it is ~2 (alpha r)^2)
+    float per = (float)(kErfcIntervals / rc);
+    if ((double)per * rc > kErfcIntervals) per = nextafterf(per, 0.0f);
+    a.u_scale = per;
+    a.dx = alpha / a.u_scale;
+  } else {
+    const double dx = alpha * rc / kErfcxIntervals;
+    a.inv_dx = 1.0 / dx;
+    a.half_dx = 0.5 * dx;
+  }
   if (n > 0) {
-    k_pack_xq<<<blocks_of(n, kThreads), kThreads, 0, st>>>((int32_t)n, x, q, (double4 *)ws,
-                                                           alpha, a.u_scale, seeds);
+    const unsigned npack = blocks_of(n, kThreads);
+    if (table) k_pack_xq<true><<<npack, kThreads, 0, st>>>(a, x, q, (double4 *)ws, seeds);
+    else k_pack_xq<false><<<npack, kThreads, 0, st>>>(a, x, q, (double4 *)ws, seeds);
     const bool wide = n > kNarrowAtoms;
-    if (e_total) {
-      if (wide) k_ewald_real<true, true><<<nblk, kEwThreads, 0, st>>>(a);
-      else k_ewald_real<false, true><<<nblk, kEwThreads, 0, st>>>(a);
-    } else {
-      if (wide) k_ewald_real<true, false><<<nblk, kEwThreads, 0, st>>>(a);
-      else k_ewald_real<false, false><<<nblk, kEwThreads, 0, st>>>(a);
-    }
+#define LJMD_REAL(EV, TABLE)                                                       \
+  wide ? k_ewald_real<true, EV, TABLE><<<nblk, kEwThreads, 0, st>>>(a)             \
+       : k_ewald_real<false, EV, TABLE><<<nblk, kEwThreads, 0, st>>>(a)
+    if (e_total) LJMD_REAL(true, false);
+    else if (table) LJMD_REAL(false, true);
+    else LJMD_REAL(false, false);
+#undef LJMD_REAL
   }
   if (e_total)
     k_colsum<1024><<<1, 1024, 0, st>>>(n > 0 ? nblk : 0, 1, 1, a.partial, e_total, 1.0, 0);
