@@ -381,11 +381,11 @@ __global__ __launch_bounds__(kThreads) void k_bmod(RecArgs a, double *z, int64_t
 // floor(u).  Its support reaches N - 1 points below the base in every dimension, so a
 // tile's particles touch a box of E = T + N - 1 points per dimension.  Particles are
 // sorted by tile (count, then scan and scatter of their indices, one launch for up to
-// 4,096 tiles); one block per tile then
-// adds its particles' weights into the box in LDS and writes the box out, and the
-// x pass adds up the (one to eight) boxes that cover each point as it reads its rows:
-// no atomics on the grid, no clearing of it, and the same cost in whatever order the
-// particles come.  The gather takes the box of phi into LDS once per tile.
+// 4,096 tiles); one block per tile (more for a crowded one) then adds its particles'
+// weights into the box in LDS and writes the box out, and the x pass adds up the (one to
+// eight) boxes that cover each point as it reads its rows: no atomics on the grid, no
+// clearing of it, and the same cost in whatever order the particles come.  The gather takes
+// the box of phi into LDS once per tile.
 //
 // Why: FP64 atomics on the grid run at about 190 per ns whatever their locality, and one
 // box per 64 consecutive particles needs 21 of them per particle (96 us at 500,000
@@ -400,9 +400,66 @@ struct TileK {
   int32_t nt[3];  // tiles per dimension
   int32_t e[3];   // box edge T + N - 1
   int32_t ntiles, box;  // box: points per box
-  int32_t *count, *start, *key, *rank, *order;
+  int32_t crowd, chunk;  // most particles of a tile's own block; particles per chunk
+  int32_t *count, *start, *key, *rank, *order;  // count[ntiles]: number of crowded tiles
   double *boxes;
 };
+
+// A tile of more than `crowd` particles is crowded: its block leaves them to other blocks,
+// two for every `chunk` consecutive particles in tile order (a chunk meets at most two
+// crowded tiles, its first particle's and its last's, as crowd >= chunk), each adding its
+// box to the tile's by FP64 atomics (the tile's box is cleared when the particles are
+// ordered).  So a droplet or a slab spreads over the chip too.  The whole reciprocal call at
+// order 4 (us), spreading by atomics / one block per tile whatever it holds / this: 262,144
+// particles in a 20th, an 8th, a quarter of the edge of a 128^3 grid 290 / 882 / 182, 266 /
+// 2,205 / 177, 191 / 626 / 151, in a slab of a tenth 174 / 237 / 150; 32,768 in an 8th of 64^3
+// 69 / 350 / 57, in a 20th of 32^3 60 / 785 / 48.  Uniform systems: 121.9 / 47.2 without
+// this, 121.8 / 47.4 with it at 500,000 and 128^3 / 32,000 and 64^3.
+constexpr int kTileCrowd = 1024;  // at least: four passes of a block
+constexpr int kTileChunk = 256;   // at least: one pass
+
+// The tile of block `blk` and its particles in tile order [p0, end): all of tile blk's for
+// blk < ntiles (the caller leaves when they are more than crowd), else the part of a chunk
+// in a crowded tile; false when there is none.  Block-uniform.
+__device__ __forceinline__ bool tile_work(const TileK &t, int n, int blk, int &tile, int &p0,
+                                          int &end) {
+  if (blk < t.ntiles) {
+    tile = xcd_block(blk, t.ntiles);
+    p0 = t.start[tile];
+    end = t.start[tile + 1];
+    return true;
+  }
+  if (t.count[t.ntiles] == 0) return false;  // no crowded tile
+  const int c0 = (blk - t.ntiles) / 2 * t.chunk, c1 = n - c0 > t.chunk ? c0 + t.chunk : n;
+  const int first = t.key[t.order[c0]];
+  tile = (blk - t.ntiles) % 2 == 0 ? first : t.key[t.order[c1 - 1]];
+  if ((blk - t.ntiles) % 2 != 0 && tile == first) return false;
+  p0 = t.start[tile];
+  end = t.start[tile + 1];
+  if (end - p0 <= t.crowd) return false;
+  p0 = p0 > c0 ? p0 : c0;
+  end = end < c1 ? end : c1;
+  return true;
+}
+
+// Clears the box of every crowded tile whose particle of rank 0 is this thread's (live
+// threads: a particle of tile `key` with m particles) and counts those tiles; the whole
+// block calls it.
+template <int THREADS>
+__device__ __forceinline__ void clear_crowded(const TileK &t, bool live, int key, int rank, int m) {
+  __shared__ int32_t crowded[THREADS], ncrowded;
+  if (threadIdx.x == 0) ncrowded = 0;
+  __syncthreads();
+  if (live && rank == 0 && m > t.crowd) {
+    crowded[atomicAdd(&ncrowded, 1)] = key;
+    atomicAdd(&t.count[t.ntiles], 1);
+  }
+  __syncthreads();
+  for (int k = 0; k < ncrowded; ++k) {
+    double *box = t.boxes + (int64_t)crowded[k] * t.box;
+    for (int q = threadIdx.x; q < t.box; q += THREADS) box[q] = 0.0;
+  }
+}
 
 // Tile of a base point, and the point's place in it.
 __device__ __forceinline__ int tile_of(const TileK &t, const int (&b)[3]) {
@@ -437,7 +494,12 @@ __global__ __launch_bounds__(kGatherAtoms) void k_tile_count(RecArgs a, TileK tk
 
 __global__ __launch_bounds__(kThreads) void k_tile_scatter(int32_t n, TileK tk) {
   const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  if (i < n) tk.order[tk.start[tk.key[i]] + tk.rank[i]] = (int32_t)i;
+  const bool live = i < n;
+  const int32_t key = live ? tk.key[i] : 0, rank = live ? tk.rank[i] : 0;
+  const int32_t s = tk.start[key];
+  if (live) tk.order[s + rank] = (int32_t)i;
+  const int32_t m = tk.start[key + 1] - s;
+  if (__syncthreads_or(live && m > tk.crowd)) clear_crowded<kThreads>(tk, live, key, rank, m);
 }
 
 // As the scan of the counts into tk.start and k_tile_scatter, in one launch, for up to
@@ -450,8 +512,8 @@ constexpr int kOrderThreads = 1024;
 constexpr int kOrderTiles = 4 * kOrderThreads;
 __global__ __launch_bounds__(kOrderThreads) void k_tile_order(int32_t n, TileK tk) {
   constexpr int kWaves = kOrderThreads / kWave;
-  __shared__ int32_t start[kOrderTiles];
-  __shared__ int32_t wsum[kWaves];
+  __shared__ int32_t start[kOrderTiles + 1];
+  __shared__ int32_t wsum[kWaves], wfull[kWaves];
   const int t = threadIdx.x, lane = t & (kWave - 1), w = t / kWave;
   const int64_t i = (int64_t)blockIdx.x * kOrderThreads + t;
   const int32_t key = i < n ? tk.key[i] : 0, rank = i < n ? tk.rank[i] : 0;
@@ -460,11 +522,18 @@ __global__ __launch_bounds__(kOrderThreads) void k_tile_order(int32_t n, TileK t
   for (int q = 0; q < 4; ++q) v[q] = 4 * t + q < tk.ntiles ? tk.count[4 * t + q] : 0;
   const int32_t s = v[0] + v[1] + v[2] + v[3];
   const int32_t inc = wave_inclusive_scan(s);
-  if (lane == kWave - 1) wsum[w] = inc;
+  const bool full = __ballot(max(max(v[0], v[1]), max(v[2], v[3])) > tk.crowd) != 0;
+  if (lane == kWave - 1) {
+    wsum[w] = inc;
+    wfull[w] = full;
+  }
   __syncthreads();
-  int32_t run = inc - s;
+  int32_t run = inc - s, crowded = 0;
 #pragma unroll
-  for (int k = 0; k < kWaves; ++k) run += k < w ? wsum[k] : 0;
+  for (int k = 0; k < kWaves; ++k) {
+    run += k < w ? wsum[k] : 0;
+    crowded |= wfull[k];
+  }
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     const int c = 4 * t + q;
@@ -472,9 +541,11 @@ __global__ __launch_bounds__(kOrderThreads) void k_tile_order(int32_t n, TileK t
     if (blockIdx.x == 0 && c < tk.ntiles) tk.start[c] = run;
     run += v[q];
     if (blockIdx.x == 0 && c == tk.ntiles - 1) tk.start[tk.ntiles] = run;
+    if (c == kOrderTiles - 1) start[kOrderTiles] = run;
   }
   __syncthreads();
   if (i < n) tk.order[start[key] + rank] = (int32_t)i;
+  if (crowded) clear_crowded<kOrderThreads>(tk, i < n, key, rank, start[key + 1] - start[key]);
 }
 
 // Origin of tile `tile` (first base point).
@@ -493,12 +564,14 @@ template <int N, int TX, int TY, int TZ, int TEAM>
 __global__ __launch_bounds__(kTileThreads) void k_spread_tile(RecArgs a, TileK tk) {
   constexpr int EX = TX + N - 1, EY = TY + N - 1, EZ = TZ + N - 1;
   __shared__ double box[EX * EY * EZ];
-  const int tile = xcd_block(blockIdx.x, gridDim.x);
+  int tile, p0, end;
+  if (!tile_work(tk, a.n, blockIdx.x, tile, p0, end)) return;  // block-uniform
   const int t = (int)threadIdx.x % TEAM;
-  const int end = tk.start[tile + 1];
   for (int k = threadIdx.x; k < EX * EY * EZ; k += kTileThreads) box[k] = 0.0;
   __syncthreads();
-  for (int p = tk.start[tile] + (int)threadIdx.x / TEAM; p < end; p += kTileThreads / TEAM) {
+  const bool own = (int)blockIdx.x < tk.ntiles;
+  if (own && end - p0 > tk.crowd) return;
+  for (uint32_t p = p0 + threadIdx.x / TEAM; p < (uint32_t)end; p += kTileThreads / TEAM) {
     const int64_t i = tk.order[p];
     double w[3][N], dw[N];
     int b[3];
@@ -528,7 +601,12 @@ __global__ __launch_bounds__(kTileThreads) void k_spread_tile(RecArgs a, TileK t
   }
   __syncthreads();
   double *out = tk.boxes + (int64_t)tile * (EX * EY * EZ);
-  for (int k = threadIdx.x; k < EX * EY * EZ; k += kTileThreads) out[k] = box[k];
+  if (own) {
+    for (int k = threadIdx.x; k < EX * EY * EZ; k += kTileThreads) out[k] = box[k];
+  } else {
+    for (int k = threadIdx.x; k < EX * EY * EZ; k += kTileThreads)
+      if (box[k] != 0.0) unsafeAtomicAdd(&out[k], box[k]);
+  }
 }
 
 // The forces of a tile's particles from the box of phi (k_gather's sums).
@@ -536,9 +614,10 @@ template <int N, int TX, int TY, int TZ, int TEAM>
 __global__ __launch_bounds__(kTileThreads) void k_gather_tile(RecArgs a, TileK tk) {
   constexpr int EX = TX + N - 1, EY = TY + N - 1, EZ = TZ + N - 1;
   __shared__ double box[EX * EY * EZ];
-  const int tile = xcd_block(blockIdx.x, gridDim.x);
-  const int p0 = tk.start[tile], end = tk.start[tile + 1];
-  if (p0 == end) return;  // block-uniform
+  int tile, p0, end;
+  if (!tile_work(tk, a.n, blockIdx.x, tile, p0, end) || p0 == end ||
+      ((int)blockIdx.x < tk.ntiles && end - p0 > tk.crowd))
+    return;  // block-uniform
   const int t = (int)threadIdx.x % TEAM;
   int o[3];
   tile_origin(tk, tile, o);
@@ -549,7 +628,7 @@ __global__ __launch_bounds__(kTileThreads) void k_gather_tile(RecArgs a, TileK t
     box[k] = a.grid[((int64_t)z * a.K[1] + y) * a.K[0] + x];
   }
   __syncthreads();
-  for (int p = p0 + (int)threadIdx.x / TEAM; p < end; p += kTileThreads / TEAM) {
+  for (uint32_t p = p0 + threadIdx.x / TEAM; p < (uint32_t)end; p += kTileThreads / TEAM) {
     const int64_t i = tk.order[p];
     double w[3][N], dw[3][N];
     int b[3];
@@ -1270,6 +1349,13 @@ TileK make_tiles(int order, const int32_t K[3], int64_t n, char *p) {
     t.ntiles *= t.nt[d];
     t.box *= t.e[d];
   }
+  // Up to 512 chunks.  Where the tiles fill the chip a tile is crowded only above twice the
+  // mean, since a uniform system of any density is then balanced as it is.
+  const int64_t part = (n / 512 + kTileChunk - 1) / kTileChunk * kTileChunk;
+  t.chunk = (int32_t)(part > kTileChunk ? part : kTileChunk);
+  const int64_t twice = t.ntiles >= 512 ? 2 * n / t.ntiles : 0;
+  t.crowd = (int32_t)(twice > kTileCrowd ? twice : kTileCrowd);
+  if (t.crowd < t.chunk) t.crowd = t.chunk;
   p = (char *)align256((size_t)p);
   const size_t ints = align256((size_t)(t.ntiles + 2) * sizeof(int32_t));
   const size_t per = align256((size_t)n * sizeof(int32_t));
@@ -1282,20 +1368,27 @@ TileK make_tiles(int order, const int32_t K[3], int64_t n, char *p) {
   return t;
 }
 
+// A block per tile and, where there can be crowded tiles, two per chunk (up to 1,026).
+unsigned tile_blocks(const RecArgs &a, const TileK &t) {
+  return (unsigned)t.ntiles + (a.n > t.crowd ? 2 * blocks_of(a.n, t.chunk) : 0);
+}
+
 template <int N>
 void spread_tiles(const RecArgs &a, const TileK &t, bool large, hipStream_t st) {
+  const unsigned nb = tile_blocks(a, t);
   if (large)
-    k_spread_tile<N, 16, 16, 8, kTileTeam><<<t.ntiles, kTileThreads, 0, st>>>(a, t);
+    k_spread_tile<N, 16, 16, 8, kTileTeam><<<nb, kTileThreads, 0, st>>>(a, t);
   else if constexpr (N == 4)
-    k_spread_tile<N, 8, 8, 8, kTileTeam><<<t.ntiles, kTileThreads, 0, st>>>(a, t);
+    k_spread_tile<N, 8, 8, 8, kTileTeam><<<nb, kTileThreads, 0, st>>>(a, t);
 }
 
 template <int N>
 void gather_tiles(const RecArgs &a, const TileK &t, bool large, hipStream_t st) {
+  const unsigned nb = tile_blocks(a, t);
   if (large)
-    k_gather_tile<N, 16, 16, 8, kTileTeam><<<t.ntiles, kTileThreads, 0, st>>>(a, t);
+    k_gather_tile<N, 16, 16, 8, kTileTeam><<<nb, kTileThreads, 0, st>>>(a, t);
   else if constexpr (N == 4)
-    k_gather_tile<N, 8, 8, 8, kTileTeam><<<t.ntiles, kTileThreads, 0, st>>>(a, t);
+    k_gather_tile<N, 8, 8, 8, kTileTeam><<<nb, kTileThreads, 0, st>>>(a, t);
 }
 
 // tk: the tiles, or null for spreading by atomics.
@@ -1304,7 +1397,7 @@ void launch_rec_order(const RecArgs &a, const TileK *tk, double *self_partial, h
   const int64_t npts = grid_points(a.K);
   // one launch for the tables and the zeros: tile counts (in pairs), or the grid
   double *zero = tk ? (double *)tk->count : a.grid;
-  const int64_t nzero = tk ? (tk->ntiles + 1) / 2 : npts;
+  const int64_t nzero = tk ? tk->ntiles / 2 + 1 : npts;  // with count[ntiles]
   k_bmod<N><<<kBmodBlocks + blocks_of(nzero, kThreads), kThreads, 0, st>>>(a, zero, nzero);
   const bool large = large_tiles(a.K);
   if (tk) {

@@ -62,3 +62,84 @@ def test_ewald_real_isolated_pairs(dev, orc, arc, far):
         err = np.linalg.norm(ops.scatter_rows(ids, f).cpu().numpy() - F_o, axis=1)
         assert (err <= tol * np.linalg.norm(F_o, axis=1)).all(), (err / tol)[near].max()
     assert abs(E.item() - e_o.sum()) <= tol.max() * e_o.sum()
+
+
+def _recip(L, order, K, xt, qt, ws):
+    """Reciprocal forces and energy through the C ABI with exactly this workspace."""
+    import ctypes
+
+    import torch
+    from paper_2109_09056_amd import _lib
+    F, e = torch.empty_like(xt), torch.empty(1, dtype=torch.float64, device=xt.device)
+    _lib.check(_lib.load().ljmd_spme_recip(
+        _lib.make_box(L), li.EWALD_ALPHA, order, (ctypes.c_int32 * 3)(*K), xt.shape[0],
+        xt.data_ptr(), qt.data_ptr(), F.data_ptr(), e.data_ptr(), 0, ws.data_ptr(), ws.numel(),
+        torch.cuda.current_stream(xt.device).cuda_stream), "spme")
+    return F, e
+
+
+def _spme_direct_bytes(n, npts):
+    """The workspace without the tiles' part: charge is spread by atomics."""
+    half = npts // 2 + npts // 8
+    return npts * 8 + half * 16 + 3 * 256 * 8 + 8 * (-(-half // 512) + max(1, -(-n // 256))) + 256
+
+
+@pytest.mark.parametrize("order,K,n", [(4, (32, 16, 64), 1025), (4, (64, 32, 64), 9000),
+                                       (4, (128, 128, 64), 9000), (6, (128, 64, 128), 5000),
+                                       (4, (256, 256, 256), 40000), (4, (8, 8, 8), 3000)])
+def test_spme_crowded_tiles(dev, order, K, n):
+    """Clumps in single tiles, over tile faces and box faces, next to sparse tiles, charges
+    in random order: forces and energy with the tiles against those without, which differ in
+    the order of at most n additions per grid point, as in the test of sparser tiles."""
+    import torch
+    from paper_2109_09056_amd import ops
+    L = np.array([17.0, 16.0, 18.0])
+    g = np.random.default_rng(n + order)
+    h = L / K
+    x = g.uniform(0, 1, (n, 3)) * L
+    x[: n // 2] = L * 0.4 + 2.0 * h * g.uniform(0, 1, (n // 2, 3))  # inside a tile, or two
+    x[n // 2: 3 * n // 4] = np.mod(3.0 * h * g.uniform(-1, 1, (n // 4 + n % 4, 3))[: 3 * n // 4 - n // 2], L)
+    x = x[g.permutation(n)]
+    q = g.uniform(-1.0, 1.0, n)
+    T = _t(dev)
+    xt, qt, npts = T(x), T(q), K[0] * K[1] * K[2]
+    out = []
+    for nbytes in (ops.workspace_bytes(ops.OP_SPME, n, ncells=npts), _spme_direct_bytes(n, npts)):
+        ws = torch.full((nbytes,), 255, dtype=torch.uint8, device=dev)  # NaN everywhere
+        F, e = _recip(L, order, K, xt, qt, ws)
+        out.append((F.cpu().numpy(), e.item()))
+    (Fa, ea), (Fb, eb) = out
+    assert np.isfinite(Fa).all()
+    scale = max(np.abs(Fb).max(), li.EWALD_ALPHA ** 2)
+    assert np.abs(Fa - Fb).max() <= 1e-13 * scale * n / 100.0
+    assert ea == pytest.approx(eb, rel=1e-12)
+
+
+def _milliseconds(f, reps=5):
+    import torch
+    f()
+    best = float("inf")
+    for _ in range(reps):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        f()
+        b.record()
+        b.synchronize()
+        best = min(best, a.elapsed_time(b))
+    return best
+
+
+def test_spme_droplet_uses_the_chip(dev):
+    """262,144 charges in an eighth of the edge of a 64^3 grid: with the tiles no more than
+    twice as long as without them (a block per tile, whatever it holds, took 12 times)."""
+    import torch
+    from paper_2109_09056_amd import ops
+    n, K, L = 262144, (64, 64, 64), np.full(3, 32.0)
+    x = (0.1 + 0.125 * np.random.default_rng(3).uniform(0, 1, (n, 3))) * L
+    x = x[np.lexsort(np.floor(x).T)]
+    T = _t(dev)
+    xt, qt, npts = T(x), T(np.where(np.arange(n) % 2, 1.0, -1.0)), 64 ** 3
+    t = [_milliseconds(lambda: _recip(L, 4, K, xt, qt, ws)) for ws in
+         (torch.empty(b, dtype=torch.uint8, device=dev)
+          for b in (ops.workspace_bytes(ops.OP_SPME, n, ncells=npts), _spme_direct_bytes(n, npts)))]
+    assert t[0] <= 2.0 * t[1], t
