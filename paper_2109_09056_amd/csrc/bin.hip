@@ -5,8 +5,8 @@
 // Four launches:
 //   1. cell id + histogram   one thread per atom; lanes of a wavefront in the
 //                            same cell share one atomic add and get ranks
-//   2. exclusive scan        one 1024-thread block over all cells, in chunks
-//                            (wavefront shuffle scans)
+//   2. exclusive scan        a 1024-thread block per chunk of cells (three launches
+//                            beyond 65,536 cells)
 //   3. scatter               one thread per atom to slot start[cell] + rank
 //   4. in-cell rank + permute  one wavefront per cell: ids of the cell are
 //                            staged in LDS, each lane ranks its atom among
@@ -54,17 +54,22 @@ __global__ void k_count(int64_t n, const double *__restrict__ x, GridK g,
   }
 }
 
-// Exclusive scan of counts[0..m) into start[0..m] (start[m] = total), one launch, no
-// flags between blocks: every block sums the counts before its chunk of kScanChunk by
-// itself (coalesced, before the one barrier) and scans its own, four consecutive counts
-// per thread.  One block over all chunks waited for its carry chunk after chunk: whole
-// binning (us), 500,000 atoms in 24,389 cells 41.4 -> 32.6, 256,000 26.1 -> 22.7, 32,000
-// 13.4 -> 12.8, an almost empty grid of 1,000,000 cells 581 -> 149 (there the counts read
-// again, m^2 / (2 kScanChunk) of them from L2, are most of the scan).
+// Exclusive scan of counts[0..m) into start[0..m] (start[m] = total), kScanChunk counts per
+// block, four consecutive ones per thread.
+// SUMMED = false, one launch, no flags between blocks: every block sums the counts before
+// its chunk by itself (coalesced, before the one barrier).  That is m^2 / (2 kScanChunk)
+// reads, so only up to kScanOnce counts; beyond, k_scan_sums and k_scan_tops leave every
+// chunk's prefix in its first place of start (SUMMED).
+// Whole binning of a sparse gas (us), one block over all chunks with its carry / every block
+// sums for itself / three launches: 32,768 cells 56 / 22 / -, 64,000 74 / 26 / 26, 125,000
+// 110 / 33.7 / 30.5, 1,000,000 603 / 150 / 86, 8,000,000 4,546 / 2,539 / 509, 16,777,216
+// 9,492 / 11,220 / 1,036.
 constexpr int32_t kScanChunk = 4 * kScanThreads;
+constexpr int32_t kScanOnce = 16 * kScanChunk;
 
+template <bool SUMMED>
 __global__ __launch_bounds__(kScanThreads) void k_scan(int32_t m, const int32_t *__restrict__ counts,
-                                                     int32_t *__restrict__ start) {
+                                                     int32_t *start) {
   constexpr int kWaves = kScanThreads / kWave;
   __shared__ int32_t wsum[kWaves], wbefore[kWaves];
   const int t = threadIdx.x;
@@ -73,10 +78,14 @@ __global__ __launch_bounds__(kScanThreads) void k_scan(int32_t m, const int32_t 
   int32_t v[4], part[4] = {0, 0, 0, 0};
 #pragma unroll
   for (int q = 0; q < 4; ++q) v[q] = c0 + 4 * t + q < m ? counts[c0 + 4 * t + q] : 0;
+  if constexpr (SUMMED) {
+    if (t == 0) part[0] = start[c0];
+  } else {
 #pragma unroll 2
-  for (int32_t c = t; c < c0; c += kScanChunk)
+    for (int32_t c = t; c < c0; c += kScanChunk)
 #pragma unroll
-    for (int q = 0; q < 4; ++q) part[q] += counts[c + q * kScanThreads];
+      for (int q = 0; q < 4; ++q) part[q] += counts[c + q * kScanThreads];
+  }
   const int32_t s = v[0] + v[1] + v[2] + v[3];
   const int32_t inc = wave_inclusive_scan(s);
   const int32_t bef = wave_inclusive_scan(part[0] + part[1] + part[2] + part[3]);
@@ -94,6 +103,53 @@ __global__ __launch_bounds__(kScanThreads) void k_scan(int32_t m, const int32_t 
     if (c < m) start[c] = run;
     run += v[q];
     if (c == m - 1) start[m] = run;
+  }
+}
+
+// The sum of every chunk into its first place of start.
+__global__ __launch_bounds__(kScanThreads) void k_scan_sums(int32_t m,
+                                                          const int32_t *__restrict__ counts,
+                                                          int32_t *__restrict__ start) {
+  constexpr int kWaves = kScanThreads / kWave;
+  __shared__ int32_t wsum[kWaves];
+  const int t = threadIdx.x;
+  const int32_t c0 = blockIdx.x * kScanChunk;
+  int32_t s = 0;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) s += c0 + 4 * t + q < m ? counts[c0 + 4 * t + q] : 0;
+  const int32_t inc = wave_inclusive_scan(s);
+  if ((t & (kWave - 1)) == kWave - 1) wsum[t / kWave] = inc;
+  __syncthreads();
+  if (t != 0) return;
+  s = 0;
+#pragma unroll
+  for (int k = 0; k < kWaves; ++k) s += wsum[k];
+  start[c0] = s;
+}
+
+// Those sums replaced by their exclusive prefix sums, one block, a run of chunks per thread.
+__global__ __launch_bounds__(kScanThreads) void k_scan_tops(int32_t nchunks,
+                                                          int32_t *__restrict__ start) {
+  constexpr int kWaves = kScanThreads / kWave;
+  __shared__ int32_t wsum[kWaves];
+  const int t = threadIdx.x;
+  const int lane = t & (kWave - 1), w = t / kWave;
+  const int32_t per = (nchunks + kScanThreads - 1) / kScanThreads;
+  const int32_t a = t * per < nchunks ? t * per : nchunks;
+  const int32_t b = a + per < nchunks ? a + per : nchunks;
+  int32_t s = 0;
+#pragma unroll 8
+  for (int32_t c = a; c < b; ++c) s += start[(int64_t)c * kScanChunk];
+  const int32_t inc = wave_inclusive_scan(s);
+  if (lane == kWave - 1) wsum[w] = inc;
+  __syncthreads();
+  int32_t run = inc - s;
+#pragma unroll
+  for (int k = 0; k < kWaves; ++k) run += k < w ? wsum[k] : 0;
+  for (int32_t c = a; c < b; ++c) {
+    const int32_t v = start[(int64_t)c * kScanChunk];
+    start[(int64_t)c * kScanChunk] = run;
+    run += v;
   }
 }
 
@@ -163,7 +219,14 @@ inline unsigned blocks_for(int64_t n, int threads) {
 
 // start[0..m] = exclusive prefix sums of counts[0..m) and their total.
 void launch_scan(int32_t m, const int32_t *counts, int32_t *start, hipStream_t st) {
-  k_scan<<<blocks_for(m, kScanChunk), kScanThreads, 0, st>>>(m, counts, start);
+  const unsigned nb = blocks_for(m, kScanChunk);
+  if (m <= kScanOnce) {
+    k_scan<false><<<nb, kScanThreads, 0, st>>>(m, counts, start);
+  } else {
+    k_scan_sums<<<nb, kScanThreads, 0, st>>>(m, counts, start);
+    k_scan_tops<<<1, kScanThreads, 0, st>>>((int32_t)nb, start);
+    k_scan<true><<<nb, kScanThreads, 0, st>>>(m, counts, start);
+  }
 }
 
 size_t bin_workspace(int64_t n, int64_t ncells) {

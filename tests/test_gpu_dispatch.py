@@ -143,3 +143,40 @@ def test_spme_droplet_uses_the_chip(dev):
          (torch.empty(b, dtype=torch.uint8, device=dev)
           for b in (ops.workspace_bytes(ops.OP_SPME, n, ncells=npts), _spme_direct_bytes(n, npts)))]
     assert t[0] <= 2.0 * t[1], t
+
+
+@pytest.mark.parametrize("cells", [(40, 40, 40), (41, 40, 40), (64, 64, 64), (101, 103, 107),
+                                   (256, 256, 256)])
+def test_bin_starts_of_sparse_grids(dev, cells):
+    """Row starts and order on both sides of 65,536 cells, where the scan changes form,
+    and over several chunks per thread of its middle pass."""
+    import torch
+    from paper_2109_09056_amd import ops
+    L = 2.8 * 1.001 * np.array(cells, float)
+    n = 7000
+    x = np.random.default_rng(cells[0]).uniform(0, 1, (n, 3)) * L
+    x[: n // 2] *= 0.01  # most of the first cells crowded, most cells empty
+    _, _, _, ids, cs = ops.bin(L, 2.8, torch.as_tensor(x, device=dev))
+    assert tuple(ops.grid(L, 2.8)) == cells
+    c = np.minimum(np.floor(x / (L / cells)).astype(np.int64), np.array(cells) - 1)
+    cell = (c[:, 2] * cells[1] + c[:, 1]) * cells[0] + c[:, 0]
+    want = np.lexsort((np.arange(n), cell))
+    assert np.array_equal(ids.cpu().numpy(), want)
+    starts = np.concatenate([[0], np.cumsum(np.bincount(cell, minlength=int(np.prod(cells))))])
+    assert np.array_equal(cs.cpu().numpy(), starts)
+
+
+def test_bin_work_is_linear_in_the_cells(dev):
+    """Eight times the cells may take at most sixteen times as long (a scan that sums all
+    counts before each chunk took 37 times)."""
+    import torch
+    from paper_2109_09056_amd import ops
+    t = []
+    for m in (128, 256):
+        L = np.full(3, 2.81 * m)
+        x = torch.rand(1000, 3, dtype=torch.float64, device=dev) * L[0]
+        out = ops.bin(L, 2.8, x)
+        ws = torch.empty(ops.workspace_bytes(ops.OP_BIN, 1000, ncells=m ** 3), dtype=torch.uint8,
+                         device=dev)
+        t.append(_milliseconds(lambda: ops.bin(L, 2.8, x, out=out[:4], cell_start=out[4], ws=ws)))
+    assert t[1] <= 16.0 * t[0], t
