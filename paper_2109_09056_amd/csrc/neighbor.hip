@@ -19,6 +19,7 @@
 // Cells with more candidates than the register slots hold fall back to
 // reading candidates from global memory per home atom.
 #include "common.h"
+#include "stencil.h"
 
 namespace ljmd {
 
@@ -34,7 +35,8 @@ namespace {
 // tiled lists (us), standard -> dense, 864 atoms (27 cells) 59.0 -> 16.7, 2,048 59.3 ->
 // 17.1, 4,000 69.6 -> 18.4, 13,500 (mean stencil of 11.1 slots, some cells above 12)
 // 65.8 -> 21.0; where the standard shape holds all, the dense one costs 20 %
-// (110,447 atoms 56.1 -> 68.5).
+// (110,447 atoms 56.1 -> 68.5), on the smallest grids 5 % (256 and 500 atoms, 8 cells, half
+// lists 9.8 -> 10.3 and 17.0 -> 17.6).
 constexpr int kSlots = 12;
 constexpr int kRowCap = 128;
 constexpr int kDenseSlots = 16;
@@ -788,7 +790,7 @@ void launch_mode(const GridK &g, const BoxK &b, double rl2, bool half, int64_t n
                  const int32_t *cell_start, const BuildOut &o, int32_t *max_count,
                  hipStream_t st) {
   const int ns = build_split(g.ncells);
-  const bool few = 27 * n <= (int64_t)g.ncells * kStandardCandidates;
+  const bool few = mean_stencil_within(g.nc, n, kStandardCandidates);
   if (few && (MODE != kTiled || o.maxn <= kRowCap)) {
     if (half)
       launch_shape<true, kSlots, kRowCap, MODE>(g, b, rl2, x, cell_start, o, max_count, ns, st);
