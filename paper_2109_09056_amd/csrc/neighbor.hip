@@ -47,6 +47,13 @@ constexpr int64_t kStandardCandidates = (kSlots - 1) * kWave;
 // atoms 189.4 -> 171.2 us (full list), 159.3 -> 143.6 (half), 362.6 -> 261.3 (dense
 // shape, 512,000 particles); batches that end at multiples of 8 atoms 174.1 / 145.8 / 265.6.
 constexpr int kBatch = 8;
+// Grids of at least this many cells (and so no split cells) have code for 2 and 4 (dense: 6
+// and 8) slots too, for gases; smaller ones, whose launches are mostly instruction fetch, take
+// the next larger.  With / without that code, two launches apart (us): 200,000 atoms at
+// density 0.02, 0.05, 0.1, 0.3 (142,000 to 29,800 cells) 230 / 246, 167 / 181, 119 / 130,
+// 72.8 / 79.4; 20,000 at 0.1 (8,000 cells) 30.7 / 29.3, at 0.2 (4,096) 30.0 / 26.6, at 0.05
+// (17,576) 37.4 / 37.5.
+constexpr unsigned kFewSlotGrid = 16384;
 constexpr int kFlushRows = kWave / kBatch;  // list rows of a batch written per store instruction
 // LDS row stride ROWCAP + 1 (odd): lanes reading entry k of different rows hit distinct banks
 
@@ -470,9 +477,10 @@ __device__ __forceinline__ bool build_quant(const BoxK &b, const QuantK &q, cons
   const int lane = threadIdx.x & (kWave - 1);
   int32_t qxy[SLOTS], qz[SLOTS], qj[SLOTS];
   bool good = true;
-  // Slots are staged in groups of four, the loads of a group in flight together; a
-  // lane's candidate numbers grow by 64 per slot, so its range is found from the last one.
-  constexpr int kGroup = 4;
+  // Slots are staged in pairs, the loads of a pair in flight together (fours take as long
+  // in a liquid and 4 to 7 % longer in a gas); a lane's candidate numbers grow by 64 per
+  // slot, so its range is found from the last one.
+  constexpr int kGroup = 2;
   int sr = 0;
 #pragma unroll
   for (int r0 = 0; r0 < SLOTS; r0 += kGroup) {
@@ -527,10 +535,15 @@ __device__ __forceinline__ bool build_quant(const BoxK &b, const QuantK &q, cons
     if (rs[sr] <= h0 && h0 < rs[sr] + (pre[sr + 1] - pre[sr])) tc = pre[sr] + (h0 - rs[sr]);
   tc = __builtin_amdgcn_readfirstlane(tc);
   // the code for the fewest slots that hold the stencil: no test of every slot's number
+  const bool few = gridDim.x >= kFewSlotGrid;
 #define LJMD_ROWS(NS)                                                                          \
   quant_rows<HALF, BUF, NS, SLOTS, ROWCAP, MODE>(b, q, cc, rl2, x, h0, h1, tc, qxy, qz, qj, o, \
                                                  rowbuf, rowcnt, maxc)
-  if (nslot <= SLOTS - 6)
+  if (few && nslot <= SLOTS - 10)
+    LJMD_ROWS(SLOTS - 10);
+  else if (few && nslot <= SLOTS - 8)
+    LJMD_ROWS(SLOTS - 8);
+  else if (nslot <= SLOTS - 6)
     LJMD_ROWS(SLOTS - 6);
   else if (nslot <= SLOTS - 4)
     LJMD_ROWS(SLOTS - 4);
@@ -593,9 +606,14 @@ __device__ __forceinline__ void fill_from_hits(int32_t h0, int32_t h1, int32_t t
     qj[r] = rs[sr] + (tt - pre[sr]);
   }
   const bool room = o.offsets[h1] <= o.cap;  // uniform
+  const bool few = gridDim.x >= kFewSlotGrid;
 #define LJMD_FILL(NS) \
   room ? fill_rows<NS, true>(qj, h0, h1, o) : fill_rows<NS, false>(qj, h0, h1, o)
-  if (nslot <= SLOTS - 6)
+  if (few && nslot <= SLOTS - 10)
+    LJMD_FILL(SLOTS - 10);
+  else if (few && nslot <= SLOTS - 8)
+    LJMD_FILL(SLOTS - 8);
+  else if (nslot <= SLOTS - 6)
     LJMD_FILL(SLOTS - 6);
   else if (nslot <= SLOTS - 4)
     LJMD_FILL(SLOTS - 4);

@@ -180,3 +180,50 @@ def test_bin_work_is_linear_in_the_cells(dev):
                          device=dev)
         t.append(_milliseconds(lambda: ops.bin(L, 2.8, x, out=out[:4], cell_start=out[4], ws=ws)))
     assert t[1] <= 16.0 * t[0], t
+
+
+@pytest.mark.parametrize("kind", ["full", "half"])
+@pytest.mark.parametrize("maxn", [128, 400])
+@pytest.mark.parametrize("nc", [25, 26])
+def test_lists_of_gases_on_large_grids(dev, orc, kind, maxn, nc):
+    """Tiled and compressed lists on both sides of 16,384 cells (15,625 and 17,576), where
+    the build has code for stencils of few slots: a gas of one or two, with clumps that bring
+    every slot count up to the unstaged path, both build shapes; row by row against the
+    oracle's lists, the compressed rows with and without the noted hits."""
+    import torch
+    from helpers import decode_rows
+    from paper_2109_09056_amd import _lib, ops
+    rl = 2.8
+    L = np.full(3, nc * rl * 1.0005)
+    g = np.random.default_rng(nc + maxn)
+    clumps = [c + rl * g.uniform(-1.2, 1.2, (m, 3))
+              for c, m in zip(g.uniform(0, 1, (16, 3)) * L, 60 * np.arange(1, 17))]
+    x = np.mod(np.concatenate([g.uniform(0, 1, (12000, 3)) * L] + clumps), L)
+    n, T = len(x), _t(dev)
+    k = ops.FULL if kind == "full" else ops.HALF
+    xs, _, _, ids, cs = ops.bin(L, rl, T(x))
+    order = ids.cpu().numpy()
+    off_o, nbr_o = orc.neighbor_lists(x[order], L, rl)
+    want = [np.sort(nbr_o[a:b]) for a, b in zip(off_o[:-1], off_o[1:])]
+    if kind == "half":
+        want = [w[w > i] for i, w in enumerate(want)]
+    nbr, nnbr, most = ops.build_neighbors(L, rl, k, xs, cs, maxn)
+    assert int(most.item()) == max(map(len, want))
+    rows = decode_rows(nbr.cpu().numpy(), nnbr.cpu().numpy(), maxn)
+    for row, w in zip(rows, want):
+        if len(w) <= maxn:
+            assert np.array_equal(np.sort(row), w)
+        else:
+            assert len(row) == maxn and np.isin(row, w).all()
+    for nbytes in (ops.workspace_bytes(ops.OP_BUILD_CSR, n),
+                   -(-4 * n // 256) * 256 + ops.workspace_bytes(ops.OP_CSR, n)):
+        off = torch.empty(n + 1, dtype=torch.int64, device=dev)
+        csr = torch.full((sum(map(len, want)),), -7, dtype=torch.int32, device=dev)
+        ws = torch.empty(nbytes, dtype=torch.uint8, device=dev)
+        _lib.check(_lib.load().ljmd_build_neighbors_csr(
+            _lib.make_box(L), rl, k, n, xs.data_ptr(), cs.data_ptr(), off.data_ptr(),
+            csr.data_ptr(), csr.numel(), ws.data_ptr(), nbytes,
+            torch.cuda.current_stream(dev).cuda_stream), "build")
+        assert np.array_equal(np.diff(off.cpu().numpy()), [len(w) for w in want])
+        c = np.split(csr.cpu().numpy(), off.cpu().numpy()[1:-1])
+        assert all(np.array_equal(np.sort(a), w) for a, w in zip(c, want))
