@@ -712,8 +712,11 @@ __global__ __launch_bounds__(ATOMS * TEAM) void k_force_half(ForceArgs a) {
 // groups first, the partial group gathers only live slots), then the team's
 // sums are combined by a butterfly over the team (both lanes of every exchange
 // add the same two numbers, so every lane ends with the same, order-fixed sum).
-// 500,000 atoms with energies (us): teams of four 96.8 -> 83.5 with masked groups
-// and the sums by row; of one and two those groups cost 70 % and 16 % and stay out.
+// Teams of four with energies take masked groups throughout: 500,000 atoms 91.6 -> 85.4 us.
+// Elsewhere those cost (us, masked and ungated gathers -> this): teams of 8 and 16 without
+// energies at 500,000 atoms 73.6 -> 64.5 and 92.9 -> 74.2 (two types 99.8 -> 86.2, 127 ->
+// 98.7), of one with two types 165 -> 159; a gas of 400,000 atoms at density 0.05, teams
+// of 1, 2, 4, 8, 16: 15.4 -> 14.5, 14.7 -> 13.4, 16.4 -> 12.7, 25.6 -> 17.6, 43.7 -> 29.8.
 // Each lane walks its entries in row order, as k_force_full does: with its team
 // of four the two kernels give bitwise the same forces and per-atom energies, and so
 // does a team of two, whose lanes keep their even and their odd entries -- the
@@ -751,6 +754,7 @@ __global__ __launch_bounds__(kCsrThreads) void k_force_csr(ForceArgs a,
     const int64_t r0 = off[i], r1 = off[i + 1];
     const int32_t cnt = r1 - r0 > t ? (int32_t)((r1 - r0 - t + TEAM - 1) / TEAM) : 0;
     const int32_t *row = csr + r0 + t;
+    constexpr bool kMaskedLoop = TEAM == 4 && EV;
     auto walk = [&](auto wrap) {
       constexpr bool W = decltype(wrap)::value;
       const int32_t *rp = row;
@@ -762,18 +766,22 @@ __global__ __launch_bounds__(kCsrThreads) void k_force_csr(ForceArgs a,
         double xj[U], yj[U], zj[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-          load_pos<1, WIDE>(a.x, j[u], a.n, xj[u], yj[u], zj[u]);
-          tj[u] = T1 ? 0 : a.type[j[u]];
+          if (!M || kMaskedLoop || k + u < cnt) {
+            load_pos<1, WIDE>(a.x, j[u], a.n, xj[u], yj[u], zj[u]);
+            tj[u] = T1 ? 0 : a.type[j[u]];
+          } else {
+            xj[u] = xi, yj[u] = yi, zj[u] = zi, tj[u] = 0;
+          }
         }
 #pragma unroll
         for (int u = 0; u < U; ++u)
           add_pair<MIXED, T1, EV, W>(a, xi, yi, zi, xj[u], yj[u], zj[u], tj[u], !M || k + u < cnt,
                                      ti, c1, tab, TEAM == 2 && u % 2 ? odd : s);
       };
-      if constexpr (TEAM >= 4) {  // masked groups only, as walk_row
+      if constexpr (kMaskedLoop) {  // masked groups only, as walk_row
 #pragma unroll 1
         for (int32_t k = 0; k < cnt; k += U, rp += U * TEAM) group(k, std::true_type{});
-      } else {  // whole groups and one masked: their longer rows gain more from it
+      } else {  // whole groups, then a partial one that gathers live slots only
         const int32_t whole = cnt - cnt % U;
         int32_t k = 0;
         for (; k < whole; k += U, rp += U * TEAM) group(k, std::false_type{});

@@ -227,3 +227,39 @@ def test_lists_of_gases_on_large_grids(dev, orc, kind, maxn, nc):
         assert np.array_equal(np.diff(off.cpu().numpy()), [len(w) for w in want])
         c = np.split(csr.cpu().numpy(), off.cpu().numpy()[1:-1])
         assert all(np.array_equal(np.sort(a), w) for a, w in zip(c, want))
+
+
+@pytest.mark.parametrize("ntypes", [1, 2])
+@pytest.mark.parametrize("rows", ["short", "long"])
+def test_csr_teams_over_ragged_rows(dev, ntypes, rows):
+    """Every team size, with and without energies, over rows of every length (0 to about 20
+    entries, and to 90): teams of two and four bitwise the tiled kernel's forces, the others
+    the same pairs in another order, so within (row length) roundings of the largest term."""
+    import torch
+    from paper_2109_09056_amd import md, ops
+    n = 3001
+    L = np.full(3, 40.0 if rows == "short" else 19.0)
+    g = np.random.default_rng(ntypes)
+    m = int(np.ceil(n ** (1.0 / 3.0)))
+    sites = np.stack(np.meshgrid(*[np.arange(m)] * 3, indexing="ij"), -1).reshape(-1, 3)
+    x = (sites[g.permutation(m ** 3)[:n]] + 0.5 + g.uniform(-0.1, 0.1, (n, 3))) * (L / m)
+    x[: n // 3] = 0.5 * x[: n // 3] + 0.25 * L  # denser in the middle
+    T = _t(dev)
+    xs, _, ts, _, cs = ops.bin(L, 2.8, T(x), None, T(g.integers(0, ntypes, n), torch.int32))
+    nl = md.NeighborList(L, 2.8, ops.FULL, device=dev).build(xs, cs)
+    off, csr = ops.list_to_csr(nl.nbr, nl.nnbr, nl.maxn)
+    p = ntypes * (ntypes + 1) // 2
+    for P in (ops.FP64, ops.MIXED):
+        a = (L, P, 2.5, T([1.0, 0.9, 1.1][:p]), T([0.4, 0.38, 0.42][:p]), xs, ts)
+        F, e, ev = (t.cpu().numpy() for t in ops.compute_forces(
+            *a[:2], ops.FULL, *a[2:], nl.nbr, nl.nnbr, nl.maxn))
+        big = np.abs(F).max()
+        for team in (1, 2, 4, 8, 16):
+            for want in (True, False):
+                F2, e2, ev2 = ops.compute_forces_csr(*a, off, csr, team=team, want_energy=want)
+                F2 = F2.cpu().numpy()
+                tol = 0.0 if team in (2, 4) else 200 * 2.0 ** -53 * 100 * big
+                assert np.abs(F2 - F).max() <= tol, (team, want)
+                if want:
+                    assert np.abs(e2.cpu().numpy() - e).max() <= tol * 2.5
+                    assert np.abs(ev2.cpu().numpy() - ev).max() <= 1e-11 * np.abs(ev).max()
