@@ -24,15 +24,20 @@ namespace {
 
 constexpr int kThreads = 128;  // atoms per block
 constexpr int kWaves = kThreads / kWave;
-// One or two types: four lanes per atom with two slots per group and lane.  Bound by the
-// gathers (x_j and g_j in two loads each, and the type, gathered with them instead of
-// after the cutoff test).  256,000 atoms two types FP64 / 500,000 one type mixed (us): two
-// lanes with 3 slots in whole and partial groups 93.8 / 139.6; masked groups and two
-// lanes with 3 slots 92.7 / 145.7; four lanes with 3, 2, 1 slots 84.9 / 131.9, 83.1 / 131.5,
-// 88.0 / 140.1.  32,000 two types mixed: 19.4 -> 16.1.  More types: one lane, 3 slots.
+// Bound by the gathers (x_j and g_j in two loads each, and the type, gathered with them
+// instead of after the cutoff test).
+// One or two types: masked groups, four lanes per atom with two slots per group and lane.
+// 256,000 atoms two types FP64 / 500,000 one type mixed (us): two lanes with 3 slots in whole
+// and partial groups 93.8 / 139.6; masked groups and two lanes with 3 slots 92.7 / 145.7; four
+// lanes with 3, 2, 1 slots 84.9 / 131.9, 83.1 / 131.5, 88.0 / 140.1.
+// More types: one lane, whole groups of four slots and a partial one that gathers live slots
+// only.  32,000 / 131,072 / 256,000 / 500,000 atoms, three types (us): masked groups of three
+// 46.8 / 74.5 / 134.8 / 252, whole ones of two, three, four 47.9 / 78.9 / 136.0 / 255, 47.5 / 74.1
+// / 130.4 / 242, 44.1 / 73.4 / 127.7 / 240; with the type after the cutoff test 48.6 / 81.3 /
+// 127.3 / 245.
 constexpr int kTeam = 4;
 constexpr int kSlots = 2;
-constexpr int kManySlots = 3;
+constexpr int kManySlots = 4;
 
 struct BwdArgs {
   BoxK b;
@@ -196,33 +201,48 @@ __global__ __launch_bounds__(kThreads * TEAM) void k_vjp(BwdArgs a) {
         }
       }
     };
-    // Masked groups of U slots, as in the forces: the U index loads, then the gathers of
-    // x_j, g_j and the type, then the U entries; slots beyond cnt repeat the lane's first
-    // entry.  Row order throughout, so the sums match one slot at a time.
+    // Groups of U slots: the U index loads, then the gathers of x_j, g_j and the type, then
+    // the U entries.  Row order throughout, so the sums match one slot at a time.
     auto walk = [&](auto wrap) {
       constexpr int U = TT == 0 ? kManySlots : kSlots;
+      constexpr bool kMaskedLoop = TT != 0;
       constexpr int kStep = TEAM * kWave;  // ints between this lane's consecutive entries
       const int32_t *rp = row;
-#pragma unroll 1
-      for (int32_t k = 0; k < cnt; k += U, rp += U * kStep) {
+      auto group = [&](int32_t k, auto masked) {  // masked: slots beyond cnt repeat the first
+        constexpr bool M = decltype(masked)::value;
         int32_t jj[U];
         int tj[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) jj[u] = rp[(k + u < cnt ? u : 0) * kStep];
+        for (int u = 0; u < U; ++u) jj[u] = rp[(!M || k + u < cnt ? u : 0) * kStep];
         double xj[U][3], gj[U][3];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-          const double *px = pos_of<WIDE>(a.x, jj[u]);
-          const double *pg = pos_of<WIDE>(a.g, jj[u]);
+          if (!M || kMaskedLoop || k + u < cnt) {
+            const double *px = pos_of<WIDE>(a.x, jj[u]);
+            const double *pg = pos_of<WIDE>(a.g, jj[u]);
 #pragma unroll
-          for (int q = 0; q < 3; ++q) {
-            xj[u][q] = px[q];
-            gj[u][q] = pg[q];
+            for (int q = 0; q < 3; ++q) {
+              xj[u][q] = px[q];
+              gj[u][q] = pg[q];
+            }
+            tj[u] = TT == 1 ? 0 : a.type[jj[u]];
+          } else {
+#pragma unroll
+            for (int q = 0; q < 3; ++q) xj[u][q] = gj[u][q] = 0.0;
+            tj[u] = 0;
           }
-          tj[u] = TT == 1 ? 0 : a.type[jj[u]];
         }
 #pragma unroll
-        for (int u = 0; u < U; ++u) entry(wrap, tj[u], xj[u], gj[u], k + u < cnt);
+        for (int u = 0; u < U; ++u) entry(wrap, tj[u], xj[u], gj[u], !M || k + u < cnt);
+      };
+      if constexpr (kMaskedLoop) {
+#pragma unroll 1
+        for (int32_t k = 0; k < cnt; k += U, rp += U * kStep) group(k, std::true_type{});
+      } else {
+        const int32_t whole = cnt - cnt % U;
+        int32_t k = 0;
+        for (; k < whole; k += U, rp += U * kStep) group(k, std::false_type{});
+        if (k < cnt) group(k, std::true_type{});
       }
     };
     if (interior)

@@ -263,3 +263,37 @@ def test_csr_teams_over_ragged_rows(dev, ntypes, rows):
                 if want:
                     assert np.abs(e2.cpu().numpy() - e).max() <= tol * 2.5
                     assert np.abs(ev2.cpu().numpy() - ev).max() <= 1e-11 * np.abs(ev).max()
+
+
+def _ragged(n, L, seed):
+    """n atoms of a jittered lattice with sites taken out, the first third of them drawn in
+    towards the middle: rows from empty to several times the mean."""
+    g = np.random.default_rng(seed)
+    m = int(np.ceil(n ** (1.0 / 3.0)))
+    sites = np.stack(np.meshgrid(*[np.arange(m)] * 3, indexing="ij"), -1).reshape(-1, 3)
+    x = (sites[g.permutation(m ** 3)[:n]] + 0.5 + g.uniform(-0.1, 0.1, (n, 3))) * (L / m)
+    x[: n // 3] = 0.5 * x[: n // 3] + 0.25 * L
+    return x
+
+
+@pytest.mark.parametrize("edge", [20.0, 40.0])
+@pytest.mark.parametrize("ntypes", [3, 8])
+def test_vjp_of_many_types_over_ragged_rows(dev, orc, ntypes, edge):
+    """VJP with three and eight types over rows of every remainder of a group of slots,
+    against the oracle's (1e-12 of the largest)."""
+    import torch
+    from paper_2109_09056_amd import md, ops
+    n, L = 1500, np.full(3, edge)
+    x, g = _ragged(n, L, ntypes), np.random.default_rng(ntypes)
+    ty = g.integers(0, ntypes, n)
+    p = ntypes * (ntypes + 1) // 2
+    eps, sig = np.linspace(0.8, 1.2, p), np.linspace(0.35, 0.45, p)
+    T = _t(dev)
+    xs, _, ts, ids, cs = ops.bin(L, 2.8, T(x), None, T(ty, torch.int32))
+    nl = md.NeighborList(L, 2.8, ops.FULL, device=dev).build(xs, cs)
+    c = g.normal(size=(n, 3))
+    gx, ge, gs = ops.force_backward(L, ops.FP64, 2.5, T(eps), T(sig), xs, ts, nl.nbr, nl.nnbr,
+                                    nl.maxn, ops.gather_rows(ids, T(c)))
+    want = orc.force_vjp(x, L, 2.5, c, eps, sig, ty.astype(np.int32))
+    for a, b in zip((ops.scatter_rows(ids, gx), ge, gs), want):
+        assert np.abs(a.cpu().numpy() - b).max() <= 1e-12 * np.abs(b).max()
