@@ -26,10 +26,15 @@ constexpr int kThreads = 128;  // atoms per block
 constexpr int kWaves = kThreads / kWave;
 // Bound by the gathers (x_j and g_j in two loads each, and the type, gathered with them
 // instead of after the cutoff test).
-// One or two types: masked groups, four lanes per atom with two slots per group and lane.
-// 256,000 atoms two types FP64 / 500,000 one type mixed (us): two lanes with 3 slots in whole
-// and partial groups 93.8 / 139.6; masked groups and two lanes with 3 slots 92.7 / 145.7; four
-// lanes with 3, 2, 1 slots 84.9 / 131.9, 83.1 / 131.5, 88.0 / 140.1.
+// One or two types: masked groups, four lanes per atom with two slots per group and lane;
+// above kShortAtoms atoms and where the rows hold at most kShortRow entries (gases), two
+// lanes with three, as half of four lanes' slots would be empty.  256,000 atoms two types FP64 / 500,000 one type mixed
+// (us): two lanes with 3 slots in whole and partial groups 93.8 / 139.6; masked groups and
+// two lanes with 3 slots 92.7 / 145.7; four lanes with 3, 2, 1 slots 84.9 / 131.9, 83.1 /
+// 131.5, 88.0 / 140.1.  Gases of 200,000 atoms at density 0.05 and 0.3, of 400,000 at 0.05,
+// one type / two, four lanes -> two: 17.0 / 21.0 -> 15.2 / 18.5, 36.0 / 43.4 -> 35.2 / 42.3,
+// 31.5 / 39.7 -> 24.9 / 31.9 (row capacities of 24 and 64; a liquid's is about 100); of 20,000
+// at 0.05, which leave the chip half idle, 7.2 / 8.1 -> 7.5 / 8.6.
 // More types: one lane, whole groups of four slots and a partial one that gathers live slots
 // only.  32,000 / 131,072 / 256,000 / 500,000 atoms, three types (us): masked groups of three
 // 46.8 / 74.5 / 134.8 / 252, whole ones of two, three, four 47.9 / 78.9 / 136.0 / 255, 47.5 / 74.1
@@ -37,6 +42,10 @@ constexpr int kWaves = kThreads / kWave;
 // 127.3 / 245.
 constexpr int kTeam = 4;
 constexpr int kSlots = 2;
+constexpr int32_t kShortRow = 64;
+constexpr int32_t kShortAtoms = 65536;
+constexpr int kShortTeam = 2;
+constexpr int kShortSlots = 3;
 constexpr int kManySlots = 4;
 
 struct BwdArgs {
@@ -204,7 +213,7 @@ __global__ __launch_bounds__(kThreads * TEAM) void k_vjp(BwdArgs a) {
     // Groups of U slots: the U index loads, then the gathers of x_j, g_j and the type, then
     // the U entries.  Row order throughout, so the sums match one slot at a time.
     auto walk = [&](auto wrap) {
-      constexpr int U = TT == 0 ? kManySlots : kSlots;
+      constexpr int U = TT == 0 ? kManySlots : (TEAM == kShortTeam ? kShortSlots : kSlots);
       constexpr bool kMaskedLoop = TT != 0;
       constexpr int kStep = TEAM * kWave;  // ints between this lane's consecutive entries
       const int32_t *rp = row;
@@ -371,8 +380,13 @@ int launch_backward(const BoxK &b, int precision, double rc, int32_t ntypes, con
     else                                                                     \
       k_vjp<M, TT, true, TEAM><<<nblk, kThreads * TEAM, 0, st>>>(a);        \
   } while (0)
-  if (ntypes == 1) {
+  const bool few = maxn <= kShortRow && n > kShortAtoms;
+  if (ntypes == 1 && few) {
+    if (mixed) LJMD_VJP(true, 1, kShortTeam); else LJMD_VJP(false, 1, kShortTeam);
+  } else if (ntypes == 1) {
     if (mixed) LJMD_VJP(true, 1, kTeam); else LJMD_VJP(false, 1, kTeam);
+  } else if (ntypes == 2 && few) {
+    if (mixed) LJMD_VJP(true, 2, kShortTeam); else LJMD_VJP(false, 2, kShortTeam);
   } else if (ntypes == 2) {
     if (mixed) LJMD_VJP(true, 2, kTeam); else LJMD_VJP(false, 2, kTeam);
   } else {

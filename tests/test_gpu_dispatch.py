@@ -297,3 +297,32 @@ def test_vjp_of_many_types_over_ragged_rows(dev, orc, ntypes, edge):
     want = orc.force_vjp(x, L, 2.5, c, eps, sig, ty.astype(np.int32))
     for a, b in zip((ops.scatter_rows(ids, gx), ge, gs), want):
         assert np.abs(a.cpu().numpy() - b).max() <= 1e-12 * np.abs(b).max()
+
+
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+@pytest.mark.parametrize("ntypes", [1, 2])
+def test_vjp_on_both_sides_of_the_short_row_line(dev, ntypes, prec):
+    """The same rows in lists of capacity 64 (two lanes per atom beyond 65,536 atoms) and 65
+    (four, which other tests hold against the oracle).  The terms are the same numbers in
+    either: a row's sum of at most 64 differs by 64 roundings of its terms, a parameter's
+    by as many as it has terms."""
+    import torch
+    from paper_2109_09056_amd import ops
+    n, L = 66001, np.full(3, 110.0)
+    x, g = _ragged(n, L, ntypes), np.random.default_rng(ntypes)
+    p = ntypes * (ntypes + 1) // 2
+    T = _t(dev)
+    xs, _, ts, _, cs = ops.bin(L, 2.8, T(x), None, T(g.integers(0, ntypes, n), torch.int32))
+    c = T(g.normal(size=(n, 3)))
+    out = []
+    for maxn in (64, 65):
+        nbr, nnbr, most = ops.build_neighbors(L, 2.8, ops.FULL, xs, cs, maxn)
+        assert int(most.item()) <= 64
+        out.append([t.cpu().numpy() for t in ops.force_backward(
+            L, ops.FP64 if prec == "fp64" else ops.MIXED, 2.5, T(np.linspace(0.8, 1.2, p)),
+            T(np.linspace(0.35, 0.45, p)), xs, ts, nbr, nnbr, maxn, c)])
+    (gx, ge, gs), (hx, he, hs) = out
+    u = 2.0 ** -53
+    assert np.abs(gx - hx).max() <= 2 * 64 * u * np.abs(hx).max()
+    assert np.abs(ge - he).max() <= 2 * 64 * n * u * np.abs(he).max()
+    assert np.abs(gs - hs).max() <= 2 * 64 * n * u * np.abs(hs).max()
