@@ -266,7 +266,8 @@ __device__ __forceinline__ void load_pos(const double *x, int32_t j, int64_t n, 
 // position and type, then the U pair evaluations, so several loads are in flight
 // per lane.  Slots beyond cnt repeat the lane's first entry and are masked: one
 // copy of the group's code instead of a whole and a partial one (a short launch
-// spends most of its time fetching instructions).  The type is gathered with the
+// spends most of its time fetching instructions).  GAS: their gathers are left out, as
+// they are most of the slots.  The type is gathered with the
 // position rather than after the cutoff test: no second round trip (two types,
 // 256,000 atoms: fused step 69.0 -> 62.2 us).  Slots are visited in row order, so
 // the sums are the same as one slot at a time.  WRAP = false skips the minimum
@@ -274,7 +275,7 @@ __device__ __forceinline__ void load_pos(const double *x, int32_t j, int64_t n, 
 // least rc from all box faces, where any pair closer than rc has the same raw and
 // minimum-image displacement, and any other pair has some |raw component| above
 // L/2 > rc and is rejected by the cutoff test either way.
-template <bool MIXED, bool T1, bool EV, int U, bool WRAP, bool WIDE, int TEAM, int V>
+template <bool MIXED, bool T1, bool EV, int U, bool WRAP, bool WIDE, int TEAM, int V, bool GAS>
 __device__ __forceinline__ void walk_row(const ForceArgs &a, const int32_t *row, int32_t cnt,
                                          double xi, double yi, double zi, int ti,
                                          const Coef &c1, const double *tab, Acc &s) {
@@ -287,8 +288,12 @@ __device__ __forceinline__ void walk_row(const ForceArgs &a, const int32_t *row,
     double xj[U], yj[U], zj[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      load_pos<V, WIDE>(a.x, j[u], a.n, xj[u], yj[u], zj[u]);
-      tj[u] = T1 ? 0 : a.type[j[u]];
+      if (!GAS || k + u < cnt) {
+        load_pos<V, WIDE>(a.x, j[u], a.n, xj[u], yj[u], zj[u]);
+        tj[u] = T1 ? 0 : a.type[j[u]];
+      } else {
+        xj[u] = xi, yj[u] = yi, zj[u] = zi, tj[u] = 0;
+      }
     }
 #pragma unroll
     for (int u = 0; u < U; ++u)
@@ -360,7 +365,7 @@ __device__ void block_colsum(const double *__restrict__ p, int64_t rows, double 
 // Rows of partial sums stand in the order of the atoms (row = logical block), and
 // a 128-atom block adds its two 64-atom halves last: its row is bitwise the sum of
 // the two rows of 64-atom blocks, so the block size never shows in a result.
-template <bool MIXED, bool T1, bool EV, bool STEP, bool WIDE, int ATOMS, int V = 1>
+template <bool MIXED, bool T1, bool EV, bool STEP, bool WIDE, int ATOMS, int V = 1, bool GAS = false>
 __global__ __launch_bounds__(ATOMS * kTeam) void k_force_full(ForceArgs a) {
   static_assert(!STEP || V == 1, "the fused step works on [n][3] arrays");
   static_assert(kTeam == 4, "one component per lane");
@@ -413,11 +418,11 @@ __global__ __launch_bounds__(ATOMS * kTeam) void k_force_full(ForceArgs a) {
     const int32_t *row =
         a.nbr + (int64_t)(i >> 6) * a.maxn * kWave + (i & (kWave - 1)) + (int64_t)t * kWave;
     if (interior)
-      walk_row<MIXED, T1, EV, kSlots, false, WIDE, kTeam, V>(a, row, cnt, xi, yi, zi, ti, c1, tab,
-                                                             s);
+      walk_row<MIXED, T1, EV, kSlots, false, WIDE, kTeam, V, GAS>(a, row, cnt, xi, yi, zi, ti, c1,
+                                                                  tab, s);
     else
-      walk_row<MIXED, T1, EV, kSlots, true, WIDE, kTeam, V>(a, row, cnt, xi, yi, zi, ti, c1, tab,
-                                                            s);
+      walk_row<MIXED, T1, EV, kSlots, true, WIDE, kTeam, V, GAS>(a, row, cnt, xi, yi, zi, ti, c1,
+                                                                 tab, s);
     if constexpr (EV) add_xf(xi, yi, zi, s);
   }
   const double e_lane = s.e;
@@ -869,6 +874,13 @@ void launch_half(const ForceArgs &a, hipStream_t st) {
         <<<nb, kHalfAtoms * kHalfTeam, 0, st>>>(a);
 }
 
+// Forces without energies over rows of at most this many entries leave out the gathers of
+// absent slots (GAS).  One type / two (us), with them -> without: 200,000 atoms at density
+// 0.01 and 0.02 (capacity 20) 7.2 / 8.4 -> 6.3 / 7.1 and 7.7 / 9.3 -> 6.6 / 7.7, 400,000 at 0.02
+// 12.7 / 16.3 -> 11.2 / 13.4, at 0.05 (24) 14.9 / 19.1 -> 15.6 / 17.6, at 0.1 (40) 18.9 / 24.1
+// -> 20.8 / 23.6; a liquid of 500,000 (108) 72 / 97 -> 85 / 102.
+constexpr int32_t gas_row(bool t1) { return t1 ? 20 : 28; }
+
 // The full-list kernel in blocks of `atoms` (64 or 128) atoms.
 template <bool MIXED, bool T1, bool EV, bool STEP, int V = 1>
 void launch_full(const ForceArgs &a, int atoms, hipStream_t st) {
@@ -883,6 +895,13 @@ void launch_full(const ForceArgs &a, int atoms, hipStream_t st) {
     k_force_full<MIXED, T1, EV, STEP, false, kForceAtoms, V>
         <<<nblk, kForceAtoms * kTeam, 0, st>>>(a);
   } else {
+    if constexpr (V == 1 && !EV && !STEP) {
+      if (a.maxn <= gas_row(T1)) {
+        k_force_full<MIXED, T1, EV, STEP, false, kHalfRowAtoms, V, true>
+            <<<nblk, kHalfRowAtoms * kTeam, 0, st>>>(a);
+        return;
+      }
+    }
     k_force_full<MIXED, T1, EV, STEP, false, kHalfRowAtoms, V>
         <<<nblk, kHalfRowAtoms * kTeam, 0, st>>>(a);
   }

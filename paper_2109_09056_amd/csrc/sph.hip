@@ -113,9 +113,16 @@ __device__ __forceinline__ void disp(const SphArgs &a, double xi, double yi, dou
   }
 }
 
+// Rows of at most this many entries leave out the gathers of absent slots (GAS).  Density and
+// acceleration (us), with them -> without: 200,000 particles, row capacity 20 9.0 + 17.1 -> 8.4
+// + 15.1, 400,000 20 15.0 + 32.6 -> 13.7 + 28.1, 24 17.4 + 34.3 -> 16.8 + 28.9, 28 20.1 + 37.1 ->
+// 22.2 + 33.0; the fluid of 512,000 (140) 108 + 138 -> 127 + 154.
+constexpr int32_t kGasRowDensity = 24;
+constexpr int32_t kGasRow = 28;
+
 // Sum of w over lane t's entries of the row (cnt of them, kStep ints apart), in masked
-// groups of U: slots beyond cnt repeat the lane's first entry.
-template <bool WRAP, bool WIDE>
+// groups of U: slots beyond cnt repeat the group's first entry.
+template <bool WRAP, bool WIDE, bool GAS>
 __device__ __forceinline__ double density_row(const SphArgs &a, const int32_t *row, int32_t cnt,
                                               double xi, double yi, double zi) {
   constexpr int U = kSphUnroll;
@@ -129,10 +136,14 @@ __device__ __forceinline__ double density_row(const SphArgs &a, const int32_t *r
     double xj[U], yj[U], zj[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const double *p = pos_of<WIDE>(a.x, j[u]);
-      xj[u] = p[0];
-      yj[u] = p[1];
-      zj[u] = p[2];
+      if (!GAS || k + u < cnt) {
+        const double *p = pos_of<WIDE>(a.x, j[u]);
+        xj[u] = p[0];
+        yj[u] = p[1];
+        zj[u] = p[2];
+      } else {
+        xj[u] = xi, yj[u] = yi, zj[u] = zi;
+      }
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -144,7 +155,7 @@ __device__ __forceinline__ double density_row(const SphArgs &a, const int32_t *r
   return s;
 }
 
-template <bool WIDE, bool WANT_U>
+template <bool WIDE, bool WANT_U, bool GAS>
 __global__ __launch_bounds__(kSphThreads) void k_sph_density(SphArgs a) {
   __shared__ double red[kRedRows * kSphWaves];
   const int t = (int)threadIdx.x % kSphTeam;
@@ -166,10 +177,10 @@ __global__ __launch_bounds__(kSphThreads) void k_sph_density(SphArgs a) {
     const int32_t cnt = ctot > t ? (ctot - t + kSphTeam - 1) / kSphTeam : 0;
     const int32_t *row =
         a.nbr + (int64_t)(i >> 6) * a.maxn * kWave + (i & (kWave - 1)) + (int64_t)t * kWave;
-    s = interior ? density_row<false, WIDE>(a, row, cnt, xi, yi, zi)
-                 : density_row<true, WIDE>(a, row, cnt, xi, yi, zi);
+    s = interior ? density_row<false, WIDE, GAS>(a, row, cnt, xi, yi, zi)
+                 : density_row<true, WIDE, GAS>(a, row, cnt, xi, yi, zi);
   }
-  s = team_sum<kSphTeam>(s);  // both lanes of the team end with the same sum
+  s = team_sum<kSphTeam>(s);  // every lane of the team ends with the same sum
   double rho = 0.0;
   if (live) {
     rho = a.wnorm * (1.0 + s);  // self term: w(0) = 1
@@ -208,7 +219,7 @@ __device__ __forceinline__ void accel_pair(const SphArgs &a, const double4 &me, 
 }
 
 // Lane t's entries of the row in masked groups of U, as density_row.
-template <bool WRAP, bool WIDE>
+template <bool WRAP, bool WIDE, bool GAS>
 __device__ __forceinline__ void accel_row(const SphArgs &a, const int32_t *row, int32_t cnt,
                                           const double4 &me, double &ax, double &ay,
                                           double &az) {
@@ -221,7 +232,10 @@ __device__ __forceinline__ void accel_row(const SphArgs &a, const int32_t *row, 
     for (int u = 0; u < U; ++u) j[u] = row[(k + u < cnt ? u : 0) * kStep];
     double4 o[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) o[u] = *rec_of<WIDE>(a.xp, j[u]);
+    for (int u = 0; u < U; ++u) {
+      o[u] = me;
+      if (!GAS || k + u < cnt) o[u] = *rec_of<WIDE>(a.xp, j[u]);
+    }
 #pragma unroll
     for (int u = 0; u < U; ++u) accel_pair<WRAP, WIDE>(a, me, o[u], k + u < cnt, ax, ay, az);
   }
@@ -230,7 +244,7 @@ __device__ __forceinline__ void accel_row(const SphArgs &a, const int32_t *row, 
 // STEP: after the acceleration, the closing half kick of this step and the next
 // step's opening half kick and drift with wrap, per component exactly as the
 // integrator's fused kick-kick-drift (unit mass: the acceleration is F/m).
-template <bool WIDE, bool STEP>
+template <bool WIDE, bool STEP, bool GAS>
 __global__ __launch_bounds__(kSphThreads) void k_sph_accel(SphArgs a) {
   const int t = (int)threadIdx.x % kSphTeam;
   const int32_t i = xcd_block(blockIdx.x, gridDim.x) * kSphAtoms + (int)threadIdx.x / kSphTeam;
@@ -248,9 +262,9 @@ __global__ __launch_bounds__(kSphThreads) void k_sph_accel(SphArgs a) {
     const int32_t *row =
         a.nbr + (int64_t)(i >> 6) * a.maxn * kWave + (i & (kWave - 1)) + (int64_t)t * kWave;
     if (interior)
-      accel_row<false, WIDE>(a, row, cnt, me, ax, ay, az);
+      accel_row<false, WIDE, GAS>(a, row, cnt, me, ax, ay, az);
     else
-      accel_row<true, WIDE>(a, row, cnt, me, ax, ay, az);
+      accel_row<true, WIDE, GAS>(a, row, cnt, me, ax, ay, az);
   }
   ax = team_sum<kSphTeam>(ax);
   ay = team_sum<kSphTeam>(ay);
@@ -300,6 +314,21 @@ SphArgs make_args(const BoxK &b, double h, double mass, double c0, double rho0, 
   return a;
 }
 
+template <bool WANT_U>
+void launch_density(const SphArgs &a, unsigned nblk, hipStream_t st) {
+  if (a.n > kNarrowAtoms) k_sph_density<true, WANT_U, false><<<nblk, kSphThreads, 0, st>>>(a);
+  else if (a.maxn <= kGasRowDensity)
+    k_sph_density<false, WANT_U, true><<<nblk, kSphThreads, 0, st>>>(a);
+  else k_sph_density<false, WANT_U, false><<<nblk, kSphThreads, 0, st>>>(a);
+}
+
+template <bool STEP>
+void launch_accel(const SphArgs &a, unsigned nblk, hipStream_t st) {
+  if (a.n > kNarrowAtoms) k_sph_accel<true, STEP, false><<<nblk, kSphThreads, 0, st>>>(a);
+  else if (a.maxn <= kGasRow) k_sph_accel<false, STEP, true><<<nblk, kSphThreads, 0, st>>>(a);
+  else k_sph_accel<false, STEP, false><<<nblk, kSphThreads, 0, st>>>(a);
+}
+
 }  // namespace
 
 size_t sph_workspace(int64_t n) {
@@ -315,15 +344,9 @@ int launch_sph_density(const BoxK &b, double h, double mass, double c0, double r
   a.rho = rho;
   a.partial = (double *)ws;
   const unsigned nblk = sph_blocks(n);
-  const bool wide = n > kNarrowAtoms;
   if (n > 0) {
-    if (u_total) {
-      if (wide) k_sph_density<true, true><<<nblk, kSphThreads, 0, st>>>(a);
-      else k_sph_density<false, true><<<nblk, kSphThreads, 0, st>>>(a);
-    } else {
-      if (wide) k_sph_density<true, false><<<nblk, kSphThreads, 0, st>>>(a);
-      else k_sph_density<false, false><<<nblk, kSphThreads, 0, st>>>(a);
-    }
+    if (u_total) launch_density<true>(a, nblk, st);
+    else launch_density<false>(a, nblk, st);
   }
   if (u_total)
     k_colsum<1024><<<1, 1024, 0, st>>>(n > 0 ? nblk : 0, 1, 1, a.partial, u_total, 1.0, 0);
@@ -347,14 +370,8 @@ int launch_sph_accel(const BoxK &b, double h, double mass, double c0, double rho
   if (n > 0) {
     k_sph_pack<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(a, (double4 *)ws);
     const unsigned nblk = sph_blocks(n);
-    const bool wide = n > kNarrowAtoms;
-    if (v) {
-      if (wide) k_sph_accel<true, true><<<nblk, kSphThreads, 0, st>>>(a);
-      else k_sph_accel<false, true><<<nblk, kSphThreads, 0, st>>>(a);
-    } else {
-      if (wide) k_sph_accel<true, false><<<nblk, kSphThreads, 0, st>>>(a);
-      else k_sph_accel<false, false><<<nblk, kSphThreads, 0, st>>>(a);
-    }
+    if (v) launch_accel<true>(a, nblk, st);
+    else launch_accel<false>(a, nblk, st);
   }
   return check_launch(v ? "ljmd_sph_accel_step" : "ljmd_sph_accel");
 }

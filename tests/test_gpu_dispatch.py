@@ -326,3 +326,37 @@ def test_vjp_on_both_sides_of_the_short_row_line(dev, ntypes, prec):
     assert np.abs(gx - hx).max() <= 2 * 64 * u * np.abs(hx).max()
     assert np.abs(ge - he).max() <= 2 * 64 * n * u * np.abs(he).max()
     assert np.abs(gs - hs).max() <= 2 * 64 * n * u * np.abs(hs).max()
+
+
+@pytest.mark.parametrize("n", [1, 130, 3001])
+def test_gas_rows_bitwise_the_general_path(dev, n):
+    """Lists of small capacity leave out the gathers of absent slots (forces without energies
+    up to 20 and, with two types or more, 28 entries; SPH densities up to 24, accelerations
+    up to 28): bitwise the results over the same rows in a list of larger capacity."""
+    import torch
+    from paper_2109_09056_amd import ops
+    L = np.full(3, 60.0)
+    T, g = _t(dev), np.random.default_rng(n)
+    xs, _, ts, _, cs = ops.bin(L, 2.8, T(_ragged(n, L, n)), None, T(g.integers(0, 2, n), torch.int32))
+    lists = {}
+    for maxn in (20, 24, 28, 40):
+        nbr, nnbr, most = ops.build_neighbors(L, 2.8, ops.FULL, xs, cs, maxn)
+        assert int(most.item()) <= 20
+        lists[maxn] = (nbr, nnbr, maxn)
+    rho = T(g.uniform(0.5, 1.5, n))
+
+    def results(l):
+        out = []
+        for P in (ops.FP64, ops.MIXED):
+            for eps, sig in (([1.0], [0.4]), ([1.0, 0.9, 1.1], [0.4, 0.38, 0.42])):
+                out.append(ops.compute_forces(L, P, ops.FULL, 2.5, T(eps), T(sig), xs, ts, *l,
+                                              want_energy=False)[0])
+        out += ops.sph_density(L, 1.2, 1.0, 10.0, 1.0, xs, *l, want_energy=True)
+        out.append(ops.sph_accel(L, 1.2, 1.0, 10.0, 1.0, xs, rho, *l))
+        out += ops.sph_accel_step(L, 1.2, 1.0, 10.0, 1.0, xs.clone(), torch.ones_like(xs), rho, *l,
+                                  1e-3)
+        return out
+
+    want = results(lists[40])
+    for maxn in (20, 24, 28):
+        assert all(torch.equal(a, b) for a, b in zip(results(lists[maxn]), want)), maxn
