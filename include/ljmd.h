@@ -102,6 +102,10 @@ extern "C" {
 #define LJMD_OP_MD_CHAIN 10  /* ljmd_md_step_chained, ljmd_md_step_sums (two halves) */
 #define LJMD_OP_DISPLACEMENT 11 /* ljmd_max_displacement */
 #define LJMD_OP_BUILD_CSR 12    /* ljmd_build_neighbors_csr */
+/* the smallest workspaces that the same calls take: less memory, at some cost in time */
+#define LJMD_OP_MD_CHAIN_LEAST 13
+#define LJMD_OP_BUILD_CSR_LEAST 14
+#define LJMD_OP_SPME_LEAST 15
 #define LJMD_SPME_MAX_GRID 256 /* largest grid edge of ljmd_spme_recip */
 
 #define LJMD_MAX_TYPES 8
@@ -201,9 +205,9 @@ int ljmd_build_neighbors(const ljmd_box *box, double rlist, int kind, int64_t n,
  *            so a too-small cap is seen as offsets[n] > cap once the call
  *            completes (the caller builds again with cap >= offsets[n])
  *   ws       >= ljmd_workspace_bytes(LJMD_OP_BUILD_CSR, n, 0, 0), for one test of
- *            every candidate; with less, down to 4 n bytes rounded up to 256 plus
- *            ljmd_workspace_bytes(LJMD_OP_CSR, n, 0, 0), the candidates are tested in
- *            both passes (the same rows)
+ *            every candidate (about 132 bytes per atom); with less, down to
+ *            ljmd_workspace_bytes(LJMD_OP_BUILD_CSR_LEAST, n, 0, 0) (4 bytes per atom),
+ *            the candidates are tested in both passes (the same rows)
  * Other arguments and errors as in ljmd_build_neighbors.
  */
 int ljmd_build_neighbors_csr(const ljmd_box *box, double rlist, int kind, int64_t n,
@@ -377,9 +381,10 @@ int ljmd_md_step_noalloc(const ljmd_box *box, int precision, double rc, int32_t 
  *            other half is then not read).  The previous call must have had the
  *            same n and the other half, and must precede this one on the stream.
  *   ws       >= ljmd_workspace_bytes(LJMD_OP_MD_CHAIN, n, 0, ntypes), kept
- *            between the calls of a run, with the same ws_bytes in each (twice
- *            ljmd_workspace_bytes(LJMD_OP_FORCES, ...) is also accepted, with the
- *            same results; a small system then runs in fewer, larger blocks)
+ *            between the calls of a run, with the same ws_bytes in each
+ *            (ljmd_workspace_bytes(LJMD_OP_MD_CHAIN_LEAST, ...) is also accepted: a
+ *            small system then runs in fewer, larger blocks, with the same results but
+ *            for the order in which ev_prev is summed)
  * Other arguments as in ljmd_md_step.
  */
 int ljmd_md_step_chained(const ljmd_box *box, int precision, double rc, int32_t ntypes,
@@ -534,9 +539,10 @@ int ljmd_sph_accel_step(const ljmd_box *box, double h, double mass, double c0, d
  *   receives E_rec + E_self.  ws >= ljmd_workspace_bytes(LJMD_OP_SPME, n,
  *   K[0]*K[1]*K[2], 0), 32-byte aligned; it holds the real charge grid and its
  *   half-complex transform, and the particles sorted by grid tile with the tiles'
- *   boxes of charge.  A workspace without the tiles' part (18 bytes per grid
- *   point, 8 per 256 particles and 8 KB) is accepted too; the charge is then spread
- *   onto the grid directly, which takes longer.  The charge
+ *   boxes of charge.  A workspace without the tiles' part, ljmd_workspace_bytes(
+ *   LJMD_OP_SPME_LEAST, ...), less than half as large, is accepted too; the charge is
+ *   then spread onto the grid directly, which takes longer (order 8 always does, and so
+ *   does order 6 on fewer than 2^20 grid points).  The charge
  *   spreading uses FP64 atomic additions: results agree run to run to rounding,
  *   not bit for bit.
  *   alpha > 0; rc as for the other pair kernels (LJMD_EBOX if too large).

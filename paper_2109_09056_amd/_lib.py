@@ -18,7 +18,8 @@ FP64, MIXED = 0, 1
 FULL, HALF = 0, 1
 KICK_DRIFT, KICK, KINETIC, KICK_KICK_DRIFT = 0, 1, 2, 3
 (OP_BIN, OP_FORCES, OP_BACKWARD, OP_INTEGRATE, OP_LOSS, OP_CSR, OP_FORCES_CSR, OP_SPH,
- OP_EWALD_REAL, OP_SPME, OP_MD_CHAIN, OP_DISPLACEMENT, OP_BUILD_CSR) = range(13)
+ OP_EWALD_REAL, OP_SPME, OP_MD_CHAIN, OP_DISPLACEMENT, OP_BUILD_CSR, OP_MD_CHAIN_LEAST,
+ OP_BUILD_CSR_LEAST, OP_SPME_LEAST) = range(16)
 SPME_MAX_GRID = 256
 MAX_TYPES = 8
 TILE = 64

@@ -282,6 +282,9 @@ size_t ljmd_workspace_bytes(int op, int64_t n, int64_t ncells, int32_t ntypes) {
     case LJMD_OP_SPH: return sph_workspace(n);
     case LJMD_OP_EWALD_REAL: return ewald_real_workspace(n);
     case LJMD_OP_SPME: return spme_workspace(n, ncells > 0 ? ncells : 1);
+    case LJMD_OP_MD_CHAIN_LEAST: return 2 * force_workspace(n);
+    case LJMD_OP_BUILD_CSR_LEAST: return build_csr_min_workspace(n);
+    case LJMD_OP_SPME_LEAST: return spme_min_workspace(n, ncells > 0 ? ncells : 1);
     default: return 0;
   }
 }

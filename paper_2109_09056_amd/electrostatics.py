@@ -44,8 +44,9 @@ class ChargedLJSim(LJSim):
         self._ws_real = torch.empty(ops.workspace_bytes(ops.OP_EWALD_REAL, n), dtype=torch.uint8,
                                     device=dev)
         g = self.grid
-        self._ws_rec = torch.empty(ops.workspace_bytes(ops.OP_SPME, n, ncells=g[0] * g[1] * g[2]),
-                                   dtype=torch.uint8, device=dev)
+        self._ws_rec = torch.empty(
+            ops.workspace_bytes(ops.OP_SPME if self.order <= 6 else ops.OP_SPME_LEAST, n,
+                                ncells=g[0] * g[1] * g[2]), dtype=torch.uint8, device=dev)
         return super().load(x, v, types, ids)
 
     def rebuild(self):

@@ -16,9 +16,9 @@ from . import _lib
 from ._lib import (EBOX, EHIP, EINVAL, EWORKSPACE, FP64, FULL, HALF, KICK, KICK_DRIFT,  # noqa: F401
                    KICK_KICK_DRIFT, KINETIC,
                    MAX_TEAM, MAX_TYPES, MIXED, OP_BACKWARD, OP_BIN, OP_CSR, OP_FORCES,
-                   OP_BUILD_CSR, OP_DISPLACEMENT, OP_EWALD_REAL, OP_FORCES_CSR, OP_INTEGRATE,
-                   OP_LOSS, OP_MD_CHAIN,
-                   OP_SPH, OP_SPME,
+                   OP_BUILD_CSR, OP_BUILD_CSR_LEAST, OP_DISPLACEMENT, OP_EWALD_REAL,
+                   OP_FORCES_CSR, OP_INTEGRATE, OP_LOSS, OP_MD_CHAIN, OP_MD_CHAIN_LEAST,
+                   OP_SPH, OP_SPME, OP_SPME_LEAST,
                    SPME_MAX_GRID, TILE, LjmdError, make_box)
 
 
@@ -47,10 +47,15 @@ def _need(t, name, dtype, shape=None, device=None):
         raise ValueError(f"{name} has shape {tuple(t.shape)}, expected {tuple(shape)}")
 
 
-def _ws(op, n, device, ncells=0, ntypes=1, ws=None):
+def _ws(op, n, device, ncells=0, ntypes=1, ws=None, least=None):
+    """(workspace, its size for the call): ws if it is large enough, else a new one.  A
+    call with a smallest size (op `least`) takes any ws from there on as it is."""
     need = int(_lib.load().ljmd_workspace_bytes(op, n, ncells, ntypes))
     if ws is not None and ws.numel() >= need:
         return ws, need
+    if ws is not None and least is not None and \
+            ws.numel() >= int(_lib.load().ljmd_workspace_bytes(least, n, ncells, ntypes)):
+        return ws, ws.numel()
     return torch.empty(max(need, 8), dtype=torch.uint8, device=device), need
 
 
@@ -166,7 +171,7 @@ def build_neighbors_csr(L, rlist, kind, x, cell_start, cap=None, offsets=None, c
     if offsets is None:
         offsets = torch.empty(n + 1, dtype=torch.int64, device=dev)
     _need(offsets, "offsets", torch.int64, (n + 1,), dev)
-    ws, need = _ws(OP_BUILD_CSR, n, dev, ws=ws)
+    ws, need = _ws(OP_BUILD_CSR, n, dev, ws=ws, least=OP_BUILD_CSR_LEAST)
     b = make_box(L)
     guess = cap is None
     if guess:
@@ -330,21 +335,25 @@ def md_step(L, precision, rc, eps, sigma, x, types, nbr, nnbr, maxn, dt, mass, v
 
 
 def _chain_ws(n, ws, dev):
-    """Byte size of the OP_MD_CHAIN workspace, checked against ws: the rows of a run
-    live there between calls, so a fresh one cannot be substituted."""
+    """Bytes of ws that a chained step uses: OP_MD_CHAIN, or all of a smaller ws down to
+    OP_MD_CHAIN_LEAST.  The rows of a run live there between calls, so a fresh one cannot
+    be substituted."""
     need = int(_lib.load().ljmd_workspace_bytes(OP_MD_CHAIN, n, 0, 1))
     if ws is None:
         raise ValueError("the chained steps need the workspace kept between the steps of a run")
     _need(ws, "ws", torch.uint8, None, dev)
+    if ws.numel() >= need:
+        return need
+    need = int(_lib.load().ljmd_workspace_bytes(OP_MD_CHAIN_LEAST, n, 0, 1))
     if ws.numel() < need:
         raise ValueError(f"ws holds {ws.numel()} bytes, {need} needed")
-    return need
+    return ws.numel()
 
 
 def md_step_chained(L, precision, rc, eps, sigma, x, types, nbr, nnbr, maxn, dt, mass, v, half,
                     ws, x_next=None, open_next=True, F=None, e_atom=None, ev_prev=None):
     """md_step whose energy/virial/KE partial rows stay in half `half` of ws (an
-    OP_MD_CHAIN workspace); its first workgroup sums the other half, left by the
+    OP_MD_CHAIN workspace); a workgroup of its own sums the other half, left by the
     previous chained step, into ev_prev when given.  Returns x_next."""
     n = x.shape[0]
     dev = x.device
@@ -655,7 +664,8 @@ def spme_recip(L, alpha, order, K, x, q, F=None, e_total=None, want_energy=False
     _need(F, "F", torch.float64, (n, 3), dev)
     _need(e_total, "e_total", torch.float64, (1,), dev)
     Kc = (ctypes.c_int32 * 3)(*[int(k) for k in K])
-    ws, need = _ws(OP_SPME, n, dev, ncells=int(K[0]) * int(K[1]) * int(K[2]), ws=ws)
+    ws, need = _ws(OP_SPME if order <= 6 else OP_SPME_LEAST, n, dev,
+                   ncells=int(K[0]) * int(K[1]) * int(K[2]), ws=ws, least=OP_SPME_LEAST)
     b = make_box(L)
     _lib.check(_lib.load().ljmd_spme_recip(
         ctypes.byref(b), float(alpha), int(order), Kc, n, _ptr(x), _ptr(q), _ptr(F),

@@ -360,3 +360,56 @@ def test_gas_rows_bitwise_the_general_path(dev, n):
     want = results(lists[40])
     for maxn in (20, 24, 28):
         assert all(torch.equal(a, b) for a, b in zip(results(lists[maxn]), want)), maxn
+
+
+@pytest.mark.parametrize("order", [4, 8])
+def test_smaller_workspaces_are_used_as_given(dev, order):
+    """Workspaces of the smallest sizes (the full ones of earlier versions) passed to the
+    Python calls: used, with nothing allocated in their place, to the same results; order 8,
+    which never uses the tiles, allocates no more than that by itself."""
+    import torch
+    from paper_2109_09056_amd import ops
+    n, L, K = 5000, np.full(3, 20.0), (32, 32, 32)
+    T, g = _t(dev), np.random.default_rng(order)
+    xs, _, ts, _, cs = ops.bin(L, 2.8, T(g.uniform(0, 1, (n, 3)) * L), None,
+                               torch.zeros(n, dtype=torch.int32, device=dev))
+    q = T(np.where(np.arange(n) % 2, 1.0, -1.0))
+    empty = lambda op, **kw: torch.empty(ops.workspace_bytes(op, n, **kw), dtype=torch.uint8,
+                                         device=dev)
+
+    def grown(f):
+        """f() and the bytes it had allocated at its peak beyond what it returns."""
+        torch.cuda.synchronize()
+        torch.cuda.reset_peak_memory_stats()
+        before = torch.cuda.memory_allocated()
+        out = f()
+        return out, torch.cuda.max_memory_allocated() - max(before, torch.cuda.memory_allocated())
+
+    F, e = torch.empty_like(xs), torch.empty(1, dtype=torch.float64, device=dev)
+    least = empty(ops.OP_SPME_LEAST, ncells=32 ** 3)
+    F0, _ = ops.spme_recip(L, 1.2, order, K, xs, q, want_energy=True)
+    (_, extra) = grown(lambda: ops.spme_recip(L, 1.2, order, K, xs, q, F=F, e_total=e, ws=least))
+    assert extra == 0
+    assert (F - F0).abs().max().item() <= 1e-11 * F0.abs().max().item()
+    (_, extra) = grown(lambda: ops.spme_recip(L, 1.2, order, K, xs, q, F=F, e_total=e))
+    assert (extra < 1.1 * least.numel()) == (order == 8)
+
+    off0, csr0 = ops.build_neighbors_csr(L, 2.8, ops.FULL, xs, cs)
+    off, csr = torch.empty_like(off0), torch.full_like(csr0, -7)
+    w = empty(ops.OP_BUILD_CSR_LEAST)
+    (_, extra) = grown(lambda: ops.build_neighbors_csr(L, 2.8, ops.FULL, xs, cs, cap=csr.numel(),
+                                                       offsets=off, csr=csr, ws=w))
+    m = int(off0[n].item())
+    assert extra == 0 and torch.equal(off, off0) and torch.equal(csr[:m], csr0[:m])
+
+    one = T([1.0])
+    nbr, nnbr, maxn = ops.build_neighbors(L, 2.8, ops.FULL, xs, cs, 200)[:2] + (200,)
+    got = []
+    for op in (ops.OP_MD_CHAIN, ops.OP_MD_CHAIN_LEAST):
+        w, v = empty(op), torch.zeros_like(xs)
+        x1 = ops.md_step_chained(L, ops.FP64, 2.5, one, T([0.3]), xs, ts, nbr, nnbr, maxn, 1e-4,
+                                 1.0, v, 0, w)
+        got.append((x1, v, ops.md_step_sums(n, 0, w)))
+    assert all(torch.equal(a, b) for a, b in zip(*got))
+    with pytest.raises(ValueError):
+        ops.md_step_sums(n, 0, empty(ops.OP_MD_CHAIN_LEAST)[:-8])
