@@ -206,6 +206,7 @@ class LJSim:
         return self
 
     DISP_HISTORY = 4096
+    MAX_WINDOW = 16384  # steps issued by one native call
 
     def _check_displacement(self):
         """Largest squared displacement since the last build, into the device history."""
@@ -368,8 +369,10 @@ class LJSim:
             if self.step_count % self.rebuild_every == 0:
                 self.rebuild()
             if run_native:
-                # up to the next rebuild or the end, issued by one call
-                k = min(self.rebuild_every - self.step_count % self.rebuild_every, nsteps - s)
+                # up to the next rebuild or the end, issued by one call (long runs without
+                # rebuilds in pieces, so that the interpreter sees interrupts)
+                every = abs(self.rebuild_every)  # a negative cadence is its absolute value
+                k = min(every - self.step_count % every, nsteps - s, self.MAX_WINDOW)
                 last = s + k == nsteps
                 half, prev = (0, False) if half is None else (1 - half, True)
                 self.x, self.xn = ops.md_steps(

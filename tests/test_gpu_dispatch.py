@@ -413,3 +413,23 @@ def test_smaller_workspaces_are_used_as_given(dev, order):
     assert all(torch.equal(a, b) for a, b in zip(*got))
     with pytest.raises(ValueError):
         ops.md_step_sums(n, 0, empty(ops.OP_MD_CHAIN_LEAST)[:-8])
+
+
+def test_windows_of_any_cadence(dev, monkeypatch):
+    """A negative cadence rebuilds as its absolute value does, and windows cut into pieces
+    give bitwise the run in whole ones."""
+    import torch
+    from paper_2109_09056_amd import md
+    w = li.Workload("t", 11, cells=4)
+    s = li.make_system(w)
+    out = []
+    for every, most in ((7, 16384), (-7, 16384), (7, 3)):
+        monkeypatch.setattr(md.LJSim, "MAX_WINDOW", most, raising=False)
+        sim = md.LJSim(w.box, rebuild_every=every, device=dev)
+        sim.load(s["x"], s["v"])
+        sim.step(25)
+        sim.step(4)
+        out.append((sim.x, sim.v, sim.F, sim.ids, sim.ev, torch.tensor(sim.nl.builds),
+                    torch.tensor(sim.step_count)))
+    for other in out[1:]:
+        assert all(torch.equal(a, b) for a, b in zip(out[0], other))
