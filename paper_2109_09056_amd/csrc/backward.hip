@@ -123,6 +123,8 @@ __global__ __launch_bounds__(kThreads * TEAM) void k_vjp(BwdArgs a) {
   __shared__ double acc[TT == 0 ? kThreads * 2 * MT : 1];
   __shared__ int32_t tid_type[TT == 0 ? kThreads : 1];
   const int T = TT == 0 ? a.ntypes : TT;
+  const int blk = flat_block<WIDE>(), nblk = flat_blocks<WIDE>(a.n, kThreads);
+  if (WIDE && blk >= nblk) return;
   if constexpr (TT != 1) {
     for (int q = threadIdx.x; q < T * T; q += kThreads * TEAM) {
       const BCoef c = bcoef(a.eps, a.sig, packed_index(q / T, q % T, T));
@@ -138,7 +140,7 @@ __global__ __launch_bounds__(kThreads * TEAM) void k_vjp(BwdArgs a) {
   if constexpr (TT == 1) c1 = bcoef(a.eps, a.sig, 0);
 
   const int tm = (int)threadIdx.x % TEAM;
-  const int32_t i = xcd_block(blockIdx.x, gridDim.x) * kThreads + (int)threadIdx.x / TEAM;
+  const int32_t i = xcd_block(blk, nblk) * kThreads + (int)threadIdx.x / TEAM;
   double ge[TT == 0 ? 1 : TT], gs[TT == 0 ? 1 : TT];
 #pragma unroll
   for (int q = 0; q < (TT == 0 ? 1 : TT); ++q) ge[q] = gs[q] = 0.0;
@@ -275,7 +277,7 @@ __global__ __launch_bounds__(kThreads * TEAM) void k_vjp(BwdArgs a) {
     }
   }
   // per-block sums G[which][ti][tj] in a fixed order
-  double *out = a.partial + (int64_t)blockIdx.x * a.stride;
+  double *out = a.partial + (int64_t)blk * a.stride;
   if constexpr (TT == 1) {
     const double v[2] = {ge[0], gs[0]};
     block_sum<NW, 2>(v, red, out);
@@ -378,7 +380,8 @@ int launch_backward(const BoxK &b, int precision, double rc, int32_t ntypes, con
     if (n <= kNarrowAtoms)                                                   \
       k_vjp<M, TT, false, TEAM><<<nblk, kThreads * TEAM, 0, st>>>(a);       \
     else                                                                     \
-      k_vjp<M, TT, true, TEAM><<<nblk, kThreads * TEAM, 0, st>>>(a);        \
+      k_vjp<M, TT, true, TEAM>                                               \
+          <<<wide_grid(nblk, kThreads * TEAM), kThreads * TEAM, 0, st>>>(a);   \
   } while (0)
   const bool few = maxn <= kShortRow && n > kShortAtoms;
   if (ntypes == 1 && few) {

@@ -291,6 +291,23 @@ __device__ __forceinline__ int xcd_block(int b, int nblk) {
   return x * q + (x < r ? x : r) + k;
 }
 
+// A launch takes fewer than 2^32 threads per grid dimension: kernels for systems of any size
+// (WIDE) get their blocks in rows (wide_grid).  A block's number and the number of blocks for
+// n atoms, `per` of them each; the last row's spare blocks have numbers beyond and leave.
+template <bool WIDE>
+__device__ __forceinline__ int flat_block() {
+  return WIDE ? (int)(blockIdx.y * gridDim.x + blockIdx.x) : (int)blockIdx.x;
+}
+template <bool WIDE>
+__device__ __forceinline__ int flat_blocks(int32_t n, int per) {
+  return WIDE ? (int)(((int64_t)n + per - 1) / per) : (int)gridDim.x;
+}
+inline dim3 wide_grid(int64_t nblk, int threads) {
+  const int64_t row = (((int64_t)1 << 32) - 1) / threads, rows = (nblk + row - 1) / row;
+  return rows <= 1 ? dim3((unsigned)nblk)
+                   : dim3((unsigned)((nblk + rows - 1) / rows), (unsigned)rows);
+}
+
 // Packed upper-triangle index of the type pair (a, b).
 __host__ __device__ __forceinline__ int packed_index(int a, int b, int T) {
   if (a > b) {

@@ -372,7 +372,9 @@ __global__ __launch_bounds__(ATOMS * kTeam) void k_force_full(ForceArgs a) {
   constexpr int kThreads = ATOMS * kTeam;
   __shared__ double tab[T1 ? 4 : 4 * LJMD_MAX_TYPES * LJMD_MAX_TYPES];
   __shared__ double red[kRedRows * (kThreads / kWave) * 8];
-  int nblk = gridDim.x, blk = blockIdx.x;
+  int nblk = flat_blocks<WIDE>(a.n, ATOMS) + (WIDE && STEP && a.prev_ev ? 1 : 0);
+  int blk = flat_block<WIDE>();
+  if (WIDE && blk >= nblk) return;
   if constexpr (STEP) {
     // chained steps: the previous launch's partial rows are complete (stream
     // order); a block of its own, dispatched first, sums them
@@ -633,6 +635,8 @@ __global__ __launch_bounds__(ATOMS * TEAM) void k_force_half(ForceArgs a) {
     s.slot[q] = -1;
   }
   if (threadIdx.x == 0) s.count = 0;
+  const int blk = flat_block<WIDE>(), nblk = flat_blocks<WIDE>(a.n, ATOMS);
+  if (WIDE && blk >= nblk) return;
   Coef c1{};
   if constexpr (T1) {
     c1 = coef_of(a.eps, a.sig, 0);
@@ -641,7 +645,7 @@ __global__ __launch_bounds__(ATOMS * TEAM) void k_force_half(ForceArgs a) {
   }
   __syncthreads();
   const int t = (int)threadIdx.x % TEAM;
-  const int32_t i = xcd_block(blockIdx.x, gridDim.x) * ATOMS + (int)threadIdx.x / TEAM;
+  const int32_t i = xcd_block(blk, nblk) * ATOMS + (int)threadIdx.x / TEAM;
   const bool live = i < a.n;
   double xi = 0.0, yi = 0.0, zi = 0.0;
   if (live) {
@@ -708,7 +712,7 @@ __global__ __launch_bounds__(ATOMS * TEAM) void k_force_half(ForceArgs a) {
   }
   if constexpr (EV) {
     const double v[7] = {e_lane, r.wxx, r.wyy, r.wzz, r.wxy, r.wxz, r.wyz};
-    block_sum<kWaves, 7>(v, red, a.partial + (int64_t)blockIdx.x * kEvStride);
+    block_sum<kWaves, 7>(v, red, a.partial + (int64_t)blk * kEvStride);
   }
 }
 
@@ -871,7 +875,7 @@ void launch_half(const ForceArgs &a, hipStream_t st) {
         <<<nb, kHalfAtoms * kHalfTeam, 0, st>>>(a);
   else
     k_force_half<MIXED, T1, EV, EATOM, true, kHalfAtoms, kHalfSlots, U>
-        <<<nb, kHalfAtoms * kHalfTeam, 0, st>>>(a);
+        <<<wide_grid(nb, kHalfAtoms * kHalfTeam), kHalfAtoms * kHalfTeam, 0, st>>>(a);
 }
 
 // Forces without energies over rows of at most this many entries leave out the gathers of
@@ -889,8 +893,9 @@ void launch_full(const ForceArgs &a, int atoms, hipStream_t st) {
   if (V == 1 && a.n > kNarrowAtoms) {
     if constexpr (V == 1)
       k_force_full<MIXED, T1, EV, STEP, true, kForceAtoms>
-          <<<blocks_of(a.n, kForceAtoms) + (STEP && a.prev_ev ? 1 : 0), kForceAtoms * kTeam, 0,
-             st>>>(a);
+          <<<wide_grid(blocks_of(a.n, kForceAtoms) + (STEP && a.prev_ev ? 1 : 0),
+                       kForceAtoms * kTeam),
+             kForceAtoms * kTeam, 0, st>>>(a);
   } else if (atoms == kForceAtoms) {
     k_force_full<MIXED, T1, EV, STEP, false, kForceAtoms, V>
         <<<nblk, kForceAtoms * kTeam, 0, st>>>(a);

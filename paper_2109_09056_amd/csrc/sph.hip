@@ -158,8 +158,10 @@ __device__ __forceinline__ double density_row(const SphArgs &a, const int32_t *r
 template <bool WIDE, bool WANT_U, bool GAS>
 __global__ __launch_bounds__(kSphThreads) void k_sph_density(SphArgs a) {
   __shared__ double red[kRedRows * kSphWaves];
+  const int blk = flat_block<WIDE>(), nblk = flat_blocks<WIDE>(a.n, kSphAtoms);
+  if (WIDE && blk >= nblk) return;
   const int t = (int)threadIdx.x % kSphTeam;
-  const int32_t i = xcd_block(blockIdx.x, gridDim.x) * kSphAtoms + (int)threadIdx.x / kSphTeam;
+  const int32_t i = xcd_block(blk, nblk) * kSphAtoms + (int)threadIdx.x / kSphTeam;
   const bool live = i < a.n;
   double xi = 0.0, yi = 0.0, zi = 0.0;
   if (live) {
@@ -190,7 +192,7 @@ __global__ __launch_bounds__(kSphThreads) void k_sph_density(SphArgs a) {
     double u[1] = {0.0};
     if (live && t == 0)
       u[0] = a.mass * a.c0sq * (log(rho / a.rho0) + a.rho0 / rho - 1.0);
-    block_sum<kSphWaves, 1>(u, red, a.partial + blockIdx.x);
+    block_sum<kSphWaves, 1>(u, red, a.partial + blk);
   }
 }
 
@@ -246,8 +248,10 @@ __device__ __forceinline__ void accel_row(const SphArgs &a, const int32_t *row, 
 // integrator's fused kick-kick-drift (unit mass: the acceleration is F/m).
 template <bool WIDE, bool STEP, bool GAS>
 __global__ __launch_bounds__(kSphThreads) void k_sph_accel(SphArgs a) {
+  const int blk = flat_block<WIDE>(), nblk = flat_blocks<WIDE>(a.n, kSphAtoms);
+  if (WIDE && blk >= nblk) return;
   const int t = (int)threadIdx.x % kSphTeam;
-  const int32_t i = xcd_block(blockIdx.x, gridDim.x) * kSphAtoms + (int)threadIdx.x / kSphTeam;
+  const int32_t i = xcd_block(blk, nblk) * kSphAtoms + (int)threadIdx.x / kSphTeam;
   const bool live = i < a.n;
   double4 me = make_double4(0.0, 0.0, 0.0, 0.0);
   if (live) me = a.xp[i];
@@ -316,7 +320,9 @@ SphArgs make_args(const BoxK &b, double h, double mass, double c0, double rho0, 
 
 template <bool WANT_U>
 void launch_density(const SphArgs &a, unsigned nblk, hipStream_t st) {
-  if (a.n > kNarrowAtoms) k_sph_density<true, WANT_U, false><<<nblk, kSphThreads, 0, st>>>(a);
+  if (a.n > kNarrowAtoms)
+    k_sph_density<true, WANT_U, false>
+        <<<wide_grid(nblk, kSphThreads), kSphThreads, 0, st>>>(a);
   else if (a.maxn <= kGasRowDensity)
     k_sph_density<false, WANT_U, true><<<nblk, kSphThreads, 0, st>>>(a);
   else k_sph_density<false, WANT_U, false><<<nblk, kSphThreads, 0, st>>>(a);
@@ -324,7 +330,8 @@ void launch_density(const SphArgs &a, unsigned nblk, hipStream_t st) {
 
 template <bool STEP>
 void launch_accel(const SphArgs &a, unsigned nblk, hipStream_t st) {
-  if (a.n > kNarrowAtoms) k_sph_accel<true, STEP, false><<<nblk, kSphThreads, 0, st>>>(a);
+  if (a.n > kNarrowAtoms)
+    k_sph_accel<true, STEP, false><<<wide_grid(nblk, kSphThreads), kSphThreads, 0, st>>>(a);
   else if (a.maxn <= kGasRow) k_sph_accel<false, STEP, true><<<nblk, kSphThreads, 0, st>>>(a);
   else k_sph_accel<false, STEP, false><<<nblk, kSphThreads, 0, st>>>(a);
 }

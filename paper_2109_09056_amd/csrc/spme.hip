@@ -261,10 +261,12 @@ __global__ __launch_bounds__(kEwThreads) void k_ewald_real(RealArgs a) {
   __shared__ double red[kRedRows * kEwThreads / kWave];
   __shared__ __align__(16) double
       tab[TABLE ? kErfcIntervals * kErfcStride : kErfcxIntervals * kErfcxStride];
+  const int blk = flat_block<WIDE>(), nblk = flat_blocks<WIDE>(a.n, kEwAtoms);
+  if (WIDE && blk >= nblk) return;
   erfc_tables<TABLE>(a, tab);
   __syncthreads();
   const int t = (int)threadIdx.x % kEwTeam;
-  const int32_t i = xcd_block(blockIdx.x, gridDim.x) * kEwAtoms + (int)threadIdx.x / kEwTeam;
+  const int32_t i = xcd_block(blk, nblk) * kEwAtoms + (int)threadIdx.x / kEwTeam;
   const bool live = i < a.n;
   double4 me = make_double4(0.0, 0.0, 0.0, 0.0);
   if (live) me = a.xq[i];
@@ -293,7 +295,7 @@ __global__ __launch_bounds__(kEwThreads) void k_ewald_real(RealArgs a) {
   }
   if constexpr (EV) {
     double v[1] = {live ? 0.5 * me.w * e : 0.0};  // per lane: the team's lanes add up
-    block_sum<kEwThreads / kWave, 1>(v, red, a.partial + blockIdx.x);
+    block_sum<kEwThreads / kWave, 1>(v, red, a.partial + blk);
   }
 }
 
@@ -1487,7 +1489,8 @@ int launch_ewald_real(const BoxK &b, double alpha, double rc, int64_t n, const d
     else k_pack_xq<false><<<npack, kThreads, 0, st>>>(a, x, q, (double4 *)ws, seeds);
     const bool wide = n > kNarrowAtoms;
 #define LJMD_REAL(EV, TABLE)                                                       \
-  wide ? k_ewald_real<true, EV, TABLE><<<nblk, kEwThreads, 0, st>>>(a)             \
+  wide ? k_ewald_real<true, EV, TABLE>                                             \
+             <<<wide_grid(nblk, kEwThreads), kEwThreads, 0, st>>>(a)               \
        : k_ewald_real<false, EV, TABLE><<<nblk, kEwThreads, 0, st>>>(a)
     if (e_total) LJMD_REAL(true, false);
     else if (table) LJMD_REAL(false, true);

@@ -433,3 +433,93 @@ def test_windows_of_any_cadence(dev, monkeypatch):
                     torch.tensor(sim.step_count)))
     for other in out[1:]:
         assert all(torch.equal(a, b) for a, b in zip(out[0], other))
+
+
+def test_more_than_2_to_the_30_particles(dev):
+    """2^30 + 65 particles, whose four lanes each are more threads than one grid dimension
+    takes: two close pairs, at the first and the last indices, everything else far from any
+    list entry.  Forces over full and half lists, their adjoint, SPH densities and
+    accelerations, Ewald real space: the pairs' values, and zeros (the kernel's own term for
+    densities) in all others.  Needs 130 GB of device memory."""
+    import torch
+    from paper_2109_09056_amd import _lib
+    if torch.cuda.mem_get_info(dev)[0] + torch.cuda.memory_reserved(dev) < 150e9:
+        pytest.skip("not enough free device memory")
+    torch.cuda.empty_cache()
+    n, L = (1 << 30) + 65, np.full(3, 20.0)
+    lib, p = _lib.load(), lambda t: None if t is None else t.data_ptr()
+    box, st = _lib.make_box(L), torch.cuda.current_stream(dev).cuda_stream
+    z = lambda *s, d=torch.float64: torch.zeros(*s, dtype=d, device=dev)
+    pairs = torch.tensor([[0, 1], [n - 2, n - 1]], device=dev)
+    tiles = (n + 63) // 64
+    nbr, nnbr = z(tiles * 64, d=torch.int32), z(n, d=torch.int32)
+    x = z(n, 3)
+    x[pairs[:, 0]] = 5.0
+    x[pairs[:, 1]] = 6.1
+    one = torch.ones(1, dtype=torch.float64, device=dev)
+    i, j = pairs[:, 0], pairs[:, 1]
+    both = torch.cat([i, j])
+
+    def lists(half):
+        nnbr.zero_()
+        nnbr[i] = 1
+        nbr[i] = j.to(torch.int32)  # capacity 1: entry 0 of row r is nbr[r]
+        nnbr[j] = 0 if half else 1
+        nbr[j] = i.to(torch.int32)
+
+    def only(t):
+        """t's rows of the two pairs; the others must hold nothing."""
+        rows = t[both].clone()
+        t[both] = 0.0
+        lo, hi = t.aminmax()
+        assert lo.item() == 0.0 and hi.item() == 0.0
+        return rows.cpu().numpy()
+
+    d = np.array([[-1.1] * 3] * 2 + [[1.1] * 3] * 2)
+    r2 = (d * d).sum(1, keepdims=True)
+    lj = 24.0 / r2 * (2.0 / r2 ** 6 - 1.0 / r2 ** 3) * d
+    out = torch.full((n, 3), -1.0, dtype=torch.float64, device=dev)
+    for half in (False, True):
+        lists(half)
+        _lib.check(lib.ljmd_compute_forces(box, _lib.FP64, int(half), 2.5, 1, p(one), p(one), n, p(x),
+                                           None, p(nbr), p(nnbr), 1, p(out), None, None, None, 0,
+                                           st), "forces")
+        assert np.abs(only(out) - lj).max() <= 1e-13 * np.abs(lj).max()
+    lists(False)
+
+    ws = torch.empty(36 << 30, dtype=torch.uint8, device=dev)
+    g = z(n, 3)
+    g[i] = 1.0
+    ge, gs = z(1), z(1)
+    _lib.check(lib.ljmd_force_backward(box, _lib.FP64, 2.5, 1, p(one), p(one), n, p(x), None, p(nbr),
+                                       p(nnbr), 1, p(g), p(out), p(ge), p(gs), 0, p(ws), ws.numel(),
+                                       st), "backward")
+    gx = only(out)
+    assert np.abs(gx[:2]).min() > 0 and np.abs(gx[:2] + gx[2:]).max() <= 1e-13 * np.abs(gx).max()
+    assert ge.item() == pytest.approx(lj[:2].sum(), rel=1e-12)  # F is linear in eps = 1
+    del g
+    torch.cuda.empty_cache()
+
+    rho = z(n)
+    h, m = 1.2, 1.0
+    _lib.check(lib.ljmd_sph_density(box, h, m, 1.0, 1.0, n, p(x), p(nbr), p(nnbr), 1, p(rho), None,
+                                    None, 0, st), "density")
+    alone = m / (np.pi * h ** 3)
+    near = rho[both].cpu().numpy()
+    assert (near > alone * 1.01).all() and np.ptp(near) <= 1e-13 * alone
+    rho[both] = rho[2].item()
+    lo, hi = rho.aminmax()
+    assert lo.item() == hi.item() == pytest.approx(alone, rel=1e-14)
+    rho.fill_(2.0)
+    _lib.check(lib.ljmd_sph_accel(box, h, m, 1.0, 1.0, n, p(x), p(rho), p(nbr), p(nnbr), 1, p(out),
+                                  p(ws), ws.numel(), st), "accel")
+    acc = only(out)
+    assert np.abs(acc[:2]).min() > 0 and np.abs(acc[:2] + acc[2:]).max() <= 1e-13 * np.abs(acc).max()
+    q = rho  # charges of 2
+    for e in (None, one):
+        _lib.check(lib.ljmd_ewald_real(box, 1.0, 2.5, n, p(x), p(q), p(nbr), p(nnbr), 1, p(out),
+                                       p(e), 0, p(ws), ws.numel(), st), "ewald")
+        f = only(out)
+        assert np.abs(f[:2]).min() > 0 and np.abs(f[:2] + f[2:]).max() <= 1e-13 * np.abs(f).max()
+    del x, out, ws, rho, q, nbr, nnbr
+    torch.cuda.empty_cache()
