@@ -344,14 +344,14 @@ def traversal_study(w, sim, reps=50):
     out["build_csr_direct_us"] = round(event_time(lambda: ops.build_neighbors_csr(
         w.box, sim.rlist, ops.FULL, sim.x, sim.cell_start, cap=csr2.numel(), offsets=off2,
         csr=csr2, ws=wsb), reps) * 1e3, 2)
-    out["tiled_team2_us"] = round(event_time(lambda: ops.compute_forces(
+    out["tiled_team4_us"] = round(event_time(lambda: ops.compute_forces(
         w.box, ops.MIXED, ops.FULL, w.rc, sim.eps, sim.sigma, sim.x, sim.types, nl.nbr,
         nl.nnbr, nl.maxn, F=F, e_atom=e, ev=ev, ws=sim._ws[ops.OP_FORCES]), reps) * 1e3, 2)
     for team in (1, 2, 4, 8, 16):
         out[f"csr_team{team}_us"] = round(event_time(lambda: ops.compute_forces_csr(
             w.box, ops.MIXED, w.rc, sim.eps, sim.sigma, sim.x, sim.types, off, csr, team=team,
             F=F, e_atom=e, ev=ev, ws=wsf), reps) * 1e3, 2)
-    # positions and forces in AoSoA(V) layouts (0: SoA) over the same tiled list, team 2
+    # positions and forces in AoSoA(V) layouts (0: SoA) over the same tiled list, team 4
     for vlen in (0, 8, 64):
         xa = ops.aosoa_convert(sim.x, vlen, True)
         Fa = torch.empty_like(xa)
@@ -368,7 +368,7 @@ def traversal_study(w, sim, reps=50):
             w.box, ops.MIXED, ops.HALF, w.rc, sim.eps, sim.sigma, sim.x, sim.types, hl.nbr,
             hl.nnbr, hl.maxn, F=F, e_atom=ea, ev=ev, ws=sim._ws[ops.OP_FORCES],
             atom_energy=ea is not None), reps) * 1e3, 2)
-    out["tiled_team2_forces_only_us"] = round(event_time(lambda: ops.compute_forces(
+    out["tiled_team4_forces_only_us"] = round(event_time(lambda: ops.compute_forces(
         w.box, ops.MIXED, ops.FULL, w.rc, sim.eps, sim.sigma, sim.x, sim.types, nl.nbr,
         nl.nnbr, nl.maxn, F=F, want_energy=False, ws=sim._ws[ops.OP_FORCES]), reps) * 1e3, 2)
     out["half_list_forces_only_us"] = round(event_time(lambda: ops.compute_forces(

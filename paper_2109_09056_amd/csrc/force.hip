@@ -64,7 +64,8 @@ struct ForceArgs {
   double *x_next;
   double dt, hdt, mass;
   int unit_mass, open_next;
-  // chained steps: block 0 also sums the previous step's partial rows into prev_ev
+  // chained steps: block 0, one more than the atoms', sums the previous step's partial rows
+  // into prev_ev
   const double *prev_partial;
   double *prev_ev;
   int64_t prev_rows;
@@ -264,7 +265,7 @@ __device__ __forceinline__ void load_pos(const double *x, int32_t j, int64_t n, 
 // Walk the lane's entries of atom i's row (every TEAM-th, row points at the first
 // of its cnt) in groups of U slots: the U index loads, then the U gathers of
 // position and type, then the U pair evaluations, so several loads are in flight
-// per lane.  Slots beyond cnt repeat the lane's first entry and are masked: one
+// per lane.  Slots beyond cnt repeat the group's first entry and are masked: one
 // copy of the group's code instead of a whole and a partial one (a short launch
 // spends most of its time fetching instructions).  GAS: their gathers are left out, as
 // they are most of the slots.  The type is gathered with the
@@ -302,29 +303,6 @@ __device__ __forceinline__ void walk_row(const ForceArgs &a, const int32_t *row,
   }
 }
 
-// TEAM lanes per atom: lane t of an atom's team walks the row entries t,
-// t + TEAM, ...; neighbouring entries of one row are mostly nearby atoms, so
-// the lanes of a team gather from nearby addresses and each gather instruction
-// touches fewer cache lines than with one lane per atom.  The team's force
-// and per-atom energy are combined by a butterfly over the team (both lanes
-// of every exchange add the same two numbers: every lane ends with the same,
-// order-fixed sum); energy and virial partials enter the block sum per lane.
-//
-// STEP: after the row, the team also finishes its atom's velocity-Verlet
-// step -- closing half kick (kinetic energy taken there), and when open_next
-// the next step's half kick, drift and wrap into x_next -- with exactly the
-// operations of ljmd_integrate, so the trajectory is bitwise the same as the
-// unfused calls; lane t < 3 handles component t (one pass of the code, its
-// velocity loaded ahead of the row).  Partial rows then carry the kinetic energy
-// in column 7.
-//
-// What bounds it: at 500,000 atoms the two gather instructions per list entry
-// (texture address unit); below about 30,000 atoms a launch is mostly
-// instruction-fetch and memory latency, so code executed once per block counts.
-// Fused step per launch, with two lanes per atom in whole and partial groups,
-// sums through ds_bpermute and the previous step's sums in block 0 -> now (us):
-// 256 atoms FP64 11.4 -> 6.7, 32,000 mixed 11.9 -> 9.0, 42,592 mixed 16.9 ->
-// 11.3, 256,000 two types FP64 71.4 -> 55.9, 500,000 mixed 89.5 -> 83.5.
 // Column sums of `rows` partial rows of kEvStride doubles by the THREADS threads
 // of one block, out[q] = sum_r p[r*kEvStride + q] for q < kEvStride: thread t
 // reads the flat array at t, t + THREADS, ... (column t % kEvStride), the lanes
@@ -361,10 +339,35 @@ __device__ void block_colsum(const double *__restrict__ p, int64_t rows, double 
   }
 }
 
+// TEAM lanes per atom: lane t of an atom's team walks the row entries t,
+// t + TEAM, ...; neighbouring entries of one row are mostly nearby atoms, so
+// the lanes of a team gather from nearby addresses and each gather instruction
+// touches fewer cache lines than with one lane per atom.  The team's force
+// and per-atom energy are combined by a butterfly over the team (both lanes
+// of every exchange add the same two numbers: every lane ends with the same,
+// order-fixed sum); energy and virial partials enter the block sum per lane.
+//
+// STEP: after the row, the team also finishes its atom's velocity-Verlet
+// step -- closing half kick (kinetic energy taken there), and when open_next
+// the next step's half kick, drift and wrap into x_next -- with exactly the
+// operations of ljmd_integrate, so the trajectory is bitwise the same as the
+// unfused calls; lane t < 3 handles component t (one pass of the code, its
+// velocity loaded ahead of the row).  Partial rows then carry the kinetic energy
+// in column 7.
+//
+// What bounds it: at 500,000 atoms the two gather instructions per list entry
+// (texture address unit); below about 30,000 atoms a launch is mostly
+// instruction-fetch and memory latency, so code executed once per block counts.
+// Fused step per launch, with two lanes per atom in whole and partial groups,
+// sums through ds_bpermute and the previous step's sums in block 0 -> now (us):
+// 256 atoms FP64 11.4 -> 6.7, 32,000 mixed 11.9 -> 9.0, 42,592 mixed 16.9 ->
+// 11.3, 256,000 two types FP64 71.4 -> 55.9, 500,000 mixed 89.5 -> 83.5.
 //
 // Rows of partial sums stand in the order of the atoms (row = logical block), and
 // a 128-atom block adds its two 64-atom halves last: its row is bitwise the sum of
-// the two rows of 64-atom blocks, so the block size never shows in a result.
+// the two rows of 64-atom blocks, so the block size does not show in the sums that
+// launch_md_step_sums forms.  block_colsum, by the threads of one block and not in
+// pairs of rows, adds in an order of its own for either size: its sums agree to rounding.
 template <bool MIXED, bool T1, bool EV, bool STEP, bool WIDE, int ATOMS, int V = 1, bool GAS = false>
 __global__ __launch_bounds__(ATOMS * kTeam) void k_force_full(ForceArgs a) {
   static_assert(!STEP || V == 1, "the fused step works on [n][3] arrays");
@@ -729,7 +732,9 @@ __global__ __launch_bounds__(ATOMS * TEAM) void k_force_half(ForceArgs a) {
 // Each lane walks its entries in row order, as k_force_full does: with its team
 // of four the two kernels give bitwise the same forces and per-atom energies, and so
 // does a team of two, whose lanes keep their even and their odd entries -- the
-// entries of two of the four lanes -- apart.
+// entries of two of the four lanes -- apart (callers rely on it above 32,768 atoms from
+// when the tiled kernel had two lanes there; the second accumulators cost nothing
+// measurable: 500,000 atoms 105.2 us without energies, before 105.2).
 template <bool MIXED, bool T1, bool EV, int TEAM, int U, bool WIDE>
 __global__ __launch_bounds__(kCsrThreads) void k_force_csr(ForceArgs a,
                                                             const int64_t *__restrict__ off,
@@ -833,13 +838,17 @@ constexpr int kCsrTeamUnroll = 4;
 
 // Full-list blocks of 64 atoms where the launch writes no partial rows (forces
 // only) or, up to this size, where the workspace holds two rows per 128 atoms
-// (chained steps); else 128.  Smaller blocks spread a mid-size grid more evenly
-// over the compute units: fused step, 128 -> 64 atoms per block (us), 256 atoms
-// 8.6 -> 6.7, 32,000 9.3 -> 9.0, 42,592 13.6 -> 11.3, 70,304 (two types) 24.7 ->
-// 21.6, 110,447 (two types) 31.6 -> 30.2, 131,072 25.8 -> 26.6; forces only at
-// 500,000 atoms 73.0 -> 71.0, with their own column sum over twice the rows 82.0 ->
-// 83.4.
-constexpr int64_t kSmallBlockAtoms = 114688;
+// (chained steps); else 128.  131,072 atoms are one round of resident 128-atom blocks, four
+// per compute unit.  Well below that the units hold unequal numbers of blocks, which
+// smaller ones even out; where the round is nearly full (from 7/8 of it) or there are
+// several, nothing is gained, and a full round loses.  Fused step, 128 -> 64 atoms per
+// block (us), one type mixed / two types FP64: 256 atoms 8.6 -> 6.7 / -, 32,000 9.8 -> 9.7 /
+// 11.4 -> 11.2, 42,592 13.8 -> 11.7 / 17.2 -> 14.1, 62,500 15.1 -> 14.8 / 18.1 -> 17.9, 70,304 20.1 ->
+// 17.3 / 24.4 -> 21.6, 87,808 20.8 -> 20.9 / 25.2 -> 25.3, 110,592 26.6 -> 26.3 / 31.7 -> 30.8,
+// 131,072 26.1 -> 27.4 / 31.9 -> 33.7, 157,216 30.7 -> 30.0 / 37.6 -> 37.5, 256,000 44.7 -> 44.5 / 56.0
+// -> 56.1; forces only at 500,000 atoms 73.0 -> 71.0, with their own column sum over twice
+// the rows 82.0 -> 83.4.
+constexpr int64_t kSmallBlockAtoms = 7 * 131072 / 8;
 
 // Half-list blocks: 128 home atoms with four lanes each and 32 tile slots; up to
 // LJMD_SMALL_GRID_ATOMS atoms (one block per compute unit) eight lanes each and 48
