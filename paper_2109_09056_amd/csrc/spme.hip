@@ -508,8 +508,7 @@ __global__ __launch_bounds__(kThreads) void k_tile_scatter(int32_t n, TileK tk) 
 // kOrderTiles tiles: every block scans all counts (four per thread) into LDS, block 0
 // also writes them.  The
 // whole reciprocal call, replayed from a graph (us): 32,000 particles and 64^3 47.1 ->
-// 45.7, 500,000 and 128^3 120.9 -> 120.6; launched one by one, 20 steps of a charged
-// liquid of 32,000 particles 1,723 -> 1,573.
+// 45.7, 500,000 and 128^3 120.9 -> 120.6.
 constexpr int kOrderThreads = 1024;
 constexpr int kOrderTiles = 4 * kOrderThreads;
 __global__ __launch_bounds__(kOrderThreads) void k_tile_order(int32_t n, TileK tk) {
